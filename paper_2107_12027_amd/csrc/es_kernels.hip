@@ -652,14 +652,19 @@ __global__ void k_temporal_metrics3d(GridDev g, const double* __restrict__ xd, d
 // ---------------------------------------------------------------------------
 constexpr int LINES = 4;           // line segments (wavefronts) per block
 
-template <int DIM, int PO>
+template <int DIM, int PO, bool STASH>
 struct ResidualLDS {
     static constexpr int NU = DIM, M = DIM + 2, NA = DIM + 1, NF = 6 + NU + NA;
     double sd[LINES][NF][seg_loads(PO) + 1];
-    // 3D: the flux differences of each lane wait here while the face dissipation
-    // runs (register pressure)
-    double rs[DIM == 3 ? LINES : 1][M + 1][64];
+    // the flux differences of each lane wait here while the face dissipation runs
+    // (register pressure)
+    double rs[STASH ? LINES : 1][STASH ? M + 1 : 1][64];
 };
+
+// Stashing the flux differences takes the FP64 dissipation from 194 to 128 registers in
+// 2D (two to four wavefronts per SIMD) and the 3D forms to three; the 2D FP32-mixed form
+// fits three without.
+__host__ __device__ constexpr bool residual_stash(int dim, bool es, bool mixed) { return es && (dim == 3 || !mixed); }
 
 // Orders the LDS accesses of one wavefront: its lanes exchange data only among
 // themselves (each wavefront owns its line of the LDS buffer), so no block
@@ -669,6 +674,18 @@ __device__ __forceinline__ void wave_lds_sync() {
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
+
+// Residual of all directions: logical blocks [0, nb0) sweep x, [nb0, nb0 + nb1)
+// sweep y, the rest z; direction k writes slab k of Ld (m + 1 components each).
+struct SweepPlan {
+    int nseg[3];          // segments per sequence (blocks of the sweep)
+    int nblk[3];          // blocks of the sweep
+    long long nlines[3];  // lines of the sweep
+    int flat[3];          // flat (1) or aligned (0) layout of the segments
+    int nsl[3];           // segments per line of the aligned layout
+    double idxi[3];       // 1 / dxi
+    double c0, c1;        // Gamma / (Gamma - 1), 1 / (Gamma - 1)
+};
 
 // One wavefront per segment of the lines along DIR: loads the segment with its
 // halo into LDS, evaluates the two-point fluxes owned by each node, the face
@@ -690,12 +707,15 @@ template <int DIM, int DIR, bool ES, bool MIXED, int PO>
 __device__ __forceinline__ void residual_segment(const GridDev& g, double G, double eps,
                                                  const double* __restrict__ prim,
                                                  const double* __restrict__ met,
-                                                 double* __restrict__ out, int blk, int nseg,
-                                                 long long nlines, bool flat, int nsl,
-                                                 ResidualLDS<DIM, PO>& lds) {
+                                                 double* __restrict__ out, int blk, const SweepPlan& sw,
+                                                 ResidualLDS<DIM, PO, residual_stash(DIM, ES, MIXED)>& lds) {
+    const int nseg = sw.nseg[DIR], nsl = sw.nsl[DIR];
+    const long long nlines = sw.nlines[DIR];
+    const bool flat = sw.flat[DIR] != 0;
     constexpr int NU = DIM, M = DIM + 2, NA = DIM + 1;
     constexpr int NGP = ghost_layers(PO), SEGP = seg_nodes(PO), NLOADP = seg_loads(PO);
-    constexpr int F_RHO = 0, F_P = 1, F_BETA = 2, F_W = 3, F_LR = 4, F_LB = 5, F_U = 6,
+    // F_V0: the first entropy variable, which the FP64 dissipation projects
+    constexpr int F_RHO = 0, F_V0 = 1, F_BETA = 2, F_W = 3, F_LR = 4, F_LB = 5, F_U = 6,
                   F_A = 6 + NU;
     auto& sd = lds.sd;
 
@@ -754,12 +774,13 @@ __device__ __forceinline__ void residual_segment(const GridDev& g, double G, dou
             u[c] = ok ? v[1 + c] : 0.0;
             uu += u[c] * u[c];
         }
+        const double beta = rho * frcp(p), lr = ok ? v[M] : 0.0, lb = ok ? v[M + 1] : 0.0;
         sd[line][F_RHO][q] = rho;
-        sd[line][F_P][q] = p;
-        sd[line][F_BETA][q] = rho * frcp(p);
+        if (ES && !MIXED) sd[line][F_V0][q] = sw.c0 + lr + lb * sw.c1 + beta;
+        sd[line][F_BETA][q] = beta;
         sd[line][F_W][q] = psqrt(1.0 + uu);
-        sd[line][F_LR][q] = ok ? v[M] : 0.0;
-        sd[line][F_LB][q] = ok ? v[M + 1] : 0.0;
+        sd[line][F_LR][q] = lr;
+        sd[line][F_LB][q] = lb;
 #pragma unroll
         for (int c = 0; c < NU; ++c) sd[line][F_U + c][q] = u[c];
 #pragma unroll
@@ -796,7 +817,6 @@ __device__ __forceinline__ void residual_segment(const GridDev& g, double G, dou
     auto node_at = [&](int q) {
         NodeRHD<NU> nd;
         nd.rho = sd[line][F_RHO][q];
-        nd.p = sd[line][F_P][q];
         nd.beta = sd[line][F_BETA][q];
         nd.W = sd[line][F_W][q];
         nd.lr = sd[line][F_LR][q];
@@ -809,7 +829,7 @@ __device__ __forceinline__ void residual_segment(const GridDev& g, double G, dou
     // ---- two-point fluxes (s, s+n), n = 1..p, owned by the lane of node s, and
     // flux differences R_s = -(1/dxi) sum_n alpha_n [F(s,s+n) - F(s-n,s)]
     const bool valid = active;
-    const double idxi = 1.0 / g.dxi[DIR];
+    const double idxi = sw.idxi[DIR];
     double R[M + 1];
 #pragma unroll
     for (int c = 0; c <= M; ++c) R[c] = 0.0;
@@ -845,7 +865,7 @@ __device__ __forceinline__ void residual_segment(const GridDev& g, double G, dou
     for (int c = 0; c <= M; ++c) R[c] = owner ? -R[c] * idxi : 0.0;
 
     if (ES) {
-        constexpr bool STASH = DIM == 3;
+        constexpr bool STASH = residual_stash(DIM, ES, MIXED);
         if (STASH) {
 #pragma unroll
             for (int c = 0; c <= M; ++c) lds.rs[line][c][lane] = R[c];
@@ -865,7 +885,6 @@ __device__ __forceinline__ void residual_segment(const GridDev& g, double G, dou
                     const int k = lane - (PO - 1) + q;
                     NodeRHD<NU, float> nd;
                     nd.rho = (float)sd[line][F_RHO][k];
-                    nd.p = (float)sd[line][F_P][k];
                     nd.beta = (float)sd[line][F_BETA][k];
                     nd.W = (float)sd[line][F_W][k];
                     nd.lr = (float)sd[line][F_LR][k];
@@ -881,15 +900,26 @@ __device__ __forceinline__ void residual_segment(const GridDev& g, double G, dou
                     ar[c] = (float)sd[line][F_A + c][lane + 1];
                 }
                 float df[M];
-                face_diss_rhd_fn<DIM, float, PO>((float)G, (float)eps, node_f, al, ar, df);
+                face_diss_rhd_gram<DIM, float, PO>((float)G, (float)eps, node_f, al, ar, df);
 #pragma unroll
                 for (int c = 0; c < M; ++c) d[c] = (double)df[c];
             } else {
                 double al[NA], ar[NA];
 #pragma unroll
                 for (int c = 0; c < NA; ++c) { al[c] = sd[line][F_A + c][lane]; ar[c] = sd[line][F_A + c][lane + 1]; }
-                face_diss_rhd_fn<DIM, double, PO>(G, eps, [&](int q) { return node_at(lane - (PO - 1) + q); }, al, ar,
-                                                  d);
+                face_diss_rhd_fn<DIM, double, PO>(
+                    G, sw.c0, sw.c1, eps,
+                    [&](int q) {
+                        const int k = lane - (PO - 1) + q;
+                        NodeV<NU> nd;
+                        nd.V0 = sd[line][F_V0][k];
+                        nd.beta = sd[line][F_BETA][k];
+                        nd.W = sd[line][F_W][k];
+#pragma unroll
+                        for (int c = 0; c < NU; ++c) nd.u[c] = sd[line][F_U + c][k];
+                        return nd;
+                    },
+                    al, ar, d);
             }
         }
         if (STASH) {
@@ -913,37 +943,27 @@ __device__ __forceinline__ void residual_segment(const GridDev& g, double G, dou
     }
 }
 
-// Residual of all directions: logical blocks [0, nb0) sweep x, [nb0, nb0 + nb1)
-// sweep y, the rest z; direction k writes slab k of Ld (m + 1 components each).
-struct SweepPlan {
-    int nseg[3];          // segments per sequence (blocks of the sweep)
-    int nblk[3];          // blocks of the sweep
-    long long nlines[3];  // lines of the sweep
-    int flat[3];          // flat (1) or aligned (0) layout of the segments
-    int nsl[3];           // segments per line of the aligned layout
-};
-
 template <int DIM, bool ES, bool MIXED, int PO>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) k_residual_rhd(GridDev g, double G, double eps,
                                                       const double* __restrict__ prim,
                                                       const double* __restrict__ met,
                                                       double* __restrict__ Ld, SweepPlan sw) {
     constexpr int M = DIM + 2;
-    __shared__ ResidualLDS<DIM, PO> lds;
+    __shared__ ResidualLDS<DIM, PO, residual_stash(DIM, ES, MIXED)> lds;
     const long long slab = (long long)(M + 1) * g.nodes;
     int b = xcd_block((int)blockIdx.x, (int)gridDim.x);
     if (b < sw.nblk[0]) {
-        residual_segment<DIM, 0, ES, MIXED, PO>(g, G, eps, prim, met, Ld, b, sw.nseg[0], sw.nlines[0], sw.flat[0], sw.nsl[0], lds);
+        residual_segment<DIM, 0, ES, MIXED, PO>(g, G, eps, prim, met, Ld, b, sw, lds);
         return;
     }
     b -= sw.nblk[0];
     if (DIM == 2 || b < sw.nblk[1]) {
-        residual_segment<DIM, 1, ES, MIXED, PO>(g, G, eps, prim, met, Ld + slab, b, sw.nseg[1], sw.nlines[1], sw.flat[1], sw.nsl[1], lds);
+        residual_segment<DIM, 1, ES, MIXED, PO>(g, G, eps, prim, met, Ld + slab, b, sw, lds);
         return;
     }
     b -= sw.nblk[1];
     if (DIM == 3)
-        residual_segment<DIM, 2, ES, MIXED, PO>(g, G, eps, prim, met, Ld + 2 * slab, b, sw.nseg[2], sw.nlines[2], sw.flat[2], sw.nsl[2], lds);
+        residual_segment<DIM, 2, ES, MIXED, PO>(g, G, eps, prim, met, Ld + 2 * slab, b, sw, lds);
 }
 
 // dU = sum_k Ld_k (components 0..m-1), dJ = sum_k Ld_k (component m), summed in
@@ -1960,9 +1980,12 @@ static void residual_all(const es_ctx* c, const double* prim, const double* met,
         sw.nseg[d] = sw.flat[d] ? (int)(((ml - 1) * pl + g.n[d] - 1) / segn + 1) : (int)(ml * sw.nsl[d]);
         sw.nlines[d] = nl;
         sw.nblk[d] = sw.nseg[d];
+        sw.idxi[d] = 1.0 / g.dxi[d];
         nb += sw.nblk[d];
     }
     const double G = c->scheme.gamma, eps = c->scheme.weno_eps;
+    sw.c0 = G / (G - 1.0);
+    sw.c1 = 1.0 / (G - 1.0);
     const bool es_ = c->scheme.dissipation != 0, mixed = c->scheme.mixed != 0;
     if (g.p == 2) residual_launch<DIM, 2>(es_, mixed, (unsigned)nb, s, g, G, eps, prim, met, Ld, sw);
     else if (g.p == 4) residual_launch<DIM, 4>(es_, mixed, (unsigned)nb, s, g, G, eps, prim, met, Ld, sw);

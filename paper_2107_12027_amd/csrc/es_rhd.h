@@ -7,6 +7,16 @@
 
 namespace es {
 
+// Makes a value be formed here: the compiler may neither sink its arithmetic past
+// this point nor hoist what follows above it (register use; a scheduling barrier
+// alone orders memory operations but lets arithmetic drift).
+template <typename R>
+__device__ __forceinline__ void form_here(R& x) {
+#ifndef ES_OPCOUNT_HOST
+    asm volatile("" : "+v"(x));
+#endif
+}
+
 // Per-precision constants of the face dissipation: the rounding level below which
 // a jump of a characteristic variable counts as zero in the sign switch Y
 // (relative to |r_l|_1 (|T V_i|_max + |T V_i+1|_max)).
@@ -34,6 +44,15 @@ __device__ __forceinline__ double frcp(double x) {
 #endif
 }
 
+// 1/x and 1/y from the reciprocal of x y: one hardware estimate and its Newton
+// steps instead of two (the product must be normal as well).
+template <typename R>
+__device__ __forceinline__ void frcp2(R x, R y, R& ix, R& iy) {
+    const R t = frcp(x * y);
+    ix = y * t;
+    iy = x * t;
+}
+
 // a / b as a times the reciprocal of b (frcp; the same conditions on b).  The op
 // count takes it as the one division it stands for.
 __device__ __forceinline__ double fdiv(double a, double b) {
@@ -46,8 +65,8 @@ __device__ __forceinline__ double fdiv(double a, double b) {
 
 // Logarithmic mean [a]/[ln a] (cited in Section 3.1 to Ismail & Roe) from the
 // values and their precomputed logarithms.  With f = (al - ar)/(al + ar) and
-// u = f^2: for u < 1e-2 the ratio ln(al/ar)/(2f) is replaced by its series
-// sum_{k=0}^{7} u^k/(2k+1) (truncation below 1e-17); otherwise [a]/[ln a].
+// u = f^2 it is (al + ar)/2 times f/artanh(f): for u < 1e-2 the series of that
+// factor, otherwise [a]/[ln a].
 __device__ __forceinline__ double xsqrt(double x) { return sqrt(x); }
 __device__ __forceinline__ double xexp(double x) { return exp(x); }
 __device__ __forceinline__ double xlog(double x) { return log(x); }
@@ -102,17 +121,19 @@ __device__ __forceinline__ R log_mean(R al, R ar, R lnal, R lnar) {
     const R s = al + ar;
     const R dif = al - ar;
     if (dif * dif < 1e-2 * (s * s)) {
+        // the series of the reciprocal, f/artanh(f) = 1 - u/3 - 4u^2/45 - ... through
+        // u^7 (truncation below 2e-18): one reciprocal (of s) instead of two
         const R f = dif * frcp(s);
         const R u = f * f;
-        R F = R(1.0 / 15.0);
-        F = fma(F, u, R(1.0 / 13.0));
-        F = fma(F, u, R(1.0 / 11.0));
-        F = fma(F, u, R(1.0 / 9.0));
-        F = fma(F, u, R(1.0 / 7.0));
-        F = fma(F, u, R(1.0 / 5.0));
-        F = fma(F, u, R(1.0 / 3.0));
+        R F = R(-25865068.0 / 1915538625.0);
+        F = fma(F, u, R(-10719068.0 / 638512875.0));
+        F = fma(F, u, R(-10196.0 / 467775.0));
+        F = fma(F, u, R(-428.0 / 14175.0));
+        F = fma(F, u, R(-44.0 / 945.0));
+        F = fma(F, u, R(-4.0 / 45.0));
+        F = fma(F, u, R(-1.0 / 3.0));
         F = fma(F, u, R(1.0));
-        return 0.5 * s * frcp(F);
+        return 0.5 * s * F;
     }
     return dif * frcp(lnal - lnar);
 }
@@ -151,14 +172,16 @@ __device__ __forceinline__ void pair_flux_rhd(double G, const NodeRHD<NU, R>& l,
         uu += um[k] * um[k];
         un += ab[k] * um[k];
     }
-    const R a0 = 1.0 + frcp((G - 1.0) * beta_ln);
-    const R iden = frcp(W_m * W_m - uu);
-    const R pb = rho_m * frcp(beta_m);
+    R ibl, ibm, iden, iW;
+    frcp2(R((G - 1.0) * beta_ln), beta_m, ibl, ibm);
+    frcp2(R(W_m * W_m - uu), W_m, iden, iW);
+    const R a0 = 1.0 + ibl;
+    const R pb = rho_m * ibm;
     const R U1 = rho_ln * W_m;
     const R U5 = (a0 * U1 * W_m + pb * uu) * iden;
     const R C = W_m * (a0 * rho_ln + pb) * iden;
     F[0] = rho_ln * (at * W_m + un);
-    const R s = (at * (U5 + pb) + C * un) * frcp(W_m);
+    const R s = (at * (U5 + pb) + C * un) * iW;
 #pragma unroll
     for (int k = 0; k < NU; ++k) F[1 + k] = um[k] * s + ab[k] * pb;
     F[NU + 1] = at * U5 + C * un;
@@ -176,7 +199,20 @@ __device__ __forceinline__ void pair_flux_rhd(double G, const NodeRHD<NU, R>& l,
 __device__ __forceinline__ float log_mean_mixed(double al, double ar, double lnal, double lnar) {
     const double s = al + ar;
     const double dif = al - ar;
-    if (dif * dif < 1e-2 * (s * s)) return (float)log_mean(al, ar, lnal, lnar);
+    if (dif * dif < 1e-2 * (s * s)) {
+        // (s/2) / (artanh(f)/f) with the series sum_{k=0}^{7} u^k/(2k+1)
+        const double f = dif * frcp(s);
+        const double u = f * f;
+        double F = 1.0 / 15.0;
+        F = fma(F, u, 1.0 / 13.0);
+        F = fma(F, u, 1.0 / 11.0);
+        F = fma(F, u, 1.0 / 9.0);
+        F = fma(F, u, 1.0 / 7.0);
+        F = fma(F, u, 1.0 / 5.0);
+        F = fma(F, u, 1.0 / 3.0);
+        F = fma(F, u, 1.0);
+        return (float)(0.5 * s * frcp(F));
+    }
     return (float)dif * frcp((float)lnal - (float)lnar);
 }
 
@@ -453,12 +489,153 @@ __device__ __forceinline__ void rotation(const R* n, R T[3][3]) {
     }
 }
 
+// Closed form of the face eigen-structure.  With v = (v_n, v_1(, v_2)) the velocity
+// in the frame (n, t_1(, t_2)) of the face, A = h W (1 - v_n^2)/(1 - v_n lambda) and
+// the columns in the slots (D, m_n, m_t, E):
+//   acoustic  f (1, A lambda, h W v_t, A),
+//             f^2 = p/(2h) [W (1/c^2 - 1) + lambda/(W (lambda - v_n))];
+//   cluster   s_e (1, W v, W), s_e^2 = rho W (Gamma - 1)/Gamma: the projection of e_D;
+//             s_1 (W v_1, h (2 W^2 v_1 v + e_1), 2 h W^2 v_1), s_1^2 = p W/(h g_1),
+//             g_1 = 1 + W^2 v_1^2: the projection of e_{m_t1};
+//             s_2 (W w, h (2 W^2 w v + e_2 - kappa e_1), 2 h W^2 w), w = v_2/g_1,
+//             kappa = W^2 v_1 v_2/g_1, s_2^2 = p W g_1/(h (1 + W^2 |v_t|^2)): what is left
+//             of the projection of e_{m_t2}.
+// They are the A0^{-1}-normalised eigenvectors (R R^T = dU/dV): the acoustic norm is
+// dV.dU = (2 beta q/(rho h)) [W q (1/c^2 - 1) + lambda/W], q = lambda - v_n = dp, of an
+// isentropic wave; on the cluster dV.dU is diagonal between the entropy wave
+// (c_0 W/rho) and the shears (beta rho h W^3 (delta_kl + W^2 v_k v_l)), the seed e_D is
+// orthogonal to the shears, and the projection of e_{m_tk} onto them is the shear dv_k.
+// About 130 operations, where forming the same basis numerically (tangent maps of the
+// primitive basis, their Gram matrix, its inverse and a Gram-Schmidt sequence) takes
+// about 1,100 in 3D and 500 in 2D.
+template <typename R>
+struct FaceCoef {
+    R W, ib, h, vn, lam[2], A[2], f[2], se, s1, s2, kappa, w;
+};
+
+// From the face entropy variables' mean: V0 = V_1, bb = V_E^2 - |V_u|^2, iVE = -1/V_E,
+// and the frame's velocity components (vn, v1, v2).
+template <int DIM, typename R>
+__device__ __forceinline__ FaceCoef<R> face_coefficients(R G, R c0, R c1, R V0, R bb, R iVE, R vn, R v1, R v2) {
+    FaceCoef<R> k;
+    k.vn = vn;
+    k.ib = frsqrt(bb);
+    R beta = bb * k.ib;
+    beta = fma(fma(-beta, beta, bb), R(0.5) * k.ib, beta);
+    // 1/W = beta/(-V_E), ln rho = V_1 - G/(G-1) - ln(beta)/(G-1) - beta, p = rho/beta
+    const R iW = beta * iVE;
+    const R p = k.ib * xexp(V0 - c0 - xlog(beta) * c1 - beta);
+    const R bc = beta + c0;                   // beta h
+    k.h = bc * k.ib;
+    R ibc;
+    frcp2(iW, bc, k.W, ibc);
+    const R c2 = G * ibc;                     // sound speed squared, G/(beta h)
+    const R vt2 = DIM == 3 ? v1 * v1 + v2 * v2 : v1 * v1;
+    const R vv = vn * vn + vt2;
+    const R E1 = iW * iW;                     // 1 - |v|^2
+    const R N2 = R(1.0) - vn * vn;
+    const R root = psqrt(c2 * E1 * (N2 - c2 * vt2));
+    const R den = R(1.0) - vv * c2;
+    const R vc = vn * (R(1.0) - c2);
+    const R vE = vn * c2 * E1;
+    const R Nm = vc - root, Np = vc + root;   // lambda = N/den
+    const R Qm = -vE - root, Qp = root - vE;  // lambda - v_n = Q/den
+    const R iden = frcp(den);
+    k.lam[0] = Nm * iden;
+    k.lam[1] = Np * iden;
+    R iDm, iDp, iQm, iQp;
+    frcp2(den - vn * Nm, den - vn * Np, iDm, iDp);
+    frcp2(Qm, Qp, iQm, iQp);
+    const R hW = k.h * k.W;
+    const R An = hW * N2 * den;
+    k.A[0] = An * iDm;
+    k.A[1] = An * iDp;
+    // f^2 = y X/(2 W), s_e^2 = y beta h/c_0, s_1^2 = y/g_1, s_2^2 = y g_1/g_t with y = p W/h
+    const R y = p * k.W * beta * ibc;
+    const R sy = psqrt(y);
+    const R X0 = k.W * (bc / G - R(1.0));
+    const R hy = R(0.5) * y * iW;
+    k.f[0] = psqrt(hy * (X0 + iW * Nm * iQm));
+    k.f[1] = psqrt(hy * (X0 + iW * Np * iQp));
+    k.se = psqrt(y * bc / c0);
+    const R W2 = k.W * k.W;
+    const R g1 = R(1.0) + W2 * v1 * v1;
+    const R r1 = frsqrt(g1);
+    k.s1 = sy * r1;
+    if (DIM == 3) {
+        const R ig1 = r1 * r1;
+        k.w = v2 * ig1;
+        k.kappa = W2 * v1 * k.w;
+        k.s2 = k.s1 * g1 * frsqrt(R(1.0) + W2 * vt2);
+    }
+    return k;
+}
+
 // Face state and scaled eigenvectors at one face (rotated frame): from the
 // rotated entropy variables V2, V3 of nodes i and i+1 and the face metrics
 // (a_t, L = |a_x|) returns lambda^ and calls col(r, q) for each column r of R,
 // q = 0: acoustic lambda_-, q = 1: acoustic lambda_+, q = 2..: the v_n cluster.
 template <int DIM, typename R, typename Col>
 __device__ __forceinline__ R face_eigen_columns(R G, const R* V2, const R* V3, R at, R L, Col&& col) {
+    constexpr int M = DIM + 2;
+    const R c0 = G / (G - R(1.0)), c1 = R(1.0) / (G - R(1.0));
+    R Vb[M], vu2 = R(0.0);
+#pragma unroll
+    for (int c = 0; c < M; ++c) Vb[c] = R(0.5) * (V2[c] + V3[c]);
+#pragma unroll
+    for (int a = 0; a < DIM; ++a) vu2 += Vb[1 + a] * Vb[1 + a];
+    const R iVE = -frcp(Vb[M - 1]);
+    R v[3];
+    v[2] = R(0.0);
+#pragma unroll
+    for (int a = 0; a < DIM; ++a) v[a] = Vb[1 + a] * iVE;
+    const FaceCoef<R> k = face_coefficients<DIM, R>(G, c0, c1, Vb[0], Vb[M - 1] * Vb[M - 1] - vu2, iVE, v[0], v[1], v[2]);
+    R r[M];
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+        // the sign of the wave with pressure change dp = lambda - v_n
+        const R f = s == 0 ? -k.f[0] : k.f[1];
+        r[0] = f;
+        r[1] = f * k.A[s] * k.lam[s];
+#pragma unroll
+        for (int a = 1; a < DIM; ++a) r[1 + a] = f * k.h * k.W * v[a];
+        r[M - 1] = f * k.A[s];
+        col(r, s);
+    }
+    r[0] = k.se;
+#pragma unroll
+    for (int a = 0; a < DIM; ++a) r[1 + a] = k.se * k.W * v[a];
+    r[M - 1] = k.se * k.W;
+    col(r, 2);
+    {
+        const R e = R(2.0) * k.s1 * k.h * k.W * k.W * v[1];
+        r[0] = k.s1 * k.W * v[1];
+#pragma unroll
+        for (int a = 0; a < DIM; ++a) r[1 + a] = e * v[a] + (a == 1 ? k.s1 * k.h : R(0.0));
+        r[M - 1] = e;
+        col(r, 3);
+    }
+    if constexpr (DIM == 3) {
+        const R e = R(2.0) * k.s2 * k.h * k.W * k.W * k.w;
+        r[0] = k.s2 * k.W * k.w;
+#pragma unroll
+        for (int a = 0; a < DIM; ++a)
+            r[1 + a] = e * v[a] + (a == 1 ? -(k.s2 * k.h * k.kappa) : (a == 2 ? k.s2 * k.h : R(0.0)));
+        r[M - 1] = e;
+        col(r, 4);
+    }
+    return fmax(fabs(at + L * k.lam[0]), fmax(fabs(at + L * k.vn), fabs(at + L * k.lam[1])));
+}
+
+// The same columns formed numerically: tangent maps of the primitive basis, the
+// acoustic columns from
+//   dp = lambda - v_n, drho = dp/(h c^2), dv_n = (1 - v_n lambda)/(rho h W^2),
+//   dv_t = -v_t (dh + h W^2 v_n dv_n)/(h (1 + W^2 |v_t|^2))   [d(h W v_t) = 0],
+// normalised by sqrt(dU.dV), the cluster's Gram matrix, its inverse and the
+// Gram-Schmidt sequence of the projected seeds.  The FP32-mixed form keeps
+// it: its results are pinned to these FP32 roundings.
+template <int DIM, typename R, typename Col>
+__device__ __forceinline__ R face_eigen_columns_gram(R G, const R* V2, const R* V3, R at, R L, Col&& col) {
     constexpr int M = DIM + 2;
     constexpr int NC = DIM;          // cluster size (entropy + transverse shear waves)
     const R c0 = G / (G - R(1.0)), c1 = R(1.0) / (G - R(1.0));
@@ -632,25 +809,252 @@ __device__ __forceinline__ R face_eigen_columns(R G, const R* V2, const R* V3, R
 //    nodes i and i+1 (A0 at that state turns [V] into the midpoint rule for [U]);
 //    face metrics: arithmetic mean (readings of this build);
 //  * lambda^ = max |a_t + L lambda_m|, lambda_+- closed form, lambda_0 = v_n;
-//  * R: acoustic columns from the primitive eigenvector (scaled by lambda - v_n)
-//      dp = lambda - v_n, drho = dp/(h c^2), dv_n = (1 - v_n lambda)/(rho h W^2),
-//      dv_t = -v_t (dh + h W^2 v_n dv_n)/(h (1 + W^2 |v_t|^2))   [d(h W v_t) = 0],
-//    normalised by sqrt(dU.dV) so that R R^T = dU/dV; the v_n cluster
-//    (basis e_rho, e_vt) is replaced by its canonical A0^{-1}-orthonormal basis
-//    from the cluster projector applied to the seeds e_D, e_{m_t1}(, e_{m_t2}),
-//    computed in the coefficient space of the cluster basis with the Gram
-//    matrix G_ab = dU_a . dV_b;
+//  * R: the acoustic eigenvectors normalised so that R R^T = dU/dV, and the canonical
+//    A0^{-1}-orthonormal basis of the v_n cluster from its projector applied to the
+//    seeds e_D, e_{m_t1}(, e_{m_t2}), both in closed form (FaceCoef);
 //  * WENO5-JS of V~ = R^T T V on both sides, Y_l = [<<V~_l>> [V~_l] > 0], with a
 //    jump [V~_l] below Y_TOL |r_l|_1 (|T V_i|_max + |T V_i+1|_max) counted as
 //    zero (sign(0) at rounding level).
 //
+// Jump <<v>> = v_{i+1/2}^+ - v_{i+1/2}^- of the WENO-JS values of order 2P - 1 from the
+// 2P point values v[0..2P-1] around the face (the two one-sided weno3 / weno5 / weno7
+// values), formed from the differences d_k = v_{k+1} - v_k: both values are the
+// nearest node plus a combination of differences, so the second differences and
+// their squares are shared by the two sides and the nodes' common part cancels
+// before any rounding.  Weights over a common denominator, as in weno5.
+template <int P, typename R>
+__device__ __forceinline__ R weno_jump(const R* v, R eps) {
+    R d[2 * P - 1];
+#pragma unroll
+    for (int k = 0; k < 2 * P - 1; ++k) d[k] = v[k + 1] - v[k];
+    if constexpr (P == 2) {
+        // value - nearest node = (w0 q0 + w1 q1)/(2 (w0 + w1)), e = eps + d^2
+        const R e0 = fma(d[0], d[0], eps), e1 = fma(d[1], d[1], eps), e2 = fma(d[2], d[2], eps);
+        const R f0 = e0 * e0, f1 = e1 * e1, f2 = e2 * e2;
+        auto side = [](R g0, R g1, R q0, R q1) {
+            const R w1 = R(2.0) * g0;
+            return fma(g1, q0, w1 * q1) * frcp(R(2.0) * (g1 + w1));
+        };
+        return d[1] + side(f2, f1, -d[2], -d[1]) - side(f0, f1, d[0], d[1]);
+    } else if constexpr (P == 3) {
+        // 4 (eps + beta_k) = 4 eps + 13/3 t_k^2 + s_k^2 with the second differences t
+        R b[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const R t = d[k + 1] - d[k];
+            b[k] = fma(R(13.0 / 3.0) * t, t, R(4.0) * eps);
+        }
+        const R s12 = d[1] + d[2], s23 = d[2] + d[3];
+        // the four-difference stencil (D0 .. D3) seen from its side: D1 = D0 + t etc.
+        auto side = [](R D0, R D1, R D2, R D3, R b0, R b1, R b2, R s1) {
+            const R s0 = fma(R(3.0), D1, -D0), s2 = fma(R(3.0), D2, -D3);
+            const R e0 = fma(s0, s0, b0), e1 = fma(s1, s1, b1), e2 = fma(s2, s2, b2);
+            const R f0 = e0 * e0, f1 = e1 * e1, f2 = e2 * e2;
+            const R w0 = f1 * f2, w1 = R(6.0) * (f0 * f2), w2 = R(3.0) * (f0 * f1);
+            const R q0 = fma(R(5.0), D1, R(-2.0) * D0), q1 = fma(R(2.0), D2, D1), q2 = fma(R(4.0), D2, -D3);
+            return fma(w0, q0, fma(w1, q1, w2 * q2)) * frcp(R(6.0) * (w0 + w1 + w2));
+        };
+        return d[2] - side(d[4], d[3], d[2], d[1], b[3], b[2], b[1], s23) - side(d[0], d[1], d[2], d[3], b[0], b[1], b[2], s12);
+    } else {
+        // beta_k = u^2/36 + 13/12 s^2 + 781/720 r^2 (weno7), here times 36
+        auto side = [eps](R D0, R D1, R D2, R D3, R D4, R D5) {
+            const R q0 = fma(R(3.0), D0, fma(R(-10.0), D1, R(13.0) * D2)), q1 = fma(R(4.0), D2, fma(R(3.0), D3, -D1));
+            const R q2 = fma(R(6.0), D3, D2 - D4), q3 = fma(R(9.0), D3, fma(R(-4.0), D4, D5));
+            const R u0 = fma(R(2.0), D0, fma(R(-7.0), D1, R(11.0) * D2)), u1 = fma(R(5.0), D2, fma(R(2.0), D3, -D1));
+            const R u2 = fma(R(2.0), D2, fma(R(5.0), D3, -D4)), u3 = fma(R(11.0), D3, fma(R(-7.0), D4, R(2.0) * D5));
+            const R s0 = fma(R(-3.0), D1, fma(R(2.0), D2, D0)), s1 = D3 - D2, s3 = fma(R(3.0), D4, fma(R(-2.0), D3, -D5));
+            const R r0 = fma(R(-2.0), D1, D0 + D2), r1 = fma(R(-2.0), D2, D1 + D3), r2 = fma(R(-2.0), D3, D2 + D4),
+                    r3 = fma(R(-2.0), D4, D3 + D5);
+            const R k3 = R(781.0 / 20.0), e = R(36.0) * eps;
+            const R b1 = fma(R(39.0) * s1, s1, e);
+            const R e0 = fma(u0, u0, fma(k3 * r0, r0, fma(R(39.0) * s0, s0, e)));
+            const R e1 = fma(u1, u1, fma(k3 * r1, r1, b1));
+            const R e2 = fma(u2, u2, fma(k3 * r2, r2, b1));
+            const R e3 = fma(u3, u3, fma(k3 * r3, r3, fma(R(39.0) * s3, s3, e)));
+            const R f0 = e0 * e0, f1 = e1 * e1, f2 = e2 * e2, f3 = e3 * e3;
+            const R f01 = f0 * f1, f23 = f2 * f3;
+            const R w0 = f1 * f23, w1 = R(12.0) * (f0 * f23), w2 = R(18.0) * (f01 * f3), w3 = R(4.0) * (f01 * f2);
+            return fma(w0, q0, fma(w1, q1, fma(w2, q2, w3 * q3))) * frcp(R(12.0) * (w0 + w1 + w2 + w3));
+        };
+        return d[3] - side(d[6], d[5], d[4], d[3], d[2], d[1]) - side(d[0], d[1], d[2], d[3], d[4], d[5]);
+    }
+}
+
+// A stencil node of the face dissipation: V_1 and what the rest of the entropy
+// variables V = (V_1, beta u, -beta W) is formed from.
+template <int DIM, typename R = double>
+struct NodeV {
+    R V0, beta, W, u[DIM];
+};
+
 // The stencil states come from node(j), j = 0..2P-1 (nodes i-P+1..i+P; WENO of
 // order w = 2P - 1: WENO7 for P = 4, WENO5 for P = 3, WENO3 for P = 2).  The face eigen-structure
-// is formed first from nodes i and i+1 alone; the rotated entropy vectors of the
-// stencil are formed afterwards and projected onto the columns at once, so that
-// they are not held while the eigen-structure is built (register use).
+// is formed first from nodes i and i+1 alone.  Its columns are turned into the fixed
+// frame (T^{-1} R), so that the stencil's entropy variables are projected as they are
+// stored, without a rotation per node, and the dissipation needs none afterwards.
+// Bound by FP64 issue; the projections (25 of them per stencil node in 3D) and the five
+// WENO jumps are most of what is left.
 template <int DIM, typename R, int P = 3, typename NodeFn>
-__device__ __forceinline__ void face_diss_rhd_fn(R G, R eps, NodeFn&& node, const R* al, const R* ar, R* d) {
+__device__ __forceinline__ void face_diss_rhd_fn(R G, R c0, R c1, R eps, NodeFn&& node, const R* al, const R* ar, R* d) {
+    constexpr int M = DIM + 2;
+    constexpr int NS = 2 * P, CI = P - 1;    // stencil size, index of node i
+    const R at = R(0.5) * (al[0] + ar[0]);
+    R ax[3] = {R(0.0), R(0.0), R(0.0)}, L2 = R(0.0);
+#pragma unroll
+    for (int j = 0; j < DIM; ++j) {
+        ax[j] = R(0.5) * (al[1 + j] + ar[1 + j]);
+        L2 += ax[j] * ax[j];
+    }
+    const R iL = frsqrt(L2);
+    R L = L2 * iL;
+    L = fma(fma(-L, L, L2), R(0.5) * iL, L);
+    R T[3][3];
+    {
+        const R nrm[3] = {ax[0] * iL, ax[1] * iL, ax[2] * iL};
+        rotation<DIM>(nrm, T);
+    }
+    // mean entropy variables of nodes i and i+1 and the rounding scale of the
+    // projections there: the largest component of V of either node, whose momentum
+    // part is never larger than its energy part in any frame
+    R Vm[M], tvmax;
+    {
+        const NodeV<DIM, R> a = node(CI), b = node(CI + 1);
+        const R ea = a.beta * a.W, eb = b.beta * b.W;
+        Vm[0] = R(0.5) * (a.V0 + b.V0);
+#pragma unroll
+        for (int k = 0; k < DIM; ++k) Vm[1 + k] = R(0.5) * (a.beta * a.u[k] + b.beta * b.u[k]);
+        Vm[M - 1] = R(-0.5) * (ea + eb);
+        tvmax = fmax(fabs(a.V0), ea) + fmax(fabs(b.V0), eb);
+    }
+    R lhat, Rm[M][M], thr[M];
+    {
+        R vu2 = R(0.0), v[DIM];
+        const R iVE = -frcp(Vm[M - 1]);
+#pragma unroll
+        for (int k = 0; k < DIM; ++k) {
+            vu2 += Vm[1 + k] * Vm[1 + k];
+            v[k] = Vm[1 + k] * iVE;
+        }
+        R vf[3] = {R(0.0), R(0.0), R(0.0)};   // in the face's frame
+#pragma unroll
+        for (int a = 0; a < DIM; ++a)
+#pragma unroll
+            for (int b = 0; b < DIM; ++b) vf[a] += T[a][b] * v[b];
+        const FaceCoef<R> k = face_coefficients<DIM, R>(G, c0, c1, Vm[0], Vm[M - 1] * Vm[M - 1] - vu2, iVE, vf[0], vf[1], vf[2]);
+        lhat = fmax(fabs(at + L * k.lam[0]), fmax(fabs(at + L * k.vn), fabs(at + L * k.lam[1])));
+        const R ytv = R(RealTraits<R>::ytol) * tvmax;
+        const R hW = k.h * k.W;
+        const R at1 = DIM == 3 ? fabs(vf[1]) + fabs(vf[2]) : fabs(vf[1]);   // |v_t|_1
+        const R a1 = fabs(vf[0]) + at1;                                      // |v|_1
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+            const R e = k.f[s] * k.A[s], g = k.f[s] * hW;
+            const R en = e * k.lam[s], m = en - g * vf[0];
+            Rm[s][0] = k.f[s];
+#pragma unroll
+            for (int a = 0; a < DIM; ++a) Rm[s][1 + a] = fma(g, v[a], m * T[0][a]);
+            Rm[s][M - 1] = e;
+            thr[s] = ytv * (k.f[s] + fabs(en) + g * at1 + e);
+        }
+        {
+            const R g = k.se * k.W;
+            Rm[2][0] = k.se;
+#pragma unroll
+            for (int a = 0; a < DIM; ++a) Rm[2][1 + a] = g * v[a];
+            Rm[2][M - 1] = g;
+            thr[2] = ytv * (k.se + g * (a1 + R(1.0)));
+        }
+        const R h2 = R(2.0) * hW;
+        {
+            const R D = k.s1 * k.W * vf[1], e = h2 * D, g = k.s1 * k.h;
+            Rm[3][0] = D;
+#pragma unroll
+            for (int a = 0; a < DIM; ++a) Rm[3][1 + a] = fma(e, v[a], g * T[1][a]);
+            Rm[3][M - 1] = e;
+            R l1 = fabs(e * vf[0]) + fabs(fma(e, vf[1], g));
+            if (DIM == 3) l1 += fabs(e * vf[2]);
+            thr[3] = ytv * (fabs(D) + l1 + fabs(e));
+        }
+        if constexpr (DIM == 3) {
+            const R D = k.s2 * k.W * k.w, e = h2 * D, g = k.s2 * k.h, gk = g * k.kappa;
+            Rm[4][0] = D;
+#pragma unroll
+            for (int a = 0; a < DIM; ++a) Rm[4][1 + a] = fma(e, v[a], fma(g, T[2][a], -gk * T[1][a]));
+            Rm[4][M - 1] = e;
+            thr[4] = ytv * (fabs(D) + fabs(e * vf[0]) + fabs(fma(e, vf[1], -gk)) + fabs(fma(e, vf[2], g)) + fabs(e));
+        }
+    }
+
+#pragma unroll
+    for (int q = 0; q < M; ++q) {
+        form_here(thr[q]);
+#pragma unroll
+        for (int c = 0; c < M; ++c) form_here(Rm[q][c]);
+    }
+    // projections of the stencil states onto the columns (the fence keeps the reads
+    // of the outer states after the eigen-structure)
+#ifndef ES_OPCOUNT_HOST
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+#endif
+    R vt[M][NS];
+#pragma unroll
+    for (int j = 0; j < NS; ++j) {
+        const NodeV<DIM, R> q = node(j);
+        R Vj[M];
+        Vj[0] = q.V0;
+#pragma unroll
+        for (int k = 0; k < DIM; ++k) Vj[1 + k] = q.beta * q.u[k];
+        Vj[M - 1] = -q.beta * q.W;
+#pragma unroll
+        for (int c = 0; c < M; ++c) {
+            R s = Rm[c][0] * Vj[0];
+#pragma unroll
+            for (int k = 1; k < M; ++k) s = fma(Rm[c][k], Vj[k], s);
+            vt[c][j] = s;
+            form_here(vt[c][j]);             // one stencil state at a time
+        }
+    }
+
+    // per column: reconstruct, switch, accumulate (in column order)
+    R dd[M];
+#pragma unroll
+    for (int c = 0; c < M; ++c) dd[c] = R(0.0);
+#pragma unroll
+    for (int q = 0; q < M; ++q) {
+        const R jw = weno_jump<P, R>(vt[q], eps);
+        const R jp = vt[q][CI + 1] - vt[q][CI];
+        // a jump within rounding of zero counts as zero (Y = 0)
+        const R on = (jw * jp > R(0.0) && fabs(jp) > thr[q]) ? jw : R(0.0);
+#pragma unroll
+        for (int c = 0; c < M; ++c) {
+            dd[c] = fma(on, Rm[q][c], dd[c]);
+            form_here(dd[c]);                // one column at a time
+        }
+    }
+#pragma unroll
+    for (int c = 0; c < M; ++c) d[c] = lhat * dd[c];
+}
+
+template <int DIM, typename R>
+__device__ __forceinline__ void face_diss_rhd(R G, R eps, const NodeRHD<DIM, R>* nd,
+                                              const R* al, const R* ar, R* d) {
+    const R c0 = G / (G - R(1.0)), c1 = R(1.0) / (G - R(1.0));
+    face_diss_rhd_fn<DIM, R>(G, c0, c1, eps,
+                             [&](int j) {
+                                 NodeV<DIM, R> q;
+                                 q.V0 = c0 + nd[j].lr + nd[j].lb * c1 + nd[j].beta;
+                                 q.beta = nd[j].beta;
+                                 q.W = nd[j].W;
+                                 for (int k = 0; k < DIM; ++k) q.u[k] = nd[j].u[k];
+                                 return q;
+                             },
+                             al, ar, d);
+}
+
+// The dissipation of the FP32-mixed form (R = float): the columns of
+// face_eigen_columns_gram, the stencil states rotated into the face's frame.
+template <int DIM, typename R, int P = 3, typename NodeFn>
+__device__ __forceinline__ void face_diss_rhd_gram(R G, R eps, NodeFn&& node, const R* al, const R* ar, R* d) {
     constexpr int M = DIM + 2;
     constexpr int NS = 2 * P, CI = P - 1;    // stencil size, index of node i
     const R at = R(0.5) * (al[0] + ar[0]);
@@ -687,7 +1091,7 @@ __device__ __forceinline__ void face_diss_rhd_fn(R G, R eps, NodeFn&& node, cons
     const R tvmax = tv2 + tv3;
 
     R Rm[M][M];
-    const R lhat = face_eigen_columns<DIM>(G, TV2, TV3, at, L, [&](const R* r, int q) {
+    const R lhat = face_eigen_columns_gram<DIM>(G, TV2, TV3, at, L, [&](const R* r, int q) {
 #pragma unroll
         for (int c = 0; c < M; ++c) Rm[q][c] = r[c];
     });
@@ -766,12 +1170,6 @@ __device__ __forceinline__ void face_diss_rhd_fn(R G, R eps, NodeFn&& node, cons
         for (int b = 0; b < DIM; ++b) s += T[b][a] * dd[1 + b];
         d[1 + a] = lhat * s;
     }
-}
-
-template <int DIM, typename R>
-__device__ __forceinline__ void face_diss_rhd(R G, R eps, const NodeRHD<DIM, R>* nd,
-                                              const R* al, const R* ar, R* d) {
-    face_diss_rhd_fn<DIM, R>(G, eps, [&](int j) { return nd[j]; }, al, ar, d);
 }
 
 }  // namespace es
