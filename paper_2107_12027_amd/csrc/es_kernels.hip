@@ -687,8 +687,8 @@ struct SweepPlan {
     double c0, c1;        // Gamma / (Gamma - 1), 1 / (Gamma - 1)
 };
 
-// One wavefront per segment of the lines along DIR: loads the segment with its
-// halo into LDS, evaluates the two-point fluxes owned by each node, the face
+// One wavefront per segment of the lines along DIR, LINES of them a block: loads the
+// segments with their halos into LDS, evaluates the two-point fluxes owned by each node, the face
 // dissipation and the flux differences, and writes this direction's part of the
 // residual (m components and J) to out.  The fluxes F(s-n, s) and the
 // dissipation of face s-1/2 come from the lanes that own them (lane shuffles).
@@ -720,7 +720,7 @@ __device__ __forceinline__ void residual_segment(const GridDev& g, double G, dou
     auto& sd = lds.sd;
 
     const int lane = threadIdx.x & 63;
-    const int line = threadIdx.x >> 6;
+    const int line = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     // segment w (nseg of them per sequence) of sequence `line`; blk numbers this
     // sweep's blocks
     const long long w = blk;
@@ -732,33 +732,46 @@ __device__ __forceinline__ void residual_segment(const GridDev& g, double G, dou
     const long long istride = DIR == 0 ? 1 : (DIR == 1 ? (long long)g.n[0] : (long long)g.n[0] * g.n[1]);
     const long long P = g.pnodes;
     const long long N = g.nodes;
-    // line and along-coordinate s (-ng .. n + ng - 1) of sequence position f0 + q,
+    // line and along-coordinate s (-ng .. n + ng - 1) of sequence l's position f0 + q,
     // and the padded / interior index of the line's node 0
     const int nf = DIR == 0 ? g.n[1] : g.n[0];
-    const SeqBase sb = flat ? seq_base(f0, PL, NGP, nf, LINES, line)
-                            : seq_base_aligned(w, nsl, SEGP, 0, NGP, nf, LINES, line);
-    auto locate = [&](int q, long long& lid, int& s, long long& pbase, long long& ibase) {
+    const SeqBase sb = flat ? seq_base(f0, PL, NGP, nf, LINES, 0)
+                            : seq_base_aligned(w, nsl, SEGP, 0, NGP, nf, LINES, 0);
+    auto locate = [&](int l, int q, long long& lid, int& s, long long& pbase, long long& ibase) {
+        SeqBase b = sb;
+        b.fa += l;
+        while (b.fa >= nf) { b.fa -= nf; ++b.fb; }
         int fa, fb;
-        seq_at(sb, q, flat, PL, NGP, nf, LINES, line, lid, s, fa, fb);
+        seq_at(b, q, flat, PL, NGP, nf, LINES, l, lid, s, fa, fb);
         if (s >= nAlong + NGP) lid = nlines;   // past the line's padded end (aligned)
         const int ci = DIR == 0 ? 0 : fa, cj = DIR == 0 ? fa : (DIR == 1 ? 0 : fb), ck = DIR == 2 ? 0 : fb;
         pbase = pidx(g, ci, cj, ck);
         ibase = iidx(g, ci, cj, ck);
     };
 
-    // ---- load the segment with its halo into LDS.  Lane q holds position q and,
-    // for q < NLOADP - 64, position 64 + q as well; the loads of both positions are
-    // issued before the first of them is used, from addresses that are always valid
-    // and outside any branch (a position off the lines reads node 0 and then takes
-    // the far-field values instead), so the wavefront waits on memory once.
-    static_assert(NLOADP > 64 && NLOADP <= 128, "two positions per lane");
+    // ---- load the segments with their halos into LDS: positions 0..NLOADP - 1 of each
+    // of the block's LINES lines.  Along x a wavefront loads its own line, lane q
+    // position q (64 consecutive doubles an instruction).  Along y and z the nodes of a
+    // line are a row or a plane apart, so that a wavefront loading its own line would
+    // touch 64 cache lines an instruction and the block as a whole each of them LINES
+    // times; there the block's threads take the LINES lines, neighbours along x,
+    // together: thread t position t / LINES of line t % LINES, a quarter of the cache
+    // lines per instruction.  (That address rate, not arithmetic, bounded the kernel:
+    // without its dissipation the 128^3 residual took 540 of 625 us.)  The positions
+    // from 64 on are loaded by the first threads as well; both positions' loads are
+    // issued before the first of them is used, from addresses that are always valid (a
+    // position off the lines reads node 0), so the wavefront waits on memory once.
+    constexpr bool COOP = DIR != 0;
+    constexpr int NSEC = NLOADP - 64;
+    static_assert(NLOADP > 64 && NSEC * LINES <= 64, "the positions from 64 on fit one wavefront");
+    const int cl = COOP ? (int)threadIdx.x % LINES : line, cq = COOP ? (int)threadIdx.x / LINES : lane;
     constexpr int NV = M + 2 + NA;   // rho, u, p, ln rho, ln beta, then the metrics
-    auto index = [&](int q, bool use, long long& qlid, int& s, bool& ok) {
-        long long pb, ib;
-        locate(q, qlid, s, pb, ib);
+    auto index = [&](int q, bool use) {
+        long long lid, pb, ib;
+        int s;
+        locate(cl, q, lid, s, pb, ib);
         (void)ib;
-        ok = use && qlid < nlines;
-        return ok ? pb + (long long)s * pstride : 0;
+        return use && lid < nlines ? pb + (long long)s * pstride : 0;
     };
     auto fetch = [&](long long idx, double* v) {
 #pragma unroll
@@ -766,53 +779,43 @@ __device__ __forceinline__ void residual_segment(const GridDev& g, double G, dou
 #pragma unroll
         for (int c = 0; c < NA; ++c) v[M + 2 + c] = met[(DIR * NA + c) * P + idx];
     };
-    auto stash = [&](int q, bool ok, const double* v) {
-        const double rho = ok ? v[0] : 1.0, p = ok ? v[M - 1] : 1.0;
-        double u[NU], uu = 0.0;
+    // (a position off the lines holds node 0's state: no owned node's stencil reads it)
+    auto stash = [&](int q, const double* v) {
+        const double rho = v[0], p = v[M - 1];
+        double uu = 0.0;
 #pragma unroll
-        for (int c = 0; c < NU; ++c) {
-            u[c] = ok ? v[1 + c] : 0.0;
-            uu += u[c] * u[c];
-        }
-        const double beta = rho * frcp(p), lr = ok ? v[M] : 0.0, lb = ok ? v[M + 1] : 0.0;
-        sd[line][F_RHO][q] = rho;
-        if (ES && !MIXED) sd[line][F_V0][q] = sw.c0 + lr + lb * sw.c1 + beta;
-        sd[line][F_BETA][q] = beta;
-        sd[line][F_W][q] = psqrt(1.0 + uu);
-        sd[line][F_LR][q] = lr;
-        sd[line][F_LB][q] = lb;
+        for (int c = 0; c < NU; ++c) uu += v[1 + c] * v[1 + c];
+        const double beta = rho * (MIXED ? frcp_mixed(p) : frcp(p)), lr = v[M], lb = v[M + 1];
+        sd[cl][F_RHO][q] = rho;
+        if (ES && !MIXED) sd[cl][F_V0][q] = sw.c0 + lr + lb * sw.c1 + beta;
+        sd[cl][F_BETA][q] = beta;
+        sd[cl][F_W][q] = MIXED ? psqrt_mixed(1.0 + uu) : psqrt(1.0 + uu);
+        sd[cl][F_LR][q] = lr;
+        sd[cl][F_LB][q] = lb;
 #pragma unroll
-        for (int c = 0; c < NU; ++c) sd[line][F_U + c][q] = u[c];
+        for (int c = 0; c < NU; ++c) sd[cl][F_U + c][q] = v[1 + c];
 #pragma unroll
-        for (int c = 0; c < NA; ++c) sd[line][F_A + c][q] = ok ? v[M + 2 + c] : (c == 1 ? 1.0 : 0.0);
+        for (int c = 0; c < NA; ++c) sd[cl][F_A + c][q] = v[M + 2 + c];
     };
-    // this lane's own node (position lane): only flags stay live (the output index
-    // is formed again at the store)
-    bool active, owner, face;
-    {
-        constexpr int NSEC = NLOADP - 64;
-        const bool sec = lane < NSEC;
+    if (!COOP || line == 0) {
+        const bool sec = cq < NSEC;
         double v0[NV], v1[NV];
-        long long lid_own, lid1;
-        int s_own, s1;
-        bool ok0, ok1;
-        const long long i0 = index(lane, true, lid_own, s_own, ok0);
-        const long long i1 = index(64 + (sec ? lane : 0), sec, lid1, s1, ok1);
-        fetch(i0, v0);
-        fetch(i1, v1);
-        // every load issued before any of them is used
+        fetch(index(cq, true), v0);
+        fetch(index(64 + (sec ? cq : 0), sec), v1);
+        // every load issued before any of them is used (and none of the second
+        // position's sunk into its branch, behind the first wait)
         __builtin_amdgcn_sched_barrier(0);
-        active = lid_own < nlines;
-        owner = active && lane >= NGP && s_own >= 0 && s_own < nAlong;
-        face = active && lane >= NGP - 1 && s_own >= -1 && s_own < nAlong;
-        stash(lane, ok0, v0);
-        // the lanes without a second position store their own again (the same
-        // values): no branch, so the second loads are not sunk after the first wait
 #pragma unroll
-        for (int c = 0; c < NV; ++c) v1[c] = sec ? v1[c] : v0[c];
-        stash(sec ? 64 + lane : lane, sec ? ok1 : ok0, v1);
+        for (int c = 0; c < NV; ++c) form_here(v1[c]);
+        stash(cq, v0);
+        if (sec) stash(64 + cq, v1);
+    } else {
+        double v0[NV];
+        fetch(index(cq, true), v0);
+        stash(cq, v0);
     }
-    wave_lds_sync();
+    if (COOP) __syncthreads();
+    else wave_lds_sync();
 
     auto node_at = [&](int q) {
         NodeRHD<NU> nd;
@@ -827,42 +830,39 @@ __device__ __forceinline__ void residual_segment(const GridDev& g, double G, dou
     };
 
     // ---- two-point fluxes (s, s+n), n = 1..p, owned by the lane of node s, and
-    // flux differences R_s = -(1/dxi) sum_n alpha_n [F(s,s+n) - F(s-n,s)]
-    const bool valid = active;
+    // flux differences R_s = -(1/dxi) sum_n alpha_n [F(s,s+n) - F(s-n,s)].  Every lane
+    // evaluates its fluxes (those of a position off the lines are never used), so that
+    // no branch has to merge them with zeros.
     const double idxi = sw.idxi[DIR];
     double R[M + 1];
-#pragma unroll
-    for (int c = 0; c <= M; ++c) R[c] = 0.0;
     {
-        NodeRHD<NU> l;
+        const NodeRHD<NU> l = node_at(lane);
         double al[NA];
-        if (valid) {
-            l = node_at(lane);
 #pragma unroll
-            for (int c = 0; c < NA; ++c) al[c] = sd[line][F_A + c][lane];
-        }
+        for (int c = 0; c < NA; ++c) al[c] = sd[line][F_A + c][lane];
 #pragma unroll
         for (int n = 1; n <= PO; ++n) {
             double F[M + 1];
+            const NodeRHD<NU> r = node_at(lane + n);
+            double ar[NA];
 #pragma unroll
-            for (int c = 0; c <= M; ++c) F[c] = 0.0;
-            if (valid) {
-                const NodeRHD<NU> r = node_at(lane + n);
-                double ar[NA];
-#pragma unroll
-                for (int c = 0; c < NA; ++c) ar[c] = sd[line][F_A + c][lane + n];
-                if (MIXED) pair_flux_rhd_mixed<NU>(G, l, r, al, ar, F, F[M]);
-                else pair_flux_rhd<NU>(G, l, r, al, ar, F, F[M]);
-            }
+            for (int c = 0; c < NA; ++c) ar[c] = sd[line][F_A + c][lane + n];
+            // FP64: twice the flux
+            if (MIXED) pair_flux_rhd_mixed<NU>(G, l, r, al, ar, F, F[M]);
+            else pair_flux_rhd_sums<NU>(G, l, r, al, ar, F, F[M]);
+            const double w = (MIXED ? 1.0 : 0.5) * alpha_pn(PO, n);
             // all lanes take part in the shuffle; owners (lane >= ng) read F(s-n, s)
 #pragma unroll
-            for (int c = 0; c <= M; ++c) R[c] += alpha_pn(PO, n) * (F[c] - __shfl_up(F[c], n, 64));
+            for (int c = 0; c <= M; ++c) {
+                const double df = F[c] - __shfl_up(F[c], n, 64);
+                R[c] = n == 1 ? w * df : R[c] + w * df;
+            }
             // one pair at a time (interleaving the three raises register pressure)
             __builtin_amdgcn_sched_barrier(0);
         }
     }
 #pragma unroll
-    for (int c = 0; c <= M; ++c) R[c] = owner ? -R[c] * idxi : 0.0;
+    for (int c = 0; c <= M; ++c) R[c] = -R[c] * idxi;
 
     if (ES) {
         constexpr bool STASH = residual_stash(DIM, ES, MIXED);
@@ -873,16 +873,17 @@ __device__ __forceinline__ void residual_segment(const GridDev& g, double G, dou
         // the fence makes the dissipation reload its stencil from LDS instead of
         // keeping the flux phase's node values live (register pressure)
         wave_lds_sync();
-        // ---- face dissipation at s+1/2 for faces s in [-1, n) of the lane's line
+        // ---- face dissipation at s+1/2, s the lane's position (the first p - 1 lanes'
+        // stencils begin before the segment: they repeat lane p - 1's face; owners use
+        // the faces of lanes ng - 1 and up)
         double d[M];
-#pragma unroll
-        for (int c = 0; c < M; ++c) d[c] = 0.0;
-        if (face) {
+        const int fl = lane < PO - 1 ? PO - 1 : lane;
+        {
             // the stencil states are read from LDS where they are used
             if (MIXED) {
                 // FP32 dissipation from FP32 copies of the stencil states and metrics
                 auto node_f = [&](int q) {
-                    const int k = lane - (PO - 1) + q;
+                    const int k = fl - (PO - 1) + q;
                     NodeRHD<NU, float> nd;
                     nd.rho = (float)sd[line][F_RHO][k];
                     nd.beta = (float)sd[line][F_BETA][k];
@@ -896,8 +897,8 @@ __device__ __forceinline__ void residual_segment(const GridDev& g, double G, dou
                 float al[NA], ar[NA];
 #pragma unroll
                 for (int c = 0; c < NA; ++c) {
-                    al[c] = (float)sd[line][F_A + c][lane];
-                    ar[c] = (float)sd[line][F_A + c][lane + 1];
+                    al[c] = (float)sd[line][F_A + c][fl];
+                    ar[c] = (float)sd[line][F_A + c][fl + 1];
                 }
                 float df[M];
                 face_diss_rhd_gram<DIM, float, PO>((float)G, (float)eps, node_f, al, ar, df);
@@ -906,11 +907,11 @@ __device__ __forceinline__ void residual_segment(const GridDev& g, double G, dou
             } else {
                 double al[NA], ar[NA];
 #pragma unroll
-                for (int c = 0; c < NA; ++c) { al[c] = sd[line][F_A + c][lane]; ar[c] = sd[line][F_A + c][lane + 1]; }
+                for (int c = 0; c < NA; ++c) { al[c] = sd[line][F_A + c][fl]; ar[c] = sd[line][F_A + c][fl + 1]; }
                 face_diss_rhd_fn<DIM, double, PO>(
                     G, sw.c0, sw.c1, eps,
                     [&](int q) {
-                        const int k = lane - (PO - 1) + q;
+                        const int k = fl - (PO - 1) + q;
                         NodeV<NU> nd;
                         nd.V0 = sd[line][F_V0][k];
                         nd.beta = sd[line][F_BETA][k];
@@ -929,22 +930,32 @@ __device__ __forceinline__ void residual_segment(const GridDev& g, double G, dou
 #pragma unroll
         for (int c = 0; c < M; ++c) {
             const double dm = __shfl_up(d[c], 1, 64);
-            if (owner) R[c] += 0.5 * (d[c] - dm) * idxi;
+            R[c] += 0.5 * (d[c] - dm) * idxi;
         }
     }
 
-    if (owner) {
-        long long lid_own, pb, ib;
-        int s_own;
-        locate(lane, lid_own, s_own, pb, ib);
-        const long long o = ib + (long long)s_own * istride;
+    // ---- store: the loading threads again (through the line's staging buffer, which its
+    // wavefront has read for the last time)
+    if (COOP) {
+        wave_lds_sync();
+#pragma unroll
+        for (int c = 0; c <= M; ++c) sd[line][c][lane] = R[c];
+        __syncthreads();
+#pragma unroll
+        for (int c = 0; c <= M; ++c) R[c] = sd[cl][c][cq];
+    }
+    long long lid, pb, ib;
+    int s;
+    locate(cl, cq, lid, s, pb, ib);
+    if (lid < nlines && cq >= NGP && s >= 0 && s < nAlong) {
+        const long long o = ib + (long long)s * istride;
 #pragma unroll
         for (int c = 0; c <= M; ++c) out[c * N + o] = R[c];
     }
 }
 
 template <int DIM, bool ES, bool MIXED, int PO>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) k_residual_rhd(GridDev g, double G, double eps,
+__global__ void __launch_bounds__(64 * LINES) __attribute__((amdgpu_waves_per_eu(2))) k_residual_rhd(GridDev g, double G, double eps,
                                                       const double* __restrict__ prim,
                                                       const double* __restrict__ met,
                                                       double* __restrict__ Ld, SweepPlan sw) {
@@ -1954,10 +1965,10 @@ hipError_t launch_metrics(const es_ctx* c, const double* x, const double* xdot,
 template <int DIM, int PO>
 static void residual_launch(bool es_, bool mixed, unsigned nb, hipStream_t s, const GridDev& g, double G,
                             double eps, const double* prim, const double* met, double* Ld, const SweepPlan& sw) {
-    if (es_ && mixed) k_residual_rhd<DIM, true, true, PO><<<nb, 256, 0, s>>>(g, G, eps, prim, met, Ld, sw);
-    else if (es_) k_residual_rhd<DIM, true, false, PO><<<nb, 256, 0, s>>>(g, G, eps, prim, met, Ld, sw);
-    else if (mixed) k_residual_rhd<DIM, false, true, PO><<<nb, 256, 0, s>>>(g, G, eps, prim, met, Ld, sw);
-    else k_residual_rhd<DIM, false, false, PO><<<nb, 256, 0, s>>>(g, G, eps, prim, met, Ld, sw);
+    if (es_ && mixed) k_residual_rhd<DIM, true, true, PO><<<nb, 64 * LINES, 0, s>>>(g, G, eps, prim, met, Ld, sw);
+    else if (es_) k_residual_rhd<DIM, true, false, PO><<<nb, 64 * LINES, 0, s>>>(g, G, eps, prim, met, Ld, sw);
+    else if (mixed) k_residual_rhd<DIM, false, true, PO><<<nb, 64 * LINES, 0, s>>>(g, G, eps, prim, met, Ld, sw);
+    else k_residual_rhd<DIM, false, false, PO><<<nb, 64 * LINES, 0, s>>>(g, G, eps, prim, met, Ld, sw);
 }
 
 template <int DIM>

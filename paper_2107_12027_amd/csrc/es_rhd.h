@@ -3,6 +3,8 @@
 // dissipation with closed-form scaled eigenvectors.
 #pragma once
 
+#include <type_traits>
+
 #include "es_common.h"
 
 namespace es {
@@ -17,6 +19,16 @@ __device__ __forceinline__ void form_here(R& x) {
 #endif
 }
 
+// A constant held in scalar registers: a fused operation reads it there, where the
+// compiler would otherwise copy each half into a vector register before every use.
+template <typename R>
+__device__ __forceinline__ R uniform_const(R c) {
+#ifndef ES_OPCOUNT_HOST
+    if constexpr (std::is_same<R, double>::value) asm("" : "+s"(c));
+#endif
+    return c;
+}
+
 // Per-precision constants of the face dissipation: the rounding level below which
 // a jump of a characteristic variable counts as zero in the sign switch Y
 // (relative to |r_l|_1 (|T V_i|_max + |T V_i+1|_max)).
@@ -28,19 +40,19 @@ struct RealTraits<double> {
     static constexpr bool wide_range = true;     // exponent range for WENO's common denominator
 };
 
-// Reciprocal of a finite, nonzero, normal x: the hardware estimate refined by two
-// Newton-Raphson steps r <- r + r (1 - x r), each of which squares the relative
-// error, so the result is within about one ulp of 1/x.  Zero, infinities and
-// denormals are not handled (NaN propagates); the callers pass state quantities.
+// Reciprocal of a finite, nonzero, normal x.  The hardware estimate r has a relative
+// error e = 1 - x r of up to 2^-24.4 (measured over 4 million arguments), so one step of
+// third order, r (1 + e + e^2), reaches the rounding of the last operation (measured
+// error 2^-53.0) in three fused operations where two Newton steps take four.  Zero,
+// infinities and denormals are not handled (NaN propagates); the callers pass state
+// quantities.
 __device__ __forceinline__ double frcp(double x) {
 #ifdef ES_OPCOUNT_HOST
     return 1.0 / x;
 #else
-    double r = __builtin_amdgcn_rcp(x);
-    double e = fma(-x, r, 1.0);
-    r = fma(r, e, r);
-    e = fma(-x, r, 1.0);
-    return fma(r, e, r);
+    const double r = __builtin_amdgcn_rcp(x);
+    const double e = fma(-x, r, 1.0);
+    return fma(r, fma(e, e, e), r);
 #endif
 }
 
@@ -72,31 +84,33 @@ __device__ __forceinline__ double xexp(double x) { return exp(x); }
 __device__ __forceinline__ double xlog(double x) { return log(x); }
 
 // Reciprocal square root and square root of a positive, normal x (state and
-// metric quantities that are positive by construction): the hardware estimate
-// of 1/sqrt(x) refined by two Newton steps r <- r + r (1/2 - x r^2/2), each of
-// which squares the relative error, and for the root s = x r with one
-// correction s <- s + (x - s^2) r/2.  Unlike the general square root there is
+// metric quantities that are positive by construction).  The hardware estimate r of
+// 1/sqrt(x) is good to 2^-24.2; with e = 1 - x r^2 the step r (1 + e/2 + 3 e^2/8) has
+// an error of third order (measured 2^-52.7).  The root takes one coupled step on
+// g = x r and h = r/2 (error of second order in e) and the correction
+// g + h (x - g^2) (measured 2^-53.0).  Unlike the general square root there is
 // no rescaling for denormal or zero arguments (a zero gives NaN), which saves
 // the range checks and two scalings per call.
 __device__ __forceinline__ double frsqrt(double x) {
 #ifdef ES_OPCOUNT_HOST
     return 1.0 / sqrt(x);
 #else
-    double r = __builtin_amdgcn_rsq(x);
-    const double hx = 0.5 * x;
-    double e = fma(-hx * r, r, 0.5);
-    r = fma(r, e, r);
-    e = fma(-hx * r, r, 0.5);
-    return fma(r, e, r);
+    const double r = __builtin_amdgcn_rsq(x);
+    const double t = x * r;
+    const double e = fma(-t, r, 1.0);
+    return fma(r * e, fma(e, 0.375, 0.5), r);
 #endif
 }
 __device__ __forceinline__ double psqrt(double x) {
 #ifdef ES_OPCOUNT_HOST
     return sqrt(x);
 #else
-    const double r = frsqrt(x);
-    const double s = x * r;
-    return fma(fma(-s, s, x), 0.5 * r, s);
+    const double r = __builtin_amdgcn_rsq(x);
+    double g = x * r, h = 0.5 * r;
+    const double u = fma(-h, g, 0.5);
+    g = fma(g, u, g);
+    h = fma(h, u, h);
+    return fma(fma(-g, g, x), h, g);
 #endif
 }
 
@@ -125,24 +139,122 @@ __device__ __forceinline__ R log_mean(R al, R ar, R lnal, R lnar) {
         // u^7 (truncation below 2e-18): one reciprocal (of s) instead of two
         const R f = dif * frcp(s);
         const R u = f * f;
-        R F = R(-25865068.0 / 1915538625.0);
-        F = fma(F, u, R(-10719068.0 / 638512875.0));
-        F = fma(F, u, R(-10196.0 / 467775.0));
-        F = fma(F, u, R(-428.0 / 14175.0));
-        F = fma(F, u, R(-44.0 / 945.0));
-        F = fma(F, u, R(-4.0 / 45.0));
-        F = fma(F, u, R(-1.0 / 3.0));
+        R F = uniform_const(R(-25865068.0 / 1915538625.0));
+        F = fma(F, u, uniform_const(R(-10719068.0 / 638512875.0)));
+        F = fma(F, u, uniform_const(R(-10196.0 / 467775.0)));
+        F = fma(F, u, uniform_const(R(-428.0 / 14175.0)));
+        F = fma(F, u, uniform_const(R(-44.0 / 945.0)));
+        F = fma(F, u, uniform_const(R(-4.0 / 45.0)));
+        F = fma(F, u, uniform_const(R(-1.0 / 3.0)));
         F = fma(F, u, R(1.0));
         return 0.5 * s * F;
     }
     return dif * frcp(lnal - lnar);
 }
 
+// Logarithm of a positive normal x and exponential of a finite x for the face state.
+// ln(2^e m) = e ln 2 + 2 artanh(f), f = (m - 1)/(m + 1), with m in [sqrt(1/2), sqrt 2) and
+// the series of artanh (|f| <= 0.172, eleven terms, truncation below 1e-18);
+// exp(n ln 2 + r) = 2^n exp(r), |r| <= ln 2/2, by its Taylor polynomial of degree 13
+// (truncation below 5e-18).  Relative error of about one rounding (absolute for a
+// logarithm near zero crossings of e ln 2 + ...).  The general functions also handle
+// zeros, infinities and denormals and carry a second word: together they take twice
+// the instructions.
+__device__ __forceinline__ double face_log(double x) {
+#ifdef ES_OPCOUNT_HOST
+    return log(x);
+#else
+    double m = __builtin_amdgcn_frexp_mant(x);          // [1/2, 1)
+    int e = __builtin_amdgcn_frexp_exp(x);
+    const bool low = m < 0.70710678118654752;
+    m = low ? 2.0 * m : m;
+    e = low ? e - 1 : e;
+    const double f = (m - 1.0) * frcp(m + 1.0), u = f * f;
+    double P = uniform_const(1.0 / 21.0);
+    P = fma(P, u, uniform_const(1.0 / 19.0));
+    P = fma(P, u, uniform_const(1.0 / 17.0));
+    P = fma(P, u, uniform_const(1.0 / 15.0));
+    P = fma(P, u, uniform_const(1.0 / 13.0));
+    P = fma(P, u, uniform_const(1.0 / 11.0));
+    P = fma(P, u, uniform_const(1.0 / 9.0));
+    P = fma(P, u, uniform_const(1.0 / 7.0));
+    P = fma(P, u, uniform_const(1.0 / 5.0));
+    P = fma(P, u, uniform_const(1.0 / 3.0));
+    const double f2 = f + f;
+    const double q = fma(f2 * u, P, f2);
+    return fma((double)e, uniform_const(0.69314718055994530942), q);
+#endif
+}
+__device__ __forceinline__ double face_exp(double x) {
+#ifdef ES_OPCOUNT_HOST
+    return exp(x);
+#else
+    const double n = __builtin_rint(x * uniform_const(1.4426950408889634074));
+    // ln 2 in two words (the first with 33 bits, so that n times it is exact)
+    double r = fma(n, uniform_const(-0x1.62e42fefp-1), x);
+    r = fma(n, uniform_const(-0x1.473de6af278edp-34), r);
+    double P = uniform_const(1.0 / 6227020800.0);
+    P = fma(P, r, uniform_const(1.0 / 479001600.0));
+    P = fma(P, r, uniform_const(1.0 / 39916800.0));
+    P = fma(P, r, uniform_const(1.0 / 3628800.0));
+    P = fma(P, r, uniform_const(1.0 / 362880.0));
+    P = fma(P, r, uniform_const(1.0 / 40320.0));
+    P = fma(P, r, uniform_const(1.0 / 5040.0));
+    P = fma(P, r, uniform_const(1.0 / 720.0));
+    P = fma(P, r, uniform_const(1.0 / 120.0));
+    P = fma(P, r, uniform_const(1.0 / 24.0));
+    P = fma(P, r, uniform_const(1.0 / 6.0));
+    P = fma(P, r, 0.5);
+    P = fma(P, r, 1.0);
+    P = fma(P, r, 1.0);
+    return __builtin_amdgcn_ldexp(P, (int)n);
+#endif
+}
+template <typename R>
+__device__ __forceinline__ R face_log(R x) { return xlog(x); }
+template <typename R>
+__device__ __forceinline__ R face_exp(R x) { return xexp(x); }
+
 template <int NU, typename R = double>
 struct NodeRHD {
     R rho, p, beta, W, lr, lb;
     R u[NU];
 };
+
+// Twice the two-point flux and VCL value of pair_flux_rhd, from the sums of the two
+// nodes' quantities instead of their means: with S_x = x_l + x_r the halves cancel
+// (pb = S_rho/S_beta, 1/(W^2 - |u|^2) = 4/(S_W^2 - |S_u|^2)) down to one factor of the
+// logarithmic mean, and the caller's weights take the remaining one half.
+template <int NU, typename R>
+__device__ __forceinline__ void pair_flux_rhd_sums(double G, const NodeRHD<NU, R>& l, const NodeRHD<NU, R>& r,
+                                                   const double* al, const double* ar, R* F, double& Jt) {
+    const R rho_ln = log_mean(l.rho, r.rho, l.lr, r.lr);
+    const R beta_ln = log_mean(l.beta, r.beta, l.lb, r.lb);
+    const R W = l.W + r.W;
+    R u[NU], uu = R(0.0), un = R(0.0);
+    const double at = al[0] + ar[0];
+    double a[NU];
+#pragma unroll
+    for (int k = 0; k < NU; ++k) {
+        u[k] = l.u[k] + r.u[k];
+        a[k] = al[1 + k] + ar[1 + k];
+        uu += u[k] * u[k];
+        un += a[k] * u[k];
+    }
+    R ibl, ib, iden, iW;
+    frcp2(R((G - 1.0) * beta_ln), R(l.beta + r.beta), ibl, ib);
+    frcp2(R(W * W - uu), W, iden, iW);
+    const R pb = (l.rho + r.rho) * ib;
+    const R ar1 = rho_ln + ibl * rho_ln;                 // a0 rho^ln
+    const R U5 = (ar1 * (W * W) + pb * uu) * iden;       // U~_E
+    const R Cu = (ar1 + pb) * (W * iden) * un;           // 2 sum_j a_j C {u_j}, the sums' a
+    F[0] = (R(0.5) * rho_ln) * (at * W + un);
+    const R s = (at * (U5 + pb) + Cu) * iW;
+#pragma unroll
+    for (int k = 0; k < NU; ++k) F[1 + k] = u[k] * s + a[k] * pb;
+    F[NU + 1] = at * U5 + Cu;
+    Jt = at;
+}
 
 // Two-point EC flux in direction k (eq. ECFluxCurv, eq. UFcircle) for RHD:
 // F = a_t U~ + sum_j a_j F~_j with a = (a_l + a_r)/2 and the RHD pair
@@ -156,39 +268,34 @@ template <int NU, typename R>
 __device__ __forceinline__ void pair_flux_rhd(double G, const NodeRHD<NU, R>& l, const NodeRHD<NU, R>& r,
                                               const double* al, const double* ar, R* F,
                                               double& Jt) {
-    const R rho_ln = log_mean(l.rho, r.rho, l.lr, r.lr);
-    const R beta_ln = log_mean(l.beta, r.beta, l.lb, r.lb);
-    const R rho_m = 0.5 * (l.rho + r.rho);
-    const R beta_m = 0.5 * (l.beta + r.beta);
-    const R W_m = 0.5 * (l.W + r.W);
-    R um[NU];
-    R uu = R(0.0), un = R(0.0);
-    const double at = 0.5 * (al[0] + ar[0]);
-    double ab[NU];
+    pair_flux_rhd_sums<NU, R>(G, l, r, al, ar, F, Jt);
 #pragma unroll
-    for (int k = 0; k < NU; ++k) {
-        um[k] = 0.5 * (l.u[k] + r.u[k]);
-        ab[k] = 0.5 * (al[1 + k] + ar[1 + k]);
-        uu += um[k] * um[k];
-        un += ab[k] * um[k];
-    }
-    R ibl, ibm, iden, iW;
-    frcp2(R((G - 1.0) * beta_ln), beta_m, ibl, ibm);
-    frcp2(R(W_m * W_m - uu), W_m, iden, iW);
-    const R a0 = 1.0 + ibl;
-    const R pb = rho_m * ibm;
-    const R U1 = rho_ln * W_m;
-    const R U5 = (a0 * U1 * W_m + pb * uu) * iden;
-    const R C = W_m * (a0 * rho_ln + pb) * iden;
-    F[0] = rho_ln * (at * W_m + un);
-    const R s = (at * (U5 + pb) + C * un) * iW;
-#pragma unroll
-    for (int k = 0; k < NU; ++k) F[1 + k] = um[k] * s + ab[k] * pb;
-    F[NU + 1] = at * U5 + C * un;
-    Jt = at;
+    for (int c = 0; c < NU + 2; ++c) F[c] = R(0.5) * F[c];
+    Jt = 0.5 * Jt;
 }
 
 #ifndef ES_OPCOUNT_HOST
+// The FP64 reciprocal and root of the FP32-mixed form (two Newton steps): its FP64
+// quantities are rounded to FP32 next, and a last bit that differs now and then moves
+// such a rounding.
+__device__ __forceinline__ double frcp_mixed(double x) {
+    double r = __builtin_amdgcn_rcp(x);
+    double e = fma(-x, r, 1.0);
+    r = fma(r, e, r);
+    e = fma(-x, r, 1.0);
+    return fma(r, e, r);
+}
+__device__ __forceinline__ double psqrt_mixed(double x) {
+    double r = __builtin_amdgcn_rsq(x);
+    const double hx = 0.5 * x;
+    double e = fma(-hx * r, r, 0.5);
+    r = fma(r, e, r);
+    e = fma(-hx * r, r, 0.5);
+    r = fma(r, e, r);
+    const double s = x * r;
+    return fma(fma(-s, s, x), 0.5 * r, s);
+}
+
 // Mixed-precision form of pair_flux_rhd: the pair algebra (means, U~, F~_j) in
 // FP32 except the small-jump branch of the logarithmic means, which stays FP64;
 // the contraction with the metrics and the VCL value in FP64.  The FP32 part is
@@ -201,7 +308,7 @@ __device__ __forceinline__ float log_mean_mixed(double al, double ar, double lna
     const double dif = al - ar;
     if (dif * dif < 1e-2 * (s * s)) {
         // (s/2) / (artanh(f)/f) with the series sum_{k=0}^{7} u^k/(2k+1)
-        const double f = dif * frcp(s);
+        const double f = dif * frcp_mixed(s);
         const double u = f * f;
         double F = 1.0 / 15.0;
         F = fma(F, u, 1.0 / 13.0);
@@ -211,7 +318,7 @@ __device__ __forceinline__ float log_mean_mixed(double al, double ar, double lna
         F = fma(F, u, 1.0 / 5.0);
         F = fma(F, u, 1.0 / 3.0);
         F = fma(F, u, 1.0);
-        return (float)(0.5 * s * frcp(F));
+        return (float)(0.5 * s * frcp_mixed(F));
     }
     return (float)dif * frcp((float)lnal - (float)lnar);
 }
@@ -477,8 +584,18 @@ __device__ __forceinline__ void rotation(const R* n, R T[3][3]) {
         T[2][0] = R(0.0); T[2][1] = R(0.0); T[2][2] = R(1.0);
         return;
     }
-    const R rp = xsqrt(n[0] * n[0] + n[1] * n[1]);
     T[0][0] = n[0]; T[0][1] = n[1]; T[0][2] = n[2];
+    const R rp2 = n[0] * n[0] + n[1] * n[1];
+    if constexpr (std::is_same<R, double>::value) {
+        // (the general root only for a rho_perp whose square is near the range's end)
+        if (rp2 > R(1e-280)) {
+            const R ir = frsqrt(rp2);
+            T[1][0] = -n[1] * ir; T[1][1] = n[0] * ir; T[1][2] = R(0.0);
+            T[2][0] = -n[2] * n[0] * ir; T[2][1] = -n[2] * n[1] * ir; T[2][2] = rp2 * ir;
+            return;
+        }
+    }
+    const R rp = xsqrt(rp2);
     if (rp > R(0.0)) {
         const R ir = frcp(rp);
         T[1][0] = -n[1] * ir; T[1][1] = n[0] * ir; T[1][2] = R(0.0);
@@ -524,7 +641,7 @@ __device__ __forceinline__ FaceCoef<R> face_coefficients(R G, R c0, R c1, R V0, 
     beta = fma(fma(-beta, beta, bb), R(0.5) * k.ib, beta);
     // 1/W = beta/(-V_E), ln rho = V_1 - G/(G-1) - ln(beta)/(G-1) - beta, p = rho/beta
     const R iW = beta * iVE;
-    const R p = k.ib * xexp(V0 - c0 - xlog(beta) * c1 - beta);
+    const R p = k.ib * face_exp(V0 - c0 - face_log(beta) * c1 - beta);
     const R bc = beta + c0;                   // beta h
     k.h = bc * k.ib;
     R ibc;
@@ -892,8 +1009,11 @@ struct NodeV {
 // is formed first from nodes i and i+1 alone.  Its columns are turned into the fixed
 // frame (T^{-1} R), so that the stencil's entropy variables are projected as they are
 // stored, without a rotation per node, and the dissipation needs none afterwards.
-// Bound by FP64 issue; the projections (25 of them per stencil node in 3D) and the five
-// WENO jumps are most of what is left.
+// Bound by FP64 issue; the projections (25 fused operations per stencil node in 3D) and
+// the five WENO jumps are most of what is left.  Taking the columns one at a time
+// (the stencil read from LDS for each) needs 128 registers instead of 166 in 3D, four
+// wavefronts per SIMD instead of three, but 5 % more operations: es_residual at 128^3
+// 529 us against 517.
 template <int DIM, typename R, int P = 3, typename NodeFn>
 __device__ __forceinline__ void face_diss_rhd_fn(R G, R c0, R c1, R eps, NodeFn&& node, const R* al, const R* ar, R* d) {
     constexpr int M = DIM + 2;
