@@ -173,12 +173,8 @@ es_status es_create(const es_grid* grid, const es_scheme* scheme, const es_monit
     if (e == hipSuccess && grid->dim == 3) e = alloc(&c->pi, (size_t)g.enodes * 9);
     if (e == hipSuccess) e = alloc(&c->red, (size_t)c->red_blocks * (3 + 8));
     if (e == hipSuccess) e = alloc(&c->scal, (size_t)es::NSCAL);
-    if (e == hipSuccess) e = alloc(&c->fail, (size_t)4);
-    if (e == hipSuccess) {
-        (void)es::launch_fill_u64(c->fail, 0ull, 2, nullptr);
-        (void)es::launch_fill_u64(c->fail + 3, 0ull, 1, nullptr);
-        e = es::launch_fill_u64(c->fail + 2, ULLONG_MAX, 1, nullptr);
-    }
+    if (e == hipSuccess) e = alloc(&c->fail, (size_t)(es::FAIL_SLOTS * es::FAIL_STRIDE));
+    if (e == hipSuccess) e = es::launch_fail_reset(c->fail, nullptr);
     // the primitive workspace seeds the pressure iteration of the next step: start
     // from zeros (an invalid seed, so the first step uses the bracket midpoint)
     if (e == hipSuccess) e = es::launch_zero(c->prim, (long long)(P * c->nprim), nullptr);
@@ -493,13 +489,19 @@ es_status es_diagnostics(es_ctx* c, const double* prim, const double* U, const d
 es_status es_ctx_status(es_ctx* c, hipStream_t s, long long* n_fail, long long* first_fail) {
     if (c == nullptr) return ES_EINVAL;
     if (hipStreamSynchronize(s) != hipSuccess) return ES_EHIP;
-    unsigned long long h[4];
-    if (hipMemcpy(h, c->fail, sizeof(h), hipMemcpyDeviceToHost) != hipSuccess) return ES_EHIP;
+    unsigned long long slots[es::FAIL_SLOTS * es::FAIL_STRIDE];
+    if (hipMemcpy(slots, c->fail, sizeof(slots), hipMemcpyDeviceToHost) != hipSuccess) return ES_EHIP;
+    unsigned long long h[4] = {0, 0, ULLONG_MAX, 0};
+    for (int k = 0; k < es::FAIL_SLOTS; ++k) {
+        const unsigned long long* q = slots + k * es::FAIL_STRIDE;
+        h[0] += q[0];
+        h[1] += q[1];
+        h[2] = q[2] < h[2] ? q[2] : h[2];
+        h[3] += q[3];
+    }
     if (n_fail) *n_fail = (long long)(h[0] + h[1] + h[3]);
     if (first_fail) *first_fail = h[2] == ULLONG_MAX ? -1 : (long long)h[2];
-    (void)es::launch_fill_u64(c->fail, 0ull, 2, s);
-    (void)es::launch_fill_u64(c->fail + 2, ULLONG_MAX, 1, s);
-    (void)es::launch_fill_u64(c->fail + 3, 0ull, 1, s);
+    (void)es::launch_fail_reset(c->fail, s);
     if (hipStreamSynchronize(s) != hipSuccess) return ES_EHIP;
     if (h[3] > 0) return ES_EMESH;
     if (h[0] > 0) return ES_EADMISSIBLE;

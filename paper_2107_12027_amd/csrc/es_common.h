@@ -150,15 +150,30 @@ __device__ __forceinline__ double mesh_value(const GridDev& g, const double* __r
     return v;
 }
 
-// Failure record of the conservative-to-primitive recovery (device array of 4
-// unsigned 64-bit counters): [0] inadmissible states, [1] iterations that did not
-// converge, [2] smallest failing interior node index, [3] nodes whose evolved
-// Jacobian is not positive (a tangled mesh).  Codes: 1 inadmissible, 2 no
-// convergence, FAIL_MESH non-positive Jacobian.
+// Failure record of the conservative-to-primitive recovery: FAIL_SLOTS records, one
+// cache line apart, of 4 unsigned 64-bit counters each: [0] inadmissible states,
+// [1] iterations that did not converge, [2] smallest failing interior node index,
+// [3] nodes whose evolved Jacobian is not positive (a tangled mesh).  Codes: 1
+// inadmissible, 2 no convergence, FAIL_MESH non-positive Jacobian.  A wavefront adds
+// its failures at once, blocks take the slots in turn, and the host sums the slots
+// up: with two atomics per failing node on one record, a 128^3 step whose state has
+// left the admissible set everywhere took 79 ms, all of it waiting for that line.
 constexpr int FAIL_MESH = 3;
+constexpr int FAIL_SLOTS = 64, FAIL_STRIDE = 16;
+
+// Called by the failing lanes of a wavefront (their interior node indices ascend with
+// the lane, as both index maps of the recovery kernels do).
 __device__ __forceinline__ void record_failure(unsigned long long* fail, int st, long long node) {
-    atomicAdd(&fail[st == 1 ? 0 : (st == FAIL_MESH ? 3 : 1)], 1ull);
-    atomicMin(&fail[2], (unsigned long long)node);
+    const unsigned long long all = __ballot(1), mesh = __ballot(st == FAIL_MESH), inad = __ballot(st == 1);
+    const int lane = (int)__lane_id();
+    if (lane != __ffsll((long long)all) - 1) return;
+    const unsigned b = (blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x;
+    unsigned long long* f = fail + (size_t)(b % FAIL_SLOTS) * FAIL_STRIDE;
+    const unsigned long long other = all & ~(mesh | inad);
+    if (inad) atomicAdd(&f[0], (unsigned long long)__popcll(inad));
+    if (other) atomicAdd(&f[1], (unsigned long long)__popcll(other));
+    if (mesh) atomicAdd(&f[3], (unsigned long long)__popcll(mesh));
+    atomicMin(&f[2], (unsigned long long)node);
 }
 
 // Exact max/min reductions of non-negative doubles: order independent.

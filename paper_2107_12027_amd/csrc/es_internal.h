@@ -36,7 +36,7 @@ struct es_ctx {
                     // metrics with J^0)
     double* red;    // reduction partials
     double* scal;   // device scalars: [0] dt, [1] gmax, [2] dtau, [3..] spare
-    unsigned long long* fail;   // [0] count inadmissible, [1] count no-convergence, [2] first index
+    unsigned long long* fail;   // FAIL_SLOTS failure records (es_common.h)
     int red_blocks;
     // adjoint workspace (allocated by the first adjoint call)
     double* adj_lamU;   // interior, m comps: cotangent of the current stage state
@@ -117,7 +117,7 @@ hipError_t launch_copy(double* dst, const double* src, long long n, hipStream_t 
 hipError_t launch_diagnostics(const es_ctx* c, const double* prim, const double* U,
                               const double* J, const double* dU, const double* dJ, double* out,
                               hipStream_t s);
-hipError_t launch_fill_u64(unsigned long long* p, unsigned long long v, int n, hipStream_t s);
+hipError_t launch_fail_reset(unsigned long long* fail, hipStream_t s);
 
 // RMHD kernels (es_kernels_rmhd.hip), dispatched from the launchers above
 hipError_t launch_prim2con_rmhd(const es_ctx* c, const double* prim, const double* J, double* U,

@@ -26,9 +26,9 @@ __device__ __forceinline__ long long eidx(const GridDev& g, int i, int j, int k)
 // ---------------------------------------------------------------------------
 // utility kernels
 // ---------------------------------------------------------------------------
-__global__ void k_fill_u64(unsigned long long* p, unsigned long long v, int n) {
+__global__ void k_fail_reset(unsigned long long* fail) {
     const int t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t < n) p[t] = v;
+    if (t < FAIL_SLOTS * FAIL_STRIDE) fail[t] = t % FAIL_STRIDE == 2 ? ~0ull : 0ull;
 }
 
 __global__ void k_zero(double* __restrict__ p, long long n) {
@@ -1845,8 +1845,8 @@ int reduction_blocks(const GridDev& g) { return interior_blocks(g); }
 // ---------------------------------------------------------------------------
 // launchers
 // ---------------------------------------------------------------------------
-hipError_t launch_fill_u64(unsigned long long* p, unsigned long long v, int n, hipStream_t s) {
-    k_fill_u64<<<grid_for(n), TPB, 0, s>>>(p, v, n);
+hipError_t launch_fail_reset(unsigned long long* fail, hipStream_t s) {
+    k_fail_reset<<<grid_for(FAIL_SLOTS * FAIL_STRIDE), TPB, 0, s>>>(fail);
     return hipGetLastError();
 }
 
