@@ -49,13 +49,13 @@ PEAK_HBM = 8.0e12                # B/s
 # two-point fluxes (100.9 each), 1 face dissipation (894.5, closed-form columns), state
 # preparation (6) and the flux-difference accumulation (66): 1269.1; two directions: 2538.2.
 # 3D RHD ES: 1640.6 per direction, 4921.7 for the three.  RMHD ES, p = 3 (the
-# numeric face eigen-structure dominates: about 35,400 per face; averaged over
-# smooth states with well-separated eigenvalues): 73905.6 per node in 2D, 111725.0
+# face eigen-structure dominates: about 13,700 per face; averaged over
+# smooth states with well-separated eigenvalues): 30482.9 per node in 2D, 46611.9
 # in 3D.
 RESIDUAL_FLOPS_PER_NODE_2D_RHD = 2538.2
 RESIDUAL_FLOPS_PER_NODE_3D_RHD = 4921.7
-RESIDUAL_FLOPS_PER_NODE_2D_RMHD = 73905.6
-RESIDUAL_FLOPS_PER_NODE_3D_RMHD = 111725.0
+RESIDUAL_FLOPS_PER_NODE_2D_RMHD = 30482.9
+RESIDUAL_FLOPS_PER_NODE_3D_RMHD = 46611.9
 
 # HBM bytes of one es_residual call, from the FETCH_SIZE and WRITE_SIZE counters
 # (rocprofv3 --pmc, one counter per run) of the residual kernel and k_sum_dirs,

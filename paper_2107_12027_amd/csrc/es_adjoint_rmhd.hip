@@ -17,8 +17,8 @@
 //     Y held at their forward values: the reverse of the accumulation, of the
 //     two WENO5 reconstructions (the gradient written out, as for RHD), of the
 //     projections V~ = r_k . T V_j, and of the rotation, then (dV/dP)^T per node.
-// The face eigen-structure is a numeric eigen-decomposition of the symmetric
-// pencil; its derivative along the face entropy variables is not carried (it
+// The face eigen-structure is an eigen-decomposition of a symmetric 6 x 6 matrix; its
+// derivative along the face entropy variables is not carried (it
 // multiplies the WENO jumps, which vanish at the order of the scheme on smooth
 // solutions), so the ES part is the frozen-eigen-structure derivative.
 #include <math.h>
@@ -88,14 +88,14 @@ __global__ void __launch_bounds__(64) k_face_eigen_rmhd(GridDev g, double G, con
     for (int c = 0; c < 8; ++c) { P2[c] = prim[c * P + i2]; P3[c] = prim[c * P + i3]; }
 #pragma unroll
     for (int c = 0; c < NA; ++c) { al[c] = met[(d * NA + c) * P + i2]; ar[c] = met[(d * NA + c) * P + i3]; }
-    double T[3][3], TV2[8], TV3[8], lhat, Rc[8][8];
-    face_eigen_rmhd<DIM>(G, P2, P3, al, ar, T, TV2, TV3, lhat, Rc);
+    double lhat;
     double* o = eig + fp.base[d] + l * fp.nface[d] + f;
     const long long es = fp.nlines[d] * fp.nface[d];
+    auto put = [&](int k, const double* r) {
 #pragma unroll
-    for (int k = 0; k < 8; ++k)
-#pragma unroll
-        for (int i = 0; i < 8; ++i) o[(k * 8 + i) * es] = Rc[k][i];
+        for (int i = 0; i < 8; ++i) o[(k * 8 + i) * es] = r[i];
+    };
+    face_eigen_rmhd<DIM>(G, P2, P3, al, ar, lhat, put);
     o[64 * es] = lhat;
 }
 

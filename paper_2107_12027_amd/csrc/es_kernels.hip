@@ -650,8 +650,6 @@ __global__ void k_temporal_metrics3d(GridDev g, const double* __restrict__ xd, d
 // ---------------------------------------------------------------------------
 // residual: all direction sweeps in one launch
 // ---------------------------------------------------------------------------
-constexpr int LINES = 4;           // line segments (wavefronts) per block
-
 template <int DIM, int PO, bool STASH>
 struct ResidualLDS {
     static constexpr int NU = DIM, M = DIM + 2, NA = DIM + 1, NF = 6 + NU + NA;
@@ -666,120 +664,37 @@ struct ResidualLDS {
 // fits three without.
 __host__ __device__ constexpr bool residual_stash(int dim, bool es, bool mixed) { return es && (dim == 3 || !mixed); }
 
-// Orders the LDS accesses of one wavefront: its lanes exchange data only among
-// themselves (each wavefront owns its line of the LDS buffer), so no block
-// barrier is needed.
-__device__ __forceinline__ void wave_lds_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
-// Residual of all directions: logical blocks [0, nb0) sweep x, [nb0, nb0 + nb1)
-// sweep y, the rest z; direction k writes slab k of Ld (m + 1 components each).
-struct SweepPlan {
-    int nseg[3];          // segments per sequence (blocks of the sweep)
-    int nblk[3];          // blocks of the sweep
-    long long nlines[3];  // lines of the sweep
-    int flat[3];          // flat (1) or aligned (0) layout of the segments
-    int nsl[3];           // segments per line of the aligned layout
-    double idxi[3];       // 1 / dxi
-    double c0, c1;        // Gamma / (Gamma - 1), 1 / (Gamma - 1)
-};
-
 // One wavefront per segment of the lines along DIR, LINES of them a block: loads the
 // segments with their halos into LDS, evaluates the two-point fluxes owned by each node, the face
 // dissipation and the flux differences, and writes this direction's part of the
 // residual (m components and J) to out.  The fluxes F(s-n, s) and the
 // dissipation of face s-1/2 come from the lanes that own them (lane shuffles).
-//
-// The lines are dealt to LINES sequences so that the wavefronts of a block work on
-// adjacent lines (es_seq.h); segment w of a sequence holds 64 consecutive positions
-// and owns the interior nodes among its lanes ng..63.  Flat layout: the positions
-// of the lines' padded node sequences (n + 2 ng nodes each) laid end to end, so a
-// segment may run across the end of one line into the next; every stencil an owned
-// node uses stays within its own line's padded nodes, and the pair fluxes and faces
-// that straddle two lines are computed and never used.  Aligned layout: ceil(n / SEG)
-// segments per line.  Flat is taken where it saves at least an eighth of the
-// wavefronts: aligned, a line of n = 128 nodes would take three, the third with 6
-// owned nodes but the full instruction stream.
 template <int DIM, int DIR, bool ES, bool MIXED, int PO>
 __device__ __forceinline__ void residual_segment(const GridDev& g, double G, double eps,
                                                  const double* __restrict__ prim,
                                                  const double* __restrict__ met,
                                                  double* __restrict__ out, int blk, const SweepPlan& sw,
                                                  ResidualLDS<DIM, PO, residual_stash(DIM, ES, MIXED)>& lds) {
-    const int nseg = sw.nseg[DIR], nsl = sw.nsl[DIR];
-    const long long nlines = sw.nlines[DIR];
-    const bool flat = sw.flat[DIR] != 0;
     constexpr int NU = DIM, M = DIM + 2, NA = DIM + 1;
-    constexpr int NGP = ghost_layers(PO), SEGP = seg_nodes(PO), NLOADP = seg_loads(PO);
     // F_V0: the first entropy variable, which the FP64 dissipation projects
     constexpr int F_RHO = 0, F_V0 = 1, F_BETA = 2, F_W = 3, F_LR = 4, F_LB = 5, F_U = 6,
                   F_A = 6 + NU;
     auto& sd = lds.sd;
 
-    const int lane = threadIdx.x & 63;
-    const int line = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    // segment w (nseg of them per sequence) of sequence `line`; blk numbers this
-    // sweep's blocks
-    const long long w = blk;
-    if (w >= nseg) return;
-    const int nAlong = g.n[DIR];
-    const int PL = nAlong + 2 * NGP;                    // padded nodes of a line
-    const long long f0 = w * SEGP;                      // sequence position of lane 0
-    const long long pstride = DIR == 0 ? 1 : (DIR == 1 ? (long long)g.P[0] : (long long)g.P[0] * g.P[1]);
-    const long long istride = DIR == 0 ? 1 : (DIR == 1 ? (long long)g.n[0] : (long long)g.n[0] * g.n[1]);
+    const Segment<DIR, PO> sg(g, sw, blk);
+    constexpr bool COOP = Segment<DIR, PO>::COOP;
+    const int lane = sg.lane, line = sg.line, cl = sg.cl, cq = sg.cq;
     const long long P = g.pnodes;
     const long long N = g.nodes;
-    // line and along-coordinate s (-ng .. n + ng - 1) of sequence l's position f0 + q,
-    // and the padded / interior index of the line's node 0
-    const int nf = DIR == 0 ? g.n[1] : g.n[0];
-    const SeqBase sb = flat ? seq_base(f0, PL, NGP, nf, LINES, 0)
-                            : seq_base_aligned(w, nsl, SEGP, 0, NGP, nf, LINES, 0);
-    auto locate = [&](int l, int q, long long& lid, int& s, long long& pbase, long long& ibase) {
-        SeqBase b = sb;
-        b.fa += l;
-        while (b.fa >= nf) { b.fa -= nf; ++b.fb; }
-        int fa, fb;
-        seq_at(b, q, flat, PL, NGP, nf, LINES, l, lid, s, fa, fb);
-        if (s >= nAlong + NGP) lid = nlines;   // past the line's padded end (aligned)
-        const int ci = DIR == 0 ? 0 : fa, cj = DIR == 0 ? fa : (DIR == 1 ? 0 : fb), ck = DIR == 2 ? 0 : fb;
-        pbase = pidx(g, ci, cj, ck);
-        ibase = iidx(g, ci, cj, ck);
-    };
-
-    // ---- load the segments with their halos into LDS: positions 0..NLOADP - 1 of each
-    // of the block's LINES lines.  Along x a wavefront loads its own line, lane q
-    // position q (64 consecutive doubles an instruction).  Along y and z the nodes of a
-    // line are a row or a plane apart, so that a wavefront loading its own line would
-    // touch 64 cache lines an instruction and the block as a whole each of them LINES
-    // times; there the block's threads take the LINES lines, neighbours along x,
-    // together: thread t position t / LINES of line t % LINES, a quarter of the cache
-    // lines per instruction.  (That address rate, not arithmetic, bounded the kernel:
-    // without its dissipation the 128^3 residual took 540 of 625 us.)  The positions
-    // from 64 on are loaded by the first threads as well; both positions' loads are
-    // issued before the first of them is used, from addresses that are always valid (a
-    // position off the lines reads node 0), so the wavefront waits on memory once.
-    constexpr bool COOP = DIR != 0;
-    constexpr int NSEC = NLOADP - 64;
-    static_assert(NLOADP > 64 && NSEC * LINES <= 64, "the positions from 64 on fit one wavefront");
-    const int cl = COOP ? (int)threadIdx.x % LINES : line, cq = COOP ? (int)threadIdx.x / LINES : lane;
-    constexpr int NV = M + 2 + NA;   // rho, u, p, ln rho, ln beta, then the metrics
-    auto index = [&](int q, bool use) {
-        long long lid, pb, ib;
-        int s;
-        locate(cl, q, lid, s, pb, ib);
-        (void)ib;
-        return use && lid < nlines ? pb + (long long)s * pstride : 0;
-    };
+    // ---- the segments with their halos into LDS: rho, u, p, ln rho, ln beta, then the
+    // metrics
+    constexpr int NV = M + 2 + NA;
     auto fetch = [&](long long idx, double* v) {
 #pragma unroll
         for (int c = 0; c < M + 2; ++c) v[c] = prim[c * P + idx];
 #pragma unroll
         for (int c = 0; c < NA; ++c) v[M + 2 + c] = met[(DIR * NA + c) * P + idx];
     };
-    // (a position off the lines holds node 0's state: no owned node's stencil reads it)
     auto stash = [&](int q, const double* v) {
         const double rho = v[0], p = v[M - 1];
         double uu = 0.0;
@@ -797,23 +712,7 @@ __device__ __forceinline__ void residual_segment(const GridDev& g, double G, dou
 #pragma unroll
         for (int c = 0; c < NA; ++c) sd[cl][F_A + c][q] = v[M + 2 + c];
     };
-    if (!COOP || line == 0) {
-        const bool sec = cq < NSEC;
-        double v0[NV], v1[NV];
-        fetch(index(cq, true), v0);
-        fetch(index(64 + (sec ? cq : 0), sec), v1);
-        // every load issued before any of them is used (and none of the second
-        // position's sunk into its branch, behind the first wait)
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int c = 0; c < NV; ++c) form_here(v1[c]);
-        stash(cq, v0);
-        if (sec) stash(64 + cq, v1);
-    } else {
-        double v0[NV];
-        fetch(index(cq, true), v0);
-        stash(cq, v0);
-    }
+    sg.template load<NV>(fetch, stash);
     if (COOP) __syncthreads();
     else wave_lds_sync();
 
@@ -944,11 +843,8 @@ __device__ __forceinline__ void residual_segment(const GridDev& g, double G, dou
 #pragma unroll
         for (int c = 0; c <= M; ++c) R[c] = sd[cl][c][cq];
     }
-    long long lid, pb, ib;
-    int s;
-    locate(cl, cq, lid, s, pb, ib);
-    if (lid < nlines && cq >= NGP && s >= 0 && s < nAlong) {
-        const long long o = ib + (long long)s * istride;
+    const long long o = sg.owned();
+    if (o >= 0) {
 #pragma unroll
         for (int c = 0; c <= M; ++c) out[c * N + o] = R[c];
     }
@@ -1975,28 +1871,9 @@ template <int DIM>
 static void residual_all(const es_ctx* c, const double* prim, const double* met, double* Ld,
                          hipStream_t s) {
     const GridDev& g = c->g;
-    SweepPlan sw{};
-    long long nb = 0;
-    const int segn = seg_nodes(g.p);
-    for (int d = 0; d < DIM; ++d) {
-        long long nl = 1;
-        for (int a = 0; a < DIM; ++a)
-            if (a != d) nl *= g.n[a];
-        // segments per sequence (the lines dealt to LINES sequences): flat, until the
-        // one owning the longest sequence's last interior node; aligned, ceil(n / SEG)
-        // per line.  One block per segment offset, one wavefront per sequence.
-        const long long pl = g.n[d] + 2 * g.ng, ml = (nl + LINES - 1) / LINES;
-        sw.flat[d] = seq_flat(g.n[d], (int)pl, segn, 0.875) ? 1 : 0;
-        sw.nsl[d] = (g.n[d] + segn - 1) / segn;
-        sw.nseg[d] = sw.flat[d] ? (int)(((ml - 1) * pl + g.n[d] - 1) / segn + 1) : (int)(ml * sw.nsl[d]);
-        sw.nlines[d] = nl;
-        sw.nblk[d] = sw.nseg[d];
-        sw.idxi[d] = 1.0 / g.dxi[d];
-        nb += sw.nblk[d];
-    }
     const double G = c->scheme.gamma, eps = c->scheme.weno_eps;
-    sw.c0 = G / (G - 1.0);
-    sw.c1 = 1.0 / (G - 1.0);
+    long long nb;
+    const SweepPlan sw = sweep_plan(g, G, nb);
     const bool es_ = c->scheme.dissipation != 0, mixed = c->scheme.mixed != 0;
     if (g.p == 2) residual_launch<DIM, 2>(es_, mixed, (unsigned)nb, s, g, G, eps, prim, met, Ld, sw);
     else if (g.p == 4) residual_launch<DIM, 4>(es_, mixed, (unsigned)nb, s, g, G, eps, prim, met, Ld, sw);

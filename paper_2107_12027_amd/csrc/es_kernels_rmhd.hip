@@ -1,6 +1,6 @@
 // RMHD kernels of libes.so (gfx950): primitive <-> conservative, the residual
-// (EC pair fluxes, Godunov-Powell source, VCL, ES dissipation with the numeric
-// eigen-structure), the CFL spectral radius and the FP64 diagnostics.  Same
+// (EC pair fluxes, Godunov-Powell source, VCL, ES dissipation with the face
+// eigen-structure of a 6 x 6 symmetric matrix), the CFL spectral radius and the FP64 diagnostics.  Same
 // launch shapes and layouts as the RHD kernels; 8 conservative components,
 // padded primitive fields (rho, u_1..3, p, B_1..3, ln rho, ln beta).
 #include <float.h>
@@ -77,109 +77,128 @@ __global__ void k_con2prim_rmhd(GridDev g, double G, StateSrc ss, double* prim, 
 }
 
 // ---------------------------------------------------------------------------
-// residual: one wavefront per line segment of seg_nodes(p) nodes (as the RHD
-// residual)
+// residual: one wavefront per line segment of seg_nodes(p) nodes, LINES neighbouring
+// lines per block (as the RHD residual).  Bound with the dissipation by the FP64 issue
+// of the eigen-structure (about 13,700 operations a face, most of them Jacobi
+// rotations) at two wavefronts per SIMD: 256 registers and, for the rare faces with
+// eigen-groups, a basis in scratch.  A 512^2 adaptive RK3 step takes 0.81 ms (3.41 with
+// the dense 8 x 8 pencil), a rotor step, most of whose faces have groups, 1.63 ms
+// (2.84).  Without the dissipation (160^2 moving mesh, EC) a step takes 79 us (95): the
+// node quantities of the pair fluxes come once per node from LDS, by shuffles.
 // ---------------------------------------------------------------------------
-constexpr int RLINES = 2;
-
-template <int DIM, int PO>
+// LDS of a block: per line the node quantities the pair fluxes, the source and the
+// dissipation read (formed once per node instead of once per use), and the flux
+// differences of each lane while the dissipation runs.
+template <int DIM, int PO, bool ES>
 struct ResidualLDSM {
-    static constexpr int NA = DIM + 1, NF = MR + 2 + NA;
-    double sd[RLINES][NF][seg_loads(PO) + 1];
-    double sp[RLINES][PO > 2 ? PO : 2][MR + 2][64];    // pair fluxes F (8), J and B~ values
+    static constexpr int NA = DIM + 1, NF = 16 + NA;
+    double sd[LINES][NF][seg_loads(PO) + 1];
+    double rs[ES ? LINES : 1][ES ? MR + 1 : 1][64];
 };
 
-struct SweepPlanM {
-    int nseg[3];
-    int nblk[3];
-    long long nlines[3];
-};
+// node quantities in LDS
+constexpr int F_RHO = 0, F_V0 = 1, F_BETA = 2, F_W = 3, F_LR = 4, F_LB = 5, F_B0 = 6, F_U = 7, F_BV = 10, F_B = 13,
+              F_A = 16;
+
+// Dissipation of face s+1/2 from the staged nodes (nd: node s's first quantity).
+template <int DIM, bool MIXED, int PO>
+__device__ __forceinline__ void face_diss_segment(double G, double c0, double c1, double eps, const double* nd,
+                                                  double* d) {
+    constexpr int ROW = seg_loads(PO) + 1;
+    face_diss_rmhd_fn<DIM, MIXED, PO>(
+        G, c0, c1, eps,
+        [&](int j) {
+            const double* q = nd + (j - (PO - 1));
+            NodeVM n;
+            n.V0 = q[F_V0 * ROW];
+            n.beta = q[F_BETA * ROW];
+            n.W = q[F_W * ROW];
+#pragma unroll
+            for (int k = 0; k < 3; ++k) { n.u[k] = q[(F_U + k) * ROW]; n.b[k] = q[(F_BV + k) * ROW]; }
+            return n;
+        },
+        [&](double* al, double* ar) {
+#pragma unroll
+            for (int c = 0; c <= DIM; ++c) { al[c] = nd[(F_A + c) * ROW]; ar[c] = nd[(F_A + c) * ROW + 1]; }
+        },
+        d);
+}
 
 template <int DIM, int DIR, bool ES, bool MIXED, int PO>
 __device__ __forceinline__ void residual_segment_rmhd(const GridDev& g, double G, double eps,
                                                       const double* __restrict__ prim,
                                                       const double* __restrict__ met,
-                                                      double* __restrict__ out, int blk, int nseg,
-                                                      long long nlines, ResidualLDSM<DIM, PO>& lds) {
+                                                      double* __restrict__ out, int blk, const SweepPlan& sw,
+                                                      ResidualLDSM<DIM, PO, ES>& lds) {
     constexpr int NA = DIM + 1;
-    constexpr int NGP = ghost_layers(PO), SEGP = seg_nodes(PO), NLOADP = seg_loads(PO);
-    constexpr int F_LR = MR, F_LB = MR + 1, F_A = MR + 2;
     auto& sd = lds.sd;
-    auto& sp = lds.sp;
-    const int lane = threadIdx.x & 63;
-    const int line = threadIdx.x >> 6;
-    const int seg = blk % nseg;
-    const long long lid = (long long)(blk / nseg) * RLINES + line;
-    const bool active = lid < nlines;
-    const int nAlong = g.n[DIR];
-    const int s0 = seg * SEGP;
-    const int s_end = min(s0 + SEGP, nAlong);
-    int ci = 0, cj = 0, ck = 0;
-    if (active) {
-        if (DIR == 0) { cj = (int)(lid % g.n[1]); ck = (int)(lid / g.n[1]); }
-        else if (DIR == 1) { ci = (int)(lid % g.n[0]); ck = (int)(lid / g.n[0]); }
-        else { ci = (int)(lid % g.n[0]); cj = (int)(lid / g.n[0]); }
-    }
-    const long long pstride = DIR == 0 ? 1 : (DIR == 1 ? (long long)g.P[0] : (long long)g.P[0] * g.P[1]);
-    const long long istride = DIR == 0 ? 1 : (DIR == 1 ? (long long)g.n[0] : (long long)g.n[0] * g.n[1]);
-    const long long pbase = pidx(g, ci, cj, ck);
-    const long long ibase = iidx(g, ci, cj, ck);
+    const Segment<DIR, PO> sg(g, sw, blk);
+    constexpr bool COOP = Segment<DIR, PO>::COOP;
+    constexpr int NGP = ghost_layers(PO);
+    const int lane = sg.lane, line = sg.line, cl = sg.cl, cq = sg.cq;
     const long long P = g.pnodes, N = g.nodes;
 
-    // Lane q holds position q and, for q < NLOADP - 64, position 64 + q as well: the
-    // loads of both are issued before either is used, from addresses that are always
-    // valid and outside any branch (a position off the line reads node 0 and then
-    // takes the far-field values instead), so the wavefront waits on memory once.
-    static_assert(NLOADP > 64 && NLOADP <= 128, "two positions per lane");
-    {
-        constexpr int NV = MR + 2 + NA;
-        const bool sec = lane < NLOADP - 64;
-        const int sa = s0 - NGP + lane, sb = s0 - NGP + 64 + (sec ? lane : 0);
-        const bool oka = active && sa < s_end + NGP, okb = sec && active && sb < s_end + NGP;
-        const long long ia = oka ? pbase + (long long)sa * pstride : 0;
-        const long long ib = okb ? pbase + (long long)sb * pstride : 0;
-        double va[NV], vb[NV];
+    sg.template load<MR + 2 + NA>(
+        [&](long long idx, double* v) {
 #pragma unroll
-        for (int c = 0; c < MR + 2; ++c) {
-            va[c] = prim[c * P + ia];
-            vb[c] = prim[c * P + ib];
-        }
+            for (int c = 0; c < MR + 2; ++c) v[c] = prim[c * P + idx];
 #pragma unroll
-        for (int c = 0; c < NA; ++c) {
-            va[F_A + c] = met[(DIR * NA + c) * P + ia];
-            vb[F_A + c] = met[(DIR * NA + c) * P + ib];
-        }
-        // every load issued before any of them is used
-        __builtin_amdgcn_sched_barrier(0);
-        // far field: rho = p = 1, the metric (0, 1, 0, ...), the rest 0
+            for (int c = 0; c < NA; ++c) v[MR + 2 + c] = met[(DIR * NA + c) * P + idx];
+        },
+        [&](int q, const double* v) {
+            const double beta = v[0] * frcp(v[4]);
+            const double W = psqrt(1.0 + v[1] * v[1] + v[2] * v[2] + v[3] * v[3]), iW = frcp(W);
+            const double b0 = v[1] * v[5] + v[2] * v[6] + v[3] * v[7];      // W (v . B)
+            sd[cl][F_RHO][q] = v[0];
+            sd[cl][F_V0][q] = sw.c0 + v[MR] + v[MR + 1] * sw.c1 + beta;
+            sd[cl][F_BETA][q] = beta;
+            sd[cl][F_W][q] = W;
+            sd[cl][F_LR][q] = v[MR];
+            sd[cl][F_LB][q] = v[MR + 1];
+            sd[cl][F_B0][q] = b0;
 #pragma unroll
-        for (int c = 0; c < NV; ++c) {
-            const double far = (c == 0 || c == 4 || c == F_A + 1) ? 1.0 : 0.0;
-            va[c] = oka ? va[c] : far;
-            vb[c] = okb ? vb[c] : far;
-        }
-        // the lanes without a second position store their own again (the same
-        // values): no branch, so the second loads are not sunk after the first wait
+            for (int k = 0; k < 3; ++k) {
+                sd[cl][F_U + k][q] = v[1 + k];
+                sd[cl][F_BV + k][q] = (v[5 + k] + b0 * v[1 + k]) * iW;      // B/W + W (v . B) v
+                sd[cl][F_B + k][q] = v[5 + k];
+            }
 #pragma unroll
-        for (int c = 0; c < NV; ++c) {
-            sd[line][c][lane] = va[c];
-            sd[line][c][sec ? 64 + lane : lane] = sec ? vb[c] : va[c];
-        }
-    }
-    __syncthreads();
+            for (int c = 0; c < NA; ++c) sd[cl][F_A + c][q] = v[MR + 2 + c];
+        });
+    if (COOP) __syncthreads();
+    else wave_lds_sync();
 
-    auto prim_at = [&](int q, double* Pq) {
-#pragma unroll
-        for (int c = 0; c < MR; ++c) Pq[c] = sd[line][c][q];
-    };
     auto node_at = [&](int q) {
-        double Pq[MR];
-        prim_at(q, Pq);
-        return node_rmhd(G, Pq, sd[line][F_LR][q], sd[line][F_LB][q]);
+        NodeRMHD n;
+        n.rho = sd[line][F_RHO][q];
+        n.beta = sd[line][F_BETA][q];
+        n.W = sd[line][F_W][q];
+        n.lr = sd[line][F_LR][q];
+        n.lb = sd[line][F_LB][q];
+        n.b0 = sd[line][F_B0][q];
+        n.Wb0 = n.W * n.b0;
+        n.b02 = n.b0 * n.b0;
+        n.Wb02 = n.W * n.b02;
+        n.sb = 0.0;
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            n.u[k] = sd[line][F_U + k][q];
+            n.b[k] = sd[line][F_BV + k][q];
+            n.B[k] = sd[line][F_B + k][q];
+            n.bk2[k] = n.b[k] * n.b[k];
+            n.Wbk2[k] = n.W * n.bk2[k];
+            n.sb += n.bk2[k];
+        }
+        return n;
     };
 
-    const int s_own = s0 - NGP + lane;
-    if (active && s_own < s_end) {
+    // ---- pair fluxes (s, s+n) owned by the lane of node s and the flux differences;
+    // F(s-n, s) comes from the lane that formed it
+    double R[MR + 1];
+    {
+        double acc[MR + 2];                     // fluxes, J and B~ pair values
+#pragma unroll
+        for (int c = 0; c < MR + 2; ++c) acc[c] = 0.0;
         const NodeRMHD l = node_at(lane);
         double al[NA];
 #pragma unroll
@@ -187,102 +206,87 @@ __device__ __forceinline__ void residual_segment_rmhd(const GridDev& g, double G
 #pragma unroll 1
         for (int n = 1; n <= PO; ++n) {
             const NodeRMHD r = node_at(lane + n);
-            double ar[NA];
+            double ar[NA], F[MR + 2];
 #pragma unroll
             for (int c = 0; c < NA; ++c) ar[c] = sd[line][F_A + c][lane + n];
-            double F[MR], Jt, Bt;
-            pair_flux_rmhd<DIM, typename std::conditional<MIXED, float, double>::type>(G, l, r, al, ar, F, Jt,
-                                                                                         Bt);
+            pair_flux_rmhd<DIM, typename std::conditional<MIXED, float, double>::type>(G, l, r, al, ar, F, F[MR],
+                                                                                         F[MR + 1]);
+            const double w = alpha_pn(PO, n) * sw.idxi[DIR];
 #pragma unroll
-            for (int c = 0; c < MR; ++c) sp[line][n - 1][c][lane] = F[c];
-            sp[line][n - 1][MR][lane] = Jt;
-            sp[line][n - 1][MR + 1][lane] = Bt;
+            for (int c = 0; c < MR + 2; ++c) acc[c] += w * (F[c] - __shfl_up(F[c], n, 64));
         }
-    }
-    __syncthreads();
-
-    const bool owner = active && lane >= NGP && s_own < s_end;
-    const double idxi = 1.0 / g.dxi[DIR];
-    double R[MR + 1];
+        // the Godunov-Powell source -Phi'(V_i) (B~ differences), Phi' = (0, b/W, b^0/W, v)
+        const double iW = frcp(l.W), sB = acc[MR + 1] * iW;
+        R[0] = -acc[0];
+        R[4] = -acc[4] - l.b0 * sB;
 #pragma unroll
-    for (int c = 0; c <= MR; ++c) R[c] = 0.0;
-    if (owner) {
-        double diff[MR + 2];
-#pragma unroll
-        for (int c = 0; c < MR + 2; ++c) {
-            double s = 0.0;
-#pragma unroll
-            for (int n = 1; n <= PO; ++n)
-                s += alpha_pn(PO, n) * (sp[line][n - 1][c][lane] - sp[line][n - 1][c][lane - n]);
-            diff[c] = s * idxi;
+        for (int k = 0; k < 3; ++k) {
+            R[1 + k] = -acc[1 + k] - l.b[k] * sB;
+            R[5 + k] = -acc[5 + k] - l.u[k] * sB;
         }
-        // flux differences and the Godunov-Powell source -Phi'(V_i) (B~ differences)
-        double Pq[MR];
-        prim_at(lane, Pq);
-        const StateRMHD<double> st = rmhd_state<double>(G, Pq);
-        double Pp[MR];
-        rmhd_phi_prime<double>(st, Pp);
-#pragma unroll
-        for (int c = 0; c < MR; ++c) R[c] = -diff[c] - Pp[c] * diff[MR + 1];
-        R[MR] = -diff[MR];
+        R[MR] = -acc[MR];
     }
 
     if (ES) {
-        __syncthreads();
-        // the flux differences wait in the (now free) pair slot 1 while the face
-        // dissipation runs (register pressure)
-        if (owner) {
+        // the flux differences wait in LDS while the face dissipation runs (register
+        // pressure)
 #pragma unroll
-            for (int c = 0; c <= MR; ++c) sp[line][1][c][lane] = R[c];
+        for (int c = 0; c <= MR; ++c) lds.rs[line][c][lane] = R[c];
+        wave_lds_sync();
+        // ---- face dissipation at s+1/2 for the faces of owned nodes
+        double d[MR];
+#pragma unroll
+        for (int c = 0; c < MR; ++c) d[c] = 0.0;
+        bool face;
+        {
+            long long pb, ib;
+            int s;
+            face = sg.locate(line, lane, s, pb, ib) && lane >= NGP - 1 && s >= -1 && s < sg.n;
         }
-        if (active && lane >= PO - 1 && s_own < s_end) {
-            double Pn[2 * PO][MR];
-#pragma unroll
-            for (int q = 0; q < 2 * PO; ++q) prim_at(lane - (PO - 1) + q, Pn[q]);
-            double al[NA], ar[NA];
-#pragma unroll
-            for (int c = 0; c < NA; ++c) { al[c] = sd[line][F_A + c][lane]; ar[c] = sd[line][F_A + c][lane + 1]; }
-            double d[MR];
-            face_diss_rmhd<DIM, MIXED, PO>(G, eps, Pn, al, ar, d);
-#pragma unroll
-            for (int c = 0; c < MR; ++c) sp[line][0][c][lane] = d[c];
+        if (face) {
+            face_diss_segment<DIM, MIXED, PO>(G, sw.c0, sw.c1, eps, &sd[line][0][lane], d);
         }
-        __syncthreads();
-        if (owner) {
 #pragma unroll
-            for (int c = 0; c <= MR; ++c) R[c] = sp[line][1][c][lane];
+        for (int c = 0; c <= MR; ++c) R[c] = lds.rs[line][c][lane];
 #pragma unroll
-            for (int c = 0; c < MR; ++c) R[c] += 0.5 * (sp[line][0][c][lane] - sp[line][0][c][lane - 1]) * idxi;
-        }
+        for (int c = 0; c < MR; ++c) R[c] += 0.5 * (d[c] - __shfl_up(d[c], 1, 64)) * sw.idxi[DIR];
     }
 
-    if (owner) {
-        const long long o = ibase + (long long)s_own * istride;
+    if (COOP) {
+        wave_lds_sync();
+#pragma unroll
+        for (int c = 0; c <= MR; ++c) sd[line][c][lane] = R[c];
+        __syncthreads();
+#pragma unroll
+        for (int c = 0; c <= MR; ++c) R[c] = sd[cl][c][cq];
+    }
+    const long long o = sg.owned();
+    if (o >= 0) {
 #pragma unroll
         for (int c = 0; c <= MR; ++c) out[c * N + o] = R[c];
     }
 }
 
 template <int DIM, bool ES, bool MIXED, int PO>
-__global__ void __launch_bounds__(128) k_residual_rmhd(GridDev g, double G, double eps,
-                                                       const double* __restrict__ prim,
-                                                       const double* __restrict__ met,
-                                                       double* __restrict__ Ld, SweepPlanM sw) {
-    __shared__ ResidualLDSM<DIM, PO> lds;
+__global__ void __launch_bounds__(64 * LINES) __attribute__((amdgpu_waves_per_eu(2))) k_residual_rmhd(GridDev g, double G, double eps,
+                                                              const double* __restrict__ prim,
+                                                              const double* __restrict__ met,
+                                                              double* __restrict__ Ld, SweepPlan sw) {
+    __shared__ ResidualLDSM<DIM, PO, ES> lds;
     const long long slab = (long long)(MR + 1) * g.nodes;
     int b = xcd_block((int)blockIdx.x, (int)gridDim.x);
     if (b < sw.nblk[0]) {
-        residual_segment_rmhd<DIM, 0, ES, MIXED, PO>(g, G, eps, prim, met, Ld, b, sw.nseg[0], sw.nlines[0], lds);
+        residual_segment_rmhd<DIM, 0, ES, MIXED, PO>(g, G, eps, prim, met, Ld, b, sw, lds);
         return;
     }
     b -= sw.nblk[0];
     if (DIM == 2 || b < sw.nblk[1]) {
-        residual_segment_rmhd<DIM, 1, ES, MIXED, PO>(g, G, eps, prim, met, Ld + slab, b, sw.nseg[1], sw.nlines[1], lds);
+        residual_segment_rmhd<DIM, 1, ES, MIXED, PO>(g, G, eps, prim, met, Ld + slab, b, sw, lds);
         return;
     }
     b -= sw.nblk[1];
     if (DIM == 3)
-        residual_segment_rmhd<DIM, 2, ES, MIXED, PO>(g, G, eps, prim, met, Ld + 2 * slab, b, sw.nseg[2], sw.nlines[2], lds);
+        residual_segment_rmhd<DIM, 2, ES, MIXED, PO>(g, G, eps, prim, met, Ld + 2 * slab, b, sw, lds);
 }
 
 // CFL partial maxima: rho_k = L_k max_m |lambda_m| / J per direction (eq. cfl), the
@@ -380,20 +384,10 @@ template <int DIM>
 static void residual_all_rmhd(const es_ctx* c, const double* prim, const double* met, double* Ld,
                               hipStream_t s) {
     const GridDev& g = c->g;
-    SweepPlanM sw{};
-    long long nb = 0;
-    const int segn = seg_nodes(g.p);
-    for (int d = 0; d < DIM; ++d) {
-        sw.nseg[d] = (g.n[d] + segn - 1) / segn;
-        long long nl = 1;
-        for (int a = 0; a < DIM; ++a)
-            if (a != d) nl *= g.n[a];
-        sw.nlines[d] = nl;
-        sw.nblk[d] = (int)(((nl + RLINES - 1) / RLINES) * sw.nseg[d]);
-        nb += sw.nblk[d];
-    }
     const double G = c->scheme.gamma, eps = c->scheme.weno_eps;
-    const dim3 grid((unsigned)nb), block(64 * RLINES);
+    long long nb;
+    const SweepPlan sw = sweep_plan(g, G, nb);
+    const dim3 grid((unsigned)nb), block(64 * LINES);
     const bool es = c->scheme.dissipation != 0, mixed = c->scheme.mixed != 0;
     if (c->scheme.order_p == 2) {
         if (es && mixed) k_residual_rmhd<DIM, true, true, 2><<<grid, block, 0, s>>>(g, G, eps, prim, met, Ld, sw);

@@ -103,6 +103,153 @@ __device__ __forceinline__ double block_reduce(double v, double* sh) {
     return r;
 }
 
+// Orders the LDS accesses of one wavefront: its lanes exchange data only among
+// themselves (each wavefront owns its line of the LDS buffer), so no block
+// barrier is needed.
+__device__ __forceinline__ void wave_lds_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// Segments of the residual kernels' sweeps.  The lines along a direction are dealt to LINES
+// sequences so that the LINES wavefronts of a block work on adjacent lines (es_seq.h);
+// segment w of a sequence holds 64 consecutive positions (and the ng after them) and owns
+// the interior nodes among its lanes ng..63.  Flat layout: the positions of the lines'
+// padded node sequences (n + 2 ng nodes each) laid end to end, so a segment may run across
+// the end of one line into the next; every stencil an owned node uses stays within its own
+// line's padded nodes, and the pair fluxes and faces that straddle two lines are computed
+// and never used.  Aligned layout: ceil(n / SEG) segments per line.  Flat is taken where it
+// saves at least an eighth of the wavefronts: aligned, a line of n = 128 nodes would take
+// three, the third with 6 owned nodes but the full instruction stream.
+//
+// Along x a wavefront loads and stores its own line, lane q position q (64 consecutive
+// doubles an instruction).  Along y and z the nodes of a line are a row or a plane apart,
+// so that a wavefront loading its own line would touch 64 cache lines an instruction and
+// the block as a whole each of them LINES times; there the block's threads take the LINES
+// lines, neighbours along x, together: thread t position t / LINES of line t % LINES, a
+// quarter of the cache lines per instruction.  (That address rate, not arithmetic, bounded
+// the RHD kernel: without its dissipation the 128^3 residual took 540 of 625 us; 370 of 517
+// after.)
+constexpr int LINES = 4;           // line segments (wavefronts) per block
+
+// Residual of all directions: logical blocks [0, nblk0) sweep x, [nblk0, nblk0 + nblk1)
+// sweep y, the rest z; direction k writes slab k of Ld (m + 1 components each).
+struct SweepPlan {
+    int nseg[3];          // segments per sequence (blocks of the sweep)
+    int nblk[3];          // blocks of the sweep
+    long long nlines[3];  // lines of the sweep
+    int flat[3];          // flat (1) or aligned (0) layout of the segments
+    int nsl[3];           // segments per line of the aligned layout
+    double idxi[3];       // 1 / dxi
+    double c0, c1;        // Gamma / (Gamma - 1), 1 / (Gamma - 1)
+};
+
+// the plan of a grid and its number of blocks
+inline SweepPlan sweep_plan(const GridDev& g, double gamma, long long& nb) {
+    SweepPlan sw{};
+    nb = 0;
+    const int segn = seg_nodes(g.p);
+    for (int d = 0; d < g.dim; ++d) {
+        long long nl = 1;
+        for (int a = 0; a < g.dim; ++a)
+            if (a != d) nl *= g.n[a];
+        // segments per sequence (the lines dealt to LINES sequences): flat, until the
+        // one owning the longest sequence's last interior node; aligned, ceil(n / SEG)
+        // per line.  One block per segment offset, one wavefront per sequence.
+        const long long pl = g.n[d] + 2 * g.ng, ml = (nl + LINES - 1) / LINES;
+        sw.flat[d] = seq_flat(g.n[d], (int)pl, segn, 0.875) ? 1 : 0;
+        sw.nsl[d] = (g.n[d] + segn - 1) / segn;
+        sw.nseg[d] = sw.flat[d] ? (int)(((ml - 1) * pl + g.n[d] - 1) / segn + 1) : (int)(ml * sw.nsl[d]);
+        sw.nlines[d] = nl;
+        sw.nblk[d] = sw.nseg[d];
+        sw.idxi[d] = 1.0 / g.dxi[d];
+        nb += sw.nblk[d];
+    }
+    sw.c0 = gamma / (gamma - 1.0);
+    sw.c1 = 1.0 / (gamma - 1.0);
+    return sw;
+}
+
+// Segment w along DIR for this thread: it loads and stores position cq of line cl.
+template <int DIR, int PO>
+struct Segment {
+    static constexpr bool COOP = DIR != 0;
+    static constexpr int NGP = ghost_layers(PO), NLOAD = seg_loads(PO), NSEC = NLOAD - 64;
+    static_assert(NLOAD > 64 && NSEC * LINES <= 64, "the positions from 64 on fit one wavefront");
+    const GridDev& g;
+    const SweepPlan& sw;
+    const int lane, line;   // of the computing wavefront
+    const int cl, cq;
+    const int n, pl, nf;
+    const long long pstride, istride;
+    SeqBase sb;
+
+    __device__ __forceinline__ Segment(const GridDev& g_, const SweepPlan& sw_, long long w)
+        : g(g_), sw(sw_), lane(threadIdx.x & 63), line(__builtin_amdgcn_readfirstlane(threadIdx.x >> 6)),
+          cl(COOP ? (int)threadIdx.x % LINES : line), cq(COOP ? (int)threadIdx.x / LINES : lane), n(g_.n[DIR]),
+          pl(g_.n[DIR] + 2 * NGP), nf(DIR == 0 ? g_.n[1] : g_.n[0]),
+          pstride(DIR == 0 ? 1 : (DIR == 1 ? (long long)g_.P[0] : (long long)g_.P[0] * g_.P[1])),
+          istride(DIR == 0 ? 1 : (DIR == 1 ? (long long)g_.n[0] : (long long)g_.n[0] * g_.n[1])) {
+        sb = sw.flat[DIR] ? seq_base(w * seg_nodes(PO), pl, NGP, nf, LINES, 0)
+                          : seq_base_aligned(w, sw.nsl[DIR], seg_nodes(PO), 0, NGP, nf, LINES, 0);
+    }
+
+    // line and along-coordinate s (-ng .. n + ng - 1) of sequence l's position q, and
+    // the padded / interior index of the line's node 0; false off the lines
+    __device__ __forceinline__ bool locate(int l, int q, int& s, long long& pbase, long long& ibase) const {
+        SeqBase b = sb;
+        b.fa += l;
+        while (b.fa >= nf) { b.fa -= nf; ++b.fb; }
+        long long lid;
+        int fa, fb;
+        seq_at(b, q, sw.flat[DIR] != 0, pl, NGP, nf, LINES, l, lid, s, fa, fb);
+        const int ci = DIR == 0 ? 0 : fa, cj = DIR == 0 ? fa : (DIR == 1 ? 0 : fb), ck = DIR == 2 ? 0 : fb;
+        pbase = pidx(g, ci, cj, ck);
+        ibase = iidx(g, ci, cj, ck);
+        return lid < sw.nlines[DIR] && s < n + NGP;   // (s: the line's padded end, aligned)
+    }
+
+    // Loads NV values per position by fetch(padded index, v) and puts them away by
+    // stash(position of line cl, v).  The positions from 64 on are loaded by the first
+    // threads as well; both positions' loads are issued before the first of them is
+    // used, from addresses that are always valid (a position off the lines reads node
+    // 0: no owned node's stencil reads it), so that a wavefront waits on memory once.
+    template <int NV, typename Fetch, typename Stash>
+    __device__ __forceinline__ void load(Fetch&& fetch, Stash&& stash) const {
+        auto index = [&](int q, bool use) {
+            long long pb, ib;
+            int s;
+            const bool on = locate(cl, q, s, pb, ib);
+            return use && on ? pb + (long long)s * pstride : 0;
+        };
+        double v0[NV], v1[NV];
+        if (!COOP || line == 0) {
+            const bool sec = cq < NSEC;
+            fetch(index(cq, true), v0);
+            fetch(index(64 + (sec ? cq : 0), sec), v1);
+            // (and none of the second position's loads sunk into its branch, behind
+            // the first wait)
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int c = 0; c < NV; ++c) asm volatile("" : "+v"(v1[c]));
+            stash(cq, v0);
+            if (sec) stash(64 + cq, v1);
+        } else {
+            fetch(index(cq, true), v0);
+            stash(cq, v0);
+        }
+    }
+
+    // Interior index of this thread's position, -1 if the segment does not own it.
+    __device__ __forceinline__ long long owned() const {
+        long long pb, ib;
+        int s;
+        const bool on = locate(cl, cq, s, pb, ib);
+        return on && cq >= NGP && s >= 0 && s < n ? ib + (long long)s * istride : -1;
+    }
+};
+
 // Conservative state read by con2prim: (U, J) directly (stage < 0), or the
 // Shu-Osher combination of Runge-Kutta stage 0 or 1 formed on the fly from U0,
 // the previous stage state Us (stage 1) and the residual L = sum_k Ld_k (slab k

@@ -65,23 +65,6 @@ __device__ __forceinline__ void rmhd_cons(const StateRMHD<R>& s, R* U) {
     for (int k = 0; k < 3; ++k) U[5 + k] = s.B[k];
 }
 
-// x_1 flux F_1(P) (eq. RMHDdiv2), p_tot = p + |b|^2/2.
-template <typename R>
-__device__ __forceinline__ void rmhd_flux1(const StateRMHD<R>& s, const R* U, R* F) {
-    const R ptot = s.p + R(0.5) * s.bsq;
-    const R iW2 = R(1.0) / (s.W * s.W);
-    F[0] = U[0] * s.v[0];
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-        R val = U[1 + c] * s.v[0] - s.B[0] * (s.B[c] * iW2 + s.vB * s.v[c]);
-        if (c == 0) val = val + ptot;
-        F[1 + c] = val;
-    }
-    F[4] = U[1];
-#pragma unroll
-    for (int c = 0; c < 3; ++c) F[5 + c] = s.v[0] * s.B[c] - s.B[0] * s.v[c];
-}
-
 // Entropy variables V = (G/(G-1) + ln rho + ln beta/(G-1) + beta, beta u, -beta W, beta b)
 template <typename R>
 __device__ __forceinline__ void rmhd_entropy_vars(double G, const StateRMHD<R>& s, R* V) {
@@ -251,10 +234,10 @@ __device__ __forceinline__ void pair_flux_rmhd(double G, const NodeRMHDT<NR>& l,
         a0 = R(1.0) + frcp(R(G - 1.0) * beta_ln);
         iden = frcp(W * W - uu);
     } else {
-        iW = 1.0 / W;
-        ib = 1.0 / beta;
-        a0 = 1.0 + 1.0 / ((G - 1.0) * beta_ln);
-        iden = 1.0 / (W * W - uu);
+        R ibl;
+        frcp2(R((G - 1.0) * beta_ln), beta, ibl, ib);
+        frcp2(R(W * W - uu), W, iden, iW);
+        a0 = 1.0 + ibl;
     }
     // U~
     R Ut[8];
@@ -269,10 +252,9 @@ __device__ __forceinline__ void pair_flux_rmhd(double G, const NodeRMHDT<NR>& l,
     R Rk[3], uR = R(0.0);
 #pragma unroll
     for (int k = 0; k < 3; ++k) { Rk[k] = (a1 * u[k] - beta * Wb0 * b[k]) * iW; uR += u[k] * Rk[k]; }
-    const R Dd = beta * (W * W - uu) * iW;
     R U5;
-    if constexpr (F32) U5 = (uR - beta * R1) * frcp(Dd);
-    else U5 = (uR - beta * R1) / Dd;
+    if constexpr (F32) U5 = (uR - beta * R1) * frcp(beta * (W * W - uu) * iW);
+    else U5 = (uR * ib - R1) * (W * iden);
     Ut[0] = U1;
 #pragma unroll
     for (int k = 0; k < 3; ++k) { Ut[1 + k] = u[k] * U5 * iW + Rk[k] * ib; Ut[5 + k] = UB[k]; }
@@ -309,222 +291,6 @@ __device__ __forceinline__ void pair_flux_rmhd(double G, const NodeRMHDT<NR>& l,
     }
     Jt = at;
     Bt = bt;
-}
-
-// ---------------------------------------------------------------------------
-// numeric scaled eigen-structure of the (Godunov-Powell modified) x_1 flux
-// Jacobian at a state in the rotated frame
-// ---------------------------------------------------------------------------
-
-// Jacobians dU/dP, dF_1/dP (+ Phi'(V) e_{B_1}^T, the Godunov-Powell term) and
-// dV/dP at the primitive state P by forward-mode dual numbers.
-__device__ __forceinline__ void rmhd_jacobians(double G, const double* P, double JU[8][8],
-                                               double JF[8][8], double JV[8][8], double* Pp) {
-    using D8 = Dual<8>;
-    D8 Pd[8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) Pd[i] = D8::seed(P[i], i);
-    const StateRMHD<D8> s = rmhd_state<D8>(G, Pd);
-    D8 U[8], F[8], V[8];
-    rmhd_cons<D8>(s, U);
-    rmhd_flux1<D8>(s, U, F);
-    rmhd_entropy_vars<D8>(G, s, V);
-    D8 Ph[8];
-    rmhd_phi_prime<D8>(s, Ph);
-#pragma unroll
-    for (int r = 0; r < 8; ++r) {
-        Pp[r] = Ph[r].v;
-#pragma unroll
-        for (int c = 0; c < 8; ++c) {
-            JU[r][c] = U[r].d[c];
-            JF[r][c] = F[r].d[c] + (c == 5 ? Ph[r].v : 0.0);
-            JV[r][c] = V[r].d[c];
-        }
-    }
-}
-
-// Inverse of a small dense matrix by Gauss-Jordan elimination with partial pivoting.
-template <int N>
-__device__ __forceinline__ void invert(double A[N][N], double X[N][N]) {
-#pragma unroll
-    for (int r = 0; r < N; ++r)
-#pragma unroll
-        for (int c = 0; c < N; ++c) X[r][c] = r == c ? 1.0 : 0.0;
-#pragma unroll
-    for (int k = 0; k < N; ++k) {
-        int piv = k;
-        double best = fabs(A[k][k]);
-#pragma unroll
-        for (int r = k + 1; r < N; ++r)
-            if (fabs(A[r][k]) > best) { best = fabs(A[r][k]); piv = r; }
-#pragma unroll
-        for (int r = k + 1; r < N; ++r) {
-            if (r == piv) {
-#pragma unroll
-                for (int c = 0; c < N; ++c) {
-                    double t = A[k][c]; A[k][c] = A[r][c]; A[r][c] = t;
-                    t = X[k][c]; X[k][c] = X[r][c]; X[r][c] = t;
-                }
-            }
-        }
-        const double ip = 1.0 / A[k][k];
-#pragma unroll
-        for (int c = 0; c < N; ++c) { A[k][c] *= ip; X[k][c] *= ip; }
-#pragma unroll
-        for (int r = 0; r < N; ++r) {
-            if (r == k) continue;
-            const double f = A[r][k];
-#pragma unroll
-            for (int c = 0; c < N; ++c) { A[r][c] -= f * A[k][c]; X[r][c] -= f * X[k][c]; }
-        }
-    }
-}
-
-// Cyclic Jacobi eigen-decomposition of the symmetric 8x8 matrix Q held as its
-// lower triangle (36 entries: only what a symmetric rotation changes is
-// updated).  lam receives the eigenvalues, the columns of Zv the orthonormal
-// eigenvectors.  Rotation (p, q): t = sgn(th)/(|th| + sqrt(th^2 + 1)),
-// th = (a_qq - a_pp)/(2 a_pq), c = 1/sqrt(t^2 + 1), s = t c, tau = s/(1 + c):
-// a_pp -= t a_pq, a_qq += t a_pq, a_pq = 0, and for r != p, q
-// a_rp -= s (a_rq + tau a_rp), a_rq += s (a_rp - tau a_rq) (the same for the
-// rows of Zv).  An element below 1e-18 of its diagonal pair is set to zero
-// instead of rotated; the sweeps stop when the off-diagonal part is below
-// 1e-30 of the diagonal (squared) or after 12 sweeps.
-__device__ __forceinline__ constexpr int tri8(int i, int j) { return i >= j ? i * (i + 1) / 2 + j : j * (j + 1) / 2 + i; }
-
-__device__ __forceinline__ void jacobi_eigen_sym8(const double Q[8][8], double lam[8], double Zv[8][8]) {
-    double a[36];
-#pragma unroll
-    for (int i = 0; i < 8; ++i)
-#pragma unroll
-        for (int j = 0; j <= i; ++j) a[tri8(i, j)] = Q[i][j];
-#pragma unroll
-    for (int r = 0; r < 8; ++r)
-#pragma unroll
-        for (int c = 0; c < 8; ++c) Zv[r][c] = r == c ? 1.0 : 0.0;
-#pragma unroll 1
-    for (int sweep = 0; sweep < 12; ++sweep) {
-        double off = 0.0, dia = 0.0;
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            dia += a[tri8(i, i)] * a[tri8(i, i)];
-#pragma unroll
-            for (int j = 0; j < i; ++j) off += a[tri8(i, j)] * a[tri8(i, j)];
-        }
-        if (!(off > 1e-30 * dia)) break;
-#pragma unroll
-        for (int p = 0; p < 8; ++p) {
-#pragma unroll
-            for (int q = p + 1; q < 8; ++q) {
-                const double apq = a[tri8(q, p)];
-                const double app = a[tri8(p, p)], aqq = a[tri8(q, q)];
-                if (fabs(apq) <= 1e-18 * (fabs(app) + fabs(aqq))) {
-                    a[tri8(q, p)] = 0.0;
-                    continue;
-                }
-                // (|th| <= 5e17 here, so th^2 + 1 stays finite; the reciprocals and
-                // roots are of positive normal numbers)
-                const double th = fdiv(aqq - app, 2.0 * apq);
-                const double t = fdiv(th >= 0.0 ? 1.0 : -1.0, fabs(th) + psqrt(th * th + 1.0));
-                const double c = frsqrt(t * t + 1.0), sn = t * c, tau = fdiv(sn, 1.0 + c);
-                a[tri8(p, p)] = app - t * apq;
-                a[tri8(q, q)] = aqq + t * apq;
-                a[tri8(q, p)] = 0.0;
-#pragma unroll
-                for (int r = 0; r < 8; ++r) {
-                    if (r == p || r == q) continue;
-                    const double arp = a[tri8(r, p)], arq = a[tri8(r, q)];
-                    a[tri8(r, p)] = arp - sn * (arq + tau * arp);
-                    a[tri8(r, q)] = arq + sn * (arp - tau * arq);
-                }
-#pragma unroll
-                for (int r = 0; r < 8; ++r) {
-                    const double zp = Zv[r][p], zq = Zv[r][q];
-                    Zv[r][p] = zp - sn * (zq + tau * zp);
-                    Zv[r][q] = zq + sn * (zp - tau * zq);
-                }
-            }
-        }
-    }
-#pragma unroll
-    for (int i = 0; i < 8; ++i) lam[i] = a[tri8(i, i)];
-}
-
-// Symmetric pencil of the eigenproblem in entropy variables: A0 = dU/dV =
-// JU JV^{-1} and S = dF/dV = JF JV^{-1} (both symmetric; symmetrised against
-// rounding); with A0 = L L^T, Q = L^{-1} S L^{-T}; Q = Z diag(lambda) Z^T gives
-// R = L Z with R R^T = A0 and (dF/dU) R = R diag(lambda) (Section 4).
-__device__ __forceinline__ void rmhd_pencil(const double JU[8][8], const double JF[8][8],
-                                            double JV[8][8], double Lc[8][8], double Q[8][8]) {
-    double X[8][8];
-    invert<8>(JV, X);
-    double A0[8][8], S[8][8];
-#pragma unroll
-    for (int r = 0; r < 8; ++r)
-#pragma unroll
-        for (int c = 0; c < 8; ++c) {
-            double a = 0.0, f = 0.0;
-#pragma unroll
-            for (int k = 0; k < 8; ++k) { a += JU[r][k] * X[k][c]; f += JF[r][k] * X[k][c]; }
-            A0[r][c] = a;
-            S[r][c] = f;
-        }
-#pragma unroll
-    for (int r = 0; r < 8; ++r)
-#pragma unroll
-        for (int c = r + 1; c < 8; ++c) {
-            const double a = 0.5 * (A0[r][c] + A0[c][r]), f = 0.5 * (S[r][c] + S[c][r]);
-            A0[r][c] = A0[c][r] = a;
-            S[r][c] = S[c][r] = f;
-        }
-    // Cholesky A0 = L L^T
-#pragma unroll
-    for (int r = 0; r < 8; ++r)
-#pragma unroll
-        for (int c = 0; c < 8; ++c) Lc[r][c] = 0.0;
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-        double d = A0[j][j];
-#pragma unroll
-        for (int k = 0; k < j; ++k) d -= Lc[j][k] * Lc[j][k];
-        const double ljj = sqrt(d);
-        Lc[j][j] = ljj;
-        const double il = 1.0 / ljj;
-#pragma unroll
-        for (int i = j + 1; i < 8; ++i) {
-            double s = A0[i][j];
-#pragma unroll
-            for (int k = 0; k < j; ++k) s -= Lc[i][k] * Lc[j][k];
-            Lc[i][j] = s * il;
-        }
-    }
-    // Y = L^{-1} S (forward substitution per column), Q = L^{-1} Y^T
-    double Y[8][8];
-#pragma unroll
-    for (int c = 0; c < 8; ++c)
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            double s = S[i][c];
-#pragma unroll
-            for (int k = 0; k < i; ++k) s -= Lc[i][k] * Y[k][c];
-            Y[i][c] = s / Lc[i][i];
-        }
-#pragma unroll
-    for (int c = 0; c < 8; ++c)
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            double s = Y[c][i];
-#pragma unroll
-            for (int k = 0; k < i; ++k) s -= Lc[i][k] * Q[k][c];
-            Q[i][c] = s / Lc[i][i];
-        }
-#pragma unroll
-    for (int r = 0; r < 8; ++r)
-#pragma unroll
-        for (int c = r + 1; c < 8; ++c) {
-            const double q = 0.5 * (Q[r][c] + Q[c][r]);
-            Q[r][c] = Q[c][r] = q;
-        }
 }
 
 // Spectral radius of the Godunov-Powell modified x_1 flux Jacobian at the
@@ -595,153 +361,422 @@ __device__ __forceinline__ void rotate8(const double T[3][3], const double* a, d
     }
 }
 
-// Eigen-groups of the RMHD pencil: eigenvalues closer than GROUP_TOL (chained)
-// form one group, and each group gets the A0^{-1}-Gram-Schmidt sequence of the
-// projections of unit seeds onto its eigenspace, P_g e_s = sum_{a in g} r_a
-// (r_a^T A0^{-1} e_s); the group of v_n (entropy and div B waves) takes e_D,
-// e_{B_n} first, the others e_1, e_2, ...  A seed contributes when what is left of
-// its projection exceeds SEED_TOL times its A0^{-1} norm.  In z-space (r = L z)
-// the A0^{-1} products are Euclidean and r_a^T A0^{-1} e_s = z_a . (L^{-1} e_s).
-// Writes Rc[k] = L z for the canonical vector z of position k (a member of k's
-// group); Zv (the eigenvectors z_a as columns) is overwritten by R = L Z.
-constexpr double GROUP_TOL = 1e-6;
-constexpr double SEED_TOL = 1e-3;
+// ---------------------------------------------------------------------------
+// scaled eigen-structure of the (Godunov-Powell modified) x_1 flux Jacobian at a
+// state in the rotated frame
+// ---------------------------------------------------------------------------
 
-__device__ __forceinline__ void canonical_columns(const double* lam, double Zv[8][8],
-                                                  const double Lc[8][8], double vn, double Rc[8][8]) {
-    // group labels: smallest index reachable through chains of close eigenvalues
-    int lab[8];
+__device__ __forceinline__ constexpr int tri(int i, int j) { return i >= j ? i * (i + 1) / 2 + j : j * (j + 1) / 2 + i; }
+
+// Cyclic Jacobi eigen-decomposition of the symmetric N x N matrix a held as its
+// lower triangle (only what a symmetric rotation changes is updated): on return the
+// diagonal of a holds the eigenvalues and the columns of Zv the orthonormal
+// eigenvectors.  Rotation (p, q): t = sgn(th)/(|th| + sqrt(th^2 + 1)),
+// th = (a_qq - a_pp)/(2 a_pq), c = 1/sqrt(t^2 + 1), s = t c, tau = s/(1 + c):
+// a_pp -= t a_pq, a_qq += t a_pq, a_pq = 0, and for r != p, q
+// a_rp -= s (a_rq + tau a_rp), a_rq += s (a_rp - tau a_rq) (the same for the
+// rows of Zv).  An element below 1e-18 of its diagonal pair, or 1e-100 (the pair may be
+// zero, and reciprocals take normal numbers; a's elements are of order one), is set to zero
+// instead of rotated; the sweeps stop when the off-diagonal part is below
+// 1e-30 of the whole (squared) or after 12 sweeps.
+template <int N>
+__device__ __forceinline__ void jacobi_eigen_sym(double* a, double Zv[N][N]) {
 #pragma unroll
-    for (int k = 0; k < 8; ++k) lab[k] = k;
+    for (int r = 0; r < N; ++r)
+#pragma unroll
+        for (int c = 0; c < N; ++c) Zv[r][c] = r == c ? 1.0 : 0.0;
+    // (the squared Frobenius norm is invariant)
+    double all = 0.0;
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        all += a[tri(i, i)] * a[tri(i, i)];
+#pragma unroll
+        for (int j = 0; j < i; ++j) all += 2.0 * a[tri(i, j)] * a[tri(i, j)];
+    }
 #pragma unroll 1
-    for (int it = 0; it < 7; ++it) {
+    for (int sweep = 0; sweep < 12; ++sweep) {
+        double off = 0.0;
 #pragma unroll
-        for (int k = 0; k < 8; ++k) {
-            int l = lab[k];
+        for (int i = 0; i < N; ++i)
 #pragma unroll
-            for (int j = 0; j < 8; ++j)
-                if (fabs(lam[k] - lam[j]) <= GROUP_TOL && lab[j] < l) l = lab[j];
-            lab[k] = l;
-        }
-    }
-    int labc = lab[0];
-    {
-        double e = fabs(lam[0] - vn);
+            for (int j = 0; j < i; ++j) off += a[tri(i, j)] * a[tri(i, j)];
+        if (!(off > 1e-30 * all)) break;
 #pragma unroll
-        for (int k = 1; k < 8; ++k)
-            if (fabs(lam[k] - vn) < e) { e = fabs(lam[k] - vn); labc = lab[k]; }
-    }
-    // seed coefficients C[a][s] = z_a . (L^{-1} e_s) and |L^{-1} e_s|
-    double C[8][8], yn[8];
+        for (int p = 0; p < N; ++p) {
 #pragma unroll
-    for (int sd = 0; sd < 8; ++sd) {
-        double li[8];
+            for (int q = p + 1; q < N; ++q) {
+                const double apq = a[tri(q, p)];
+                const double app = a[tri(p, p)], aqq = a[tri(q, q)];
+                if (fabs(apq) <= 1e-18 * (fabs(app) + fabs(aqq)) + 1e-100) {
+                    a[tri(q, p)] = 0.0;
+                    continue;
+                }
+                // (|th| <= 5e17 here, so th^2 + 1 stays finite; the reciprocals and
+                // roots are of positive normal numbers)
+                const double th = fdiv(aqq - app, 2.0 * apq);
+                const double t = fdiv(th >= 0.0 ? 1.0 : -1.0, fabs(th) + psqrt(th * th + 1.0));
+                const double c = frsqrt(t * t + 1.0), sn = t * c, tau = fdiv(sn, 1.0 + c);
+                a[tri(p, p)] = app - t * apq;
+                a[tri(q, q)] = aqq + t * apq;
+                a[tri(q, p)] = 0.0;
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            double v = i == sd ? 1.0 : 0.0;
+                for (int r = 0; r < N; ++r) {
+                    if (r == p || r == q) continue;
+                    const double arp = a[tri(r, p)], arq = a[tri(r, q)];
+                    a[tri(r, p)] = arp - sn * (arq + tau * arp);
+                    a[tri(r, q)] = arq + sn * (arp - tau * arq);
+                }
 #pragma unroll
-            for (int k = 0; k < i; ++k) v -= Lc[i][k] * li[k];
-            li[i] = v / Lc[i][i];
-        }
-        double q = 0.0;
-#pragma unroll
-        for (int i = 0; i < 8; ++i) q += li[i] * li[i];
-        yn[sd] = sqrt(q);
-#pragma unroll
-        for (int a = 0; a < 8; ++a) {
-            double c = 0.0;
-#pragma unroll
-            for (int i = 0; i < 8; ++i) c += Zv[i][a] * li[i];
-            C[a][sd] = c;
-        }
-    }
-    // R = L Z in place (row i of R needs rows 0..i of Z)
-#pragma unroll
-    for (int i = 7; i >= 0; --i)
-#pragma unroll
-        for (int a = 0; a < 8; ++a) {
-            double sum = 0.0;
-#pragma unroll
-            for (int k = 0; k <= i; ++k) sum += Lc[i][k] * Zv[k][a];
-            Zv[i][a] = sum;
-        }
-    // Gram-Schmidt in the coordinates of the orthonormal z_a: at slot t every group
-    // projects its seed of slot t (e_D, e_{B_n}, e_1, ... for the group of v_n; e_t
-    // for the others), removes the components along its members accepted so far,
-    // and gives the remainder, normalised, to its next member when it exceeds
-    // SEED_TOL |L^{-1} e_s| (the groups have disjoint supports, so they proceed
-    // side by side).  W[k] holds the coordinates of the basis vector of position k.
-    constexpr int SC[8] = {0, 5, 1, 2, 3, 4, 6, 7};
-    double W[8][8];
-    bool acc[8];
-#pragma unroll
-    for (int k = 0; k < 8; ++k) {
-        acc[k] = false;
-#pragma unroll
-        for (int a = 0; a < 8; ++a) W[k][a] = 0.0;
-    }
-#pragma unroll
-    for (int t = 0; t < 8; ++t) {
-        double r[8];
-#pragma unroll
-        for (int a = 0; a < 8; ++a) r[a] = lab[a] == labc ? C[a][SC[t]] : C[a][t];
-#pragma unroll
-        for (int k = 0; k < 8; ++k) {
-            if (!acc[k]) continue;
-            double ip = 0.0;
-#pragma unroll
-            for (int a = 0; a < 8; ++a) ip += W[k][a] * r[a];
-#pragma unroll
-            for (int a = 0; a < 8; ++a) r[a] -= ip * W[k][a];
-        }
-        bool placed[8];
-#pragma unroll
-        for (int k = 0; k < 8; ++k) placed[k] = acc[k];
-#pragma unroll
-        for (int k = 0; k < 8; ++k) {
-            if (acc[k]) continue;
-            // k may take this slot when all earlier members of its group were placed
-            // at earlier slots (one member per group and slot)
-            bool next = true;
-#pragma unroll
-            for (int j = 0; j < k; ++j)
-                if (lab[j] == lab[k] && !placed[j]) next = false;
-            if (!next) continue;
-            double nn = 0.0;
-#pragma unroll
-            for (int a = 0; a < 8; ++a) nn += lab[a] == lab[k] ? r[a] * r[a] : 0.0;
-            nn = sqrt(nn);
-            const double ys = lab[k] == labc ? yn[SC[t]] : yn[t];
-            if (nn > SEED_TOL * ys) {
-                const double inn = 1.0 / nn;
-#pragma unroll
-                for (int a = 0; a < 8; ++a) W[k][a] = lab[a] == lab[k] ? r[a] * inn : 0.0;
-                acc[k] = true;
+                for (int r = 0; r < N; ++r) {
+                    const double zp = Zv[r][p], zq = Zv[r][q];
+                    Zv[r][p] = zp - sn * (zq + tau * zp);
+                    Zv[r][q] = zq + sn * (zp - tau * zq);
+                }
             }
         }
     }
-    // columns of R for the canonical basis: R_c[k] = R W[k]
+}
+
+// Eigen-groups: eigenvalues closer than GROUP_TOL (chained) form one group, and each
+// group gets the A0^{-1}-Gram-Schmidt sequence of the projections of unit seeds onto
+// its eigenspace, P_g e_s = sum_{a in g} r_a (r_a^T A0^{-1} e_s); the group of v_n
+// (entropy and div B waves) takes e_D, e_{B_n} first, the others e_1, e_2, ...  A seed
+// contributes when what is left of its projection exceeds SEED_TOL times its A0^{-1}
+// norm.
+constexpr double GROUP_TOL = 1e-6;
+constexpr double SEED_TOL = 1e-3;
+
+// Scaled eigenvector matrix R (R R^T = dU/dV) of the Godunov-Powell modified x_1 Jacobian
+// at the state whose entropy variables are Vb (rotated frame).
+//
+// The pencil (dV . dF, dV . dU) in closed form.  With the perturbation of the
+// four-velocity and of the magnetic four-vector in an orthonormal tetrad (u, e_1, e_2,
+// e_3), du = y_a e_a, db = z_a e_a + (b . du) u, and isentropic pressure changes dp (the
+// entropy wave is orthogonal to them and an eigenvector by itself),
+//   dV . dU^mu = beta { u^mu [dp^2/(rho h c^2) + (rho h + b^2) |y|^2 - (b . y)^2 + |z|^2]
+//                       + 2 du^mu (dp + b . z) - 2 b^mu (y . z) },
+// dU^0 the conserved variables, dU^1 the (modified) flux.  With e_1 along n - v_n t (t the
+// time covector: normal to u), dV . dU^1 - v_n dV . dU^0 is (beta/gamma_n) {2 y_1 (dp + b_2
+// z_2 + b_3 z_3) - 2 b_1 (y_2 z_2 + y_3 z_3)}, gamma_n = 1/sqrt(1 - v_n^2): z_1 is the div B
+// wave (lambda = v_n), and the rest couples (dp, z_2, z_3) with (y_1, y_2, y_3) by a 3 x 3
+// matrix K.  e_2 lies along the transverse velocity, so that e_3 has no component along
+// t or n.  After eliminating z_1, dV . dU^0 = [D C; C^T H] with D diagonal; with L_s L_s^T
+// = H - C^T D^{-1} C, Kh = D^{-1/2} K L_s^{-T} and Ch = D^{-1/2} C L_s^{-T} the symmetric
+// matrix of lambda - v_n is
+//   Q = [0 Kh; Kh^T -(Ch^T Kh + Kh^T Ch)],
+// 6 x 6, its eigenvectors by Jacobi rotations.  (The dense route -- 8 x 8 Jacobians by
+// dual numbers, an inverse, Cholesky, an 8 x 8 decomposition and the Gram-Schmidt
+// sequences of all groups -- took 35,400 operations a face and a kilobyte of scratch a lane.)
+struct FaceRMHD {
+    double rho, beta, W, iW, vn, b0, u[3], b[3];      // state
+    double h2, h3, kap, gn, C1, C2, t1, t2, t3, w;    // tetrad, b in it, rho h + |b|^2
+    double ip, iz;                                    // D^{-1/2}
+    double m11, m21, m31, m22, m32, m33;              // L_s^{-1}
+    double Ch[3][3];
+};
+
+__device__ __forceinline__ FaceRMHD rmhd_face_state(double G, double c0, double c1, const double* Vb) {
+    FaceRMHD s;
+    const double ib = frsqrt(Vb[4] * Vb[4] - (Vb[1] * Vb[1] + Vb[2] * Vb[2] + Vb[3] * Vb[3]));
+    s.beta = frcp(ib);
+    s.W = -Vb[4] * ib;
+    s.iW = frcp(s.W);
+    double ub = 0.0;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        s.u[k] = Vb[1 + k] * ib;
+        s.b[k] = Vb[5 + k] * ib;
+        ub += s.u[k] * s.b[k];
+    }
+    s.b0 = ub * s.iW;
+    s.rho = face_exp(Vb[0] - c0 - face_log(s.beta) * c1 - s.beta);
+    const double Gp = G * s.rho * ib;
+    s.vn = s.u[0] * s.iW;
+    // tetrad: e_1 = gn (vn; 1, 0, 0), e_2 = (gn ut; vn gn ut, kap uh), e_3 = (0; 0, wh),
+    // uh = (h2, h3), wh = (-h3, h2)
+    const double ut2 = s.u[1] * s.u[1] + s.u[2] * s.u[2];
+    const bool moves = ut2 > 1e-280;
+    const double iut = moves ? frsqrt(ut2) : 0.0;
+    s.h2 = moves ? s.u[1] * iut : 1.0;
+    s.h3 = moves ? s.u[2] * iut : 0.0;
+    const double q = 1.0 + ut2, ikap = frsqrt(q);
+    s.kap = q * ikap;
+    s.gn = s.W * ikap;
+    s.C1 = s.gn * s.vn;                               // e_1^0, e_2^0
+    s.C2 = s.gn * (ut2 * iut);
+    s.t1 = s.gn * (s.b[0] - s.vn * s.b0);
+    s.t2 = s.C2 * (s.vn * s.b[0] - s.b0) + s.kap * (s.h2 * s.b[1] + s.h3 * s.b[2]);
+    s.t3 = s.h2 * s.b[2] - s.h3 * s.b[1];
+    s.w = s.rho + c0 * s.rho * ib + (s.t1 * s.t1 + s.t2 * s.t2 + s.t3 * s.t3);
+    // D^{-1/2}, H - C^T D^{-1} C and its Cholesky factor's inverse (lower, m)
+    s.iz = frsqrt(s.W);
+    s.ip = psqrt(Gp) * s.iz;
+    const double X = Gp + s.t2 * s.t2 + s.t3 * s.t3;
+    const double f = s.W * ut2 * ikap * ikap;
+    {
+        const double H11 = s.W * (s.w - s.t1 * s.t1) - f * s.t2 * s.t2 - s.C1 * s.C1 * X * s.iW;
+        const double H21 = -s.W * s.t1 * s.t2 + f * s.t1 * s.t2 - s.C1 * (s.C2 * X - s.t2 * s.b0) * s.iW;
+        const double H22 = s.W * (s.w - s.t2 * s.t2) - f * s.t1 * s.t1 -
+                           (s.C2 * (s.C2 * X - 2.0 * s.t2 * s.b0) + s.b0 * s.b0) * s.iW;
+        const double H31 = s.t3 * (s.C1 * s.b0 * s.iW - s.W * s.t1);
+        const double H32 = s.t3 * (s.C2 * s.b0 * s.iW - s.W * s.t2);
+        const double H33 = s.W * (s.w - s.t3 * s.t3) - s.b0 * s.b0 * s.iW;
+        s.m11 = frsqrt(H11);
+        const double l21 = H21 * s.m11, l31 = H31 * s.m11;
+        s.m22 = frsqrt(H22 - l21 * l21);
+        const double l32 = (H32 - l31 * l21) * s.m22;
+        s.m33 = frsqrt(H33 - l31 * l31 - l32 * l32);
+        s.m21 = -l21 * s.m11 * s.m22;
+        s.m32 = -l32 * s.m22 * s.m33;
+        s.m31 = -(l31 * s.m11 + l32 * s.m21) * s.m33;
+    }
+    const double Lj[3][3] = {{s.m11, s.m21, s.m31}, {0.0, s.m22, s.m32}, {0.0, 0.0, s.m33}};   // L_s^{-T}
+#pragma unroll
+    for (int j = 0; j < 3; ++j) {
+        const double tj = s.C1 * Lj[0][j] + s.C2 * Lj[1][j];
+        s.Ch[0][j] = s.ip * tj;
+        s.Ch[1][j] = s.iz * (s.t2 * tj - s.b0 * Lj[1][j]);
+        s.Ch[2][j] = s.iz * (s.t3 * tj - s.b0 * Lj[2][j]);
+    }
+    return s;
+}
+
+// The decomposition: eigenvalues mu of Q (lambda = v_n + mu) and eigenvectors Z.
+__device__ __forceinline__ void rmhd_face_modes(double G, double c0, double c1, const double* Vb, double* mu,
+                                                double Z[6][6]) {
+    double a[21];
+    {
+        const FaceRMHD s = rmhd_face_state(G, c0, c1, Vb);
+        // Kh (rows dp, z_2, z_3) and Q
+        const double Lj[3][3] = {{s.m11, s.m21, s.m31}, {0.0, s.m22, s.m32}, {0.0, 0.0, s.m33}};
+        double Kh[3][3];
+        const double ign = s.kap * s.iW;
+#pragma unroll
+        for (int j = 0; j < 3; ++j) {
+            Kh[0][j] = ign * s.ip * Lj[0][j];
+            Kh[1][j] = ign * s.iz * (s.t2 * Lj[0][j] - s.t1 * Lj[1][j]);
+            Kh[2][j] = ign * s.iz * (s.t3 * Lj[0][j] - s.t1 * Lj[2][j]);
+        }
+#pragma unroll
+        for (int i = 0; i < 3; ++i)
+#pragma unroll
+            for (int j = 0; j <= i; ++j) {
+                double t = 0.0;
+#pragma unroll
+                for (int r = 0; r < 3; ++r) t += s.Ch[r][i] * Kh[r][j] + Kh[r][i] * s.Ch[r][j];
+                a[tri(i, j)] = 0.0;
+                a[tri(3 + i, 3 + j)] = -t;
+            }
+#pragma unroll
+        for (int i = 0; i < 3; ++i)
+#pragma unroll
+            for (int j = 0; j < 3; ++j) a[tri(3 + i, j)] = Kh[j][i];
+    }
+    jacobi_eigen_sym<6>(a, Z);
+#pragma unroll
+    for (int k = 0; k < 6; ++k) mu[k] = a[tri(k, k)];
+}
+
+// lambda^ = max |at + L lambda| of the modes; grouped: some eigenvalues other than the
+// v_n pair are within GROUP_TOL of each other.
+__device__ __forceinline__ double rmhd_face_speed(const double* Vb, const double* mu, double at, double L,
+                                                  bool& grouped) {
+    const double vn = -Vb[1] * frcp(Vb[4]);
+    double lhat = fabs(at + L * vn), near = 1.0;
+#pragma unroll
+    for (int k = 0; k < 6; ++k) {
+        lhat = fmax(lhat, fabs(at + L * (vn + mu[k])));
+        near = fmin(near, fabs(mu[k]));
+#pragma unroll
+        for (int j = 0; j < k; ++j) near = fmin(near, fabs(mu[k] - mu[j]));
+    }
+    grouped = near <= GROUP_TOL;
+    return lhat;
+}
+
+// The conserved perturbation r (and, if wanted, its dual A0^{-1} r) of the A0^{-1}-orthonormal
+// coordinates e[0..5] (the six-vector of Q), e[6] (entropy wave) and e[7] (div B wave).
+template <bool DUAL>
+__device__ __forceinline__ void rmhd_column(double G, double c0, double c1, const FaceRMHD& s, double isb,
+                                            const double* e, double* r, double* dual) {
+    const double e3 = e[3] * isb, e4 = e[4] * isb, e5 = e[5] * isb;
+    const double y1 = s.m11 * e3 + s.m21 * e4 + s.m31 * e5;
+    const double y2 = s.m22 * e4 + s.m32 * e5;
+    const double y3 = s.m33 * e5;
+    const double dp = s.ip * (e[0] * isb - (s.Ch[0][0] * e3 + s.Ch[0][1] * e4 + s.Ch[0][2] * e5));
+    const double z2 = s.iz * (e[1] * isb - (s.Ch[1][0] * e3 + s.Ch[1][1] * e4 + s.Ch[1][2] * e5));
+    const double z3 = s.iz * (e[2] * isb - (s.Ch[2][0] * e3 + s.Ch[2][1] * e4 + s.Ch[2][2] * e5));
+    const double z1 = s.C2 * s.iW * (s.t2 * y1 - s.t1 * y2) + e[7] * (isb * s.iz);
+    const double drho = dp * (s.beta / G) + e[6] * psqrt(s.rho * s.iW / c0);
+    // four-vectors (time, normal, transverse) of du and db
+    const double bz = s.t1 * z1 + s.t2 * z2 + s.t3 * z3, by = s.t1 * y1 + s.t2 * y2 + s.t3 * y3;
+    const double du0 = s.C1 * y1 + s.C2 * y2, db0 = s.C1 * z1 + s.C2 * z2 + by * s.W;
+    const double kh = s.kap * y2, kz = s.kap * z2;
+    const double du[3] = {s.gn * y1 + s.vn * s.C2 * y2, kh * s.h2 - y3 * s.h3, kh * s.h3 + y3 * s.h2};
+    const double db[3] = {s.gn * z1 + s.vn * s.C2 * z2 + by * s.u[0], kz * s.h2 - z3 * s.h3 + by * s.u[1],
+                          kz * s.h3 + z3 * s.h2 + by * s.u[2]};
+    const double dw = drho + c0 * dp + 2.0 * bz;
+    const double A = dw * s.W + s.w * du0;            // T^{0i} = w W u^i - b^0 b^i
+    r[0] = drho * s.W + s.rho * du0;
+    r[4] = A * s.W + s.w * s.W * du0 - (dp + bz) - 2.0 * s.b0 * db0;
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+        r[1 + i] = A * s.u[i] + s.w * s.W * du[i] - db0 * s.b[i] - s.b0 * db[i];
+        r[5 + i] = s.W * db[i] + s.b[i] * du0 - db0 * s.u[i] - s.b0 * du[i];
+    }
+    if (DUAL) {
+        const double dbeta = (drho - s.beta * dp) * (s.beta / s.rho);
+        dual[0] = drho / s.rho + dbeta * (c1 / s.beta + 1.0);
+        dual[4] = -(dbeta * s.W + s.beta * du0);
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+            dual[1 + i] = dbeta * s.u[i] + s.beta * du[i];
+            dual[5 + i] = dbeta * s.b[i] + s.beta * db[i];
+        }
+    }
+}
+
+// The canonical basis of every eigen-group as coordinates Es[k] of column k: within its
+// group, the eigenvectors are turned by plane rotations until the seed of slot t has a
+// component along one more of them only (the Gram-Schmidt sequence of the projected
+// seeds, up to signs).  same[k]: the group of column k as a bit mask, placed: the columns
+// whose seed was found.  Reached by faces whose field lies along or across the normal.
+__device__ __forceinline__ void canonical_basis(double G, double c0, double c1, const double* Vb, const double* mu,
+                                                const double Z[6][6], double (*Es)[8]) {
+    double E[8][8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+#pragma unroll
+        for (int k = 0; k < 8; ++k) E[i][k] = i < 6 && k < 6 ? Z[i < 6 ? i : 0][k < 6 ? k : 0] : (i == k ? 1.0 : 0.0);
+    int same[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+        same[k] = 0;
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+            same[k] |= fabs((k < 6 ? mu[k < 6 ? k : 0] : 0.0) - (j < 6 ? mu[j < 6 ? j : 0] : 0.0)) <= GROUP_TOL ? 1 << j : 0;
+    }
+    // chains of length up to 8: the closure by three squarings
+#pragma unroll 1
+    for (int it = 0; it < 3; ++it) {
+        int up[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            up[k] = same[k];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) up[k] |= (same[k] >> j) & 1 ? same[j] : 0;
+        }
+#pragma unroll
+        for (int k = 0; k < 8; ++k) same[k] = up[k];
+    }
+    const int cluster = same[6];
+    // seed s has the coordinates Gs[s][i] = dual of unit vector i, in memory: one seed
+    // at a time is read back
+    double Gs[8][8];
+    {
+        const FaceRMHD s = rmhd_face_state(G, c0, c1, Vb);
+        const double isb = frsqrt(s.beta);
+#pragma unroll 1
+        for (int i = 0; i < 8; ++i) {
+            double e[8], r[8], d[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) e[j] = i == j ? 1.0 : 0.0;
+            rmhd_column<true>(G, c0, c1, s, isb, e, r, d);
+#pragma unroll
+            for (int j = 0; j < 8; ++j) Gs[j][i] = d[j];
+        }
+    }
+    int placed = 0;
+#pragma unroll 1
+    for (int t = 0; t < 8; ++t) {
+        const int sc = t == 0 ? 0 : (t == 1 ? 5 : (t < 6 ? t - 1 : t));
+        double go[8], gc[8], yo = 0.0, yc = 0.0, c[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            go[i] = Gs[t][i];
+            gc[i] = Gs[sc][i];
+            yo += go[i] * go[i];
+            yc += gc[i] * gc[i];
+        }
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            const bool in = (cluster >> k) & 1;
+            double x = 0.0;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) x += (in ? gc[i] : go[i]) * E[i][k];
+            c[k] = x;
+        }
+        const int before = placed;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            // the first column of its group without a seed takes this one
+            const int open = same[i] & ~before;
+            if (!((open >> i) & 1) || (open & ((1 << i) - 1))) continue;
+#pragma unroll
+            for (int j = i + 1; j < 8; ++j) {
+                // (components at rounding level stay: their squares may underflow)
+                if (!((open >> j) & 1) || fabs(c[j]) <= 1e-18 * sqrt(yo + yc)) continue;
+                const double n = sqrt(c[i] * c[i] + c[j] * c[j]), in = 1.0 / n, cs = c[i] * in, sn = c[j] * in;
+#pragma unroll
+                for (int q = 0; q < 8; ++q) {
+                    const double a = E[q][i], b = E[q][j];
+                    E[q][i] = cs * a + sn * b;
+                    E[q][j] = cs * b - sn * a;
+                }
+                c[i] = n;
+            }
+            const double y = (cluster >> i) & 1 ? yc : yo;
+            if (fabs(c[i]) > SEED_TOL * sqrt(y)) placed |= 1 << i;
+        }
+    }
+    // (a column that no seed reached carries no dissipation)
 #pragma unroll
     for (int k = 0; k < 8; ++k)
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            double sum = 0.0;
-#pragma unroll
-            for (int a = 0; a < 8; ++a) sum += Zv[i][a] * W[k][a];
-            Rc[k][i] = sum;
-        }
+        for (int i = 0; i < 8; ++i) Es[k][i] = (placed >> k) & 1 ? E[i][k] : 0.0;
 }
 
-// Face frame and eigen-structure of the RMHD dissipation at face i+1/2 (shared by
-// face_diss_rmhd and its adjoint): the rotation T of the face metric normal, the
-// rotated entropy variables TV2, TV3 of nodes i and i+1, lambda^ and the columns
-// Rc[k] = L z_k of R (z_k the canonical basis vector of position k).
-// Frame of face i+1/2: the rotation T of the mean metric normal (a_t, L n) of
-// nodes i and i+1 and their rotated entropy variables TV2, TV3.
+// Column k of R handed to col(k, r) (rotated frame), k = 0..5 the modes, 6 the entropy
+// wave, 7 the div B wave; with eigen-groups their canonical columns.  (The state is
+// formed again after the decomposition, from Vb, instead of being held through it: about
+// 230 operations for 70 registers, which keeps two wavefronts per SIMD.)
+template <typename Col>
+__device__ __forceinline__ void rmhd_face_columns(double G, double c0, double c1, double* Vb, const double* mu,
+                                                  const double Z[6][6], bool grouped, Col&& col) {
+#pragma unroll
+    for (int c = 0; c < 8; ++c) form_here(Vb[c]);
+    if (grouped) {
+        double Es[8][8];
+        canonical_basis(G, c0, c1, Vb, mu, Z, Es);
+        const FaceRMHD s = rmhd_face_state(G, c0, c1, Vb);
+        const double isb = frsqrt(s.beta);
+#pragma unroll 1
+        for (int k = 0; k < 8; ++k) {
+            double e[8], r[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) e[i] = Es[k][i];
+            rmhd_column<false>(G, c0, c1, s, isb, e, r, nullptr);
+            col(k, r);
+        }
+        return;
+    }
+    const FaceRMHD s = rmhd_face_state(G, c0, c1, Vb);
+    const double isb = frsqrt(s.beta);
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+        double e[8], r[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) e[i] = k < 6 ? (i < 6 ? Z[i < 6 ? i : 0][k < 6 ? k : 0] : 0.0) : (i == k ? 1.0 : 0.0);
+        rmhd_column<false>(G, c0, c1, s, isb, e, r, nullptr);
+        col(k, r);
+    }
+}
+
+// Frame of face i+1/2: the rotation T of the mean metric normal (a_t, L n) of nodes i
+// and i+1.
 template <int DIM>
-__device__ __forceinline__ void face_frame_rmhd(double G, const double* P2, const double* P3, const double* al,
-                                                const double* ar, double T[3][3], double* TV2, double* TV3,
-                                                double& at, double& L) {
+__device__ __forceinline__ void face_metric_rmhd(const double* al, const double* ar, double T[3][3], double& at,
+                                                 double& L) {
     at = 0.5 * (al[0] + ar[0]);
     double ax[3] = {0.0, 0.0, 0.0};
 #pragma unroll
@@ -750,6 +785,15 @@ __device__ __forceinline__ void face_frame_rmhd(double G, const double* P2, cons
     const double iL = 1.0 / L;
     double nrm[3] = {ax[0] * iL, ax[1] * iL, ax[2] * iL};
     rotation<3>(nrm, T);            // n_3 = 0 in 2D gives the 2D rotation
+}
+
+// The frame with the rotated entropy variables TV2, TV3 of nodes i and i+1 from their
+// primitive states.
+template <int DIM>
+__device__ __forceinline__ void face_frame_rmhd(double G, const double* P2, const double* P3, const double* al,
+                                                const double* ar, double T[3][3], double* TV2, double* TV3,
+                                                double& at, double& L) {
+    face_metric_rmhd<DIM>(al, ar, T, at, L);
 #pragma unroll
     for (int q = 0; q < 2; ++q) {
         const StateRMHD<double> s = rmhd_state<double>(G, q == 0 ? P2 : P3);
@@ -759,119 +803,166 @@ __device__ __forceinline__ void face_frame_rmhd(double G, const double* P2, cons
     }
 }
 
-template <int DIM>
+// Eigen-structure of face i+1/2 from the primitive states of nodes i and i+1: lambda^ and
+// the columns, handed to col(k, r) (rotated frame).
+template <int DIM, typename Col>
 __device__ __forceinline__ void face_eigen_rmhd(double G, const double* P2, const double* P3, const double* al,
-                                                const double* ar, double T[3][3], double* TV2, double* TV3,
-                                                double& lhat, double Rc[8][8]) {
-    double at, L;
-    face_frame_rmhd<DIM>(G, P2, P3, al, ar, T, TV2, TV3, at, L);
-    // face state (rotated frame)
-    double Vb[8];
+                                                const double* ar, double& lhat, Col&& col) {
+    const double c0 = G / (G - 1.0), c1 = 1.0 / (G - 1.0);
+    double Vb[8], mu[6], Z[6][6], at, L;
+    {
+        double T[3][3], TV2[8], TV3[8];
+        face_frame_rmhd<DIM>(G, P2, P3, al, ar, T, TV2, TV3, at, L);
 #pragma unroll
-    for (int c = 0; c < 8; ++c) Vb[c] = 0.5 * (TV2[c] + TV3[c]);
-    const double vu2 = Vb[1] * Vb[1] + Vb[2] * Vb[2] + Vb[3] * Vb[3];
-    const double beta = sqrt(Vb[4] * Vb[4] - vu2);
-    const double ib = 1.0 / beta;
-    double Pf[8];
-    const double W = -Vb[4] * ib;
-    const double rho = exp(Vb[0] - G / (G - 1.0) - log(beta) / (G - 1.0) - beta);
-    Pf[0] = rho;
-    Pf[4] = rho * ib;
-    double u[3], b[3], ub = 0.0;
-#pragma unroll
-    for (int k = 0; k < 3; ++k) { u[k] = Vb[1 + k] * ib; b[k] = Vb[5 + k] * ib; ub += u[k] * b[k]; }
-    const double b0 = ub / W;
-#pragma unroll
-    for (int k = 0; k < 3; ++k) { Pf[1 + k] = u[k]; Pf[5 + k] = W * b[k] - b0 * u[k]; }
-    const double vn = u[0] / W;
-
-    double JU[8][8], JF[8][8], JV[8][8], Pp[8], Lc[8][8], Q[8][8], Zv[8][8];
-    rmhd_jacobians(G, Pf, JU, JF, JV, Pp);
-    rmhd_pencil(JU, JF, JV, Lc, Q);
-    double lam[8];
-    jacobi_eigen_sym8(Q, lam, Zv);
-    lhat = 0.0;
-#pragma unroll
-    for (int k = 0; k < 8; ++k) lhat = fmax(lhat, fabs(at + L * lam[k]));
-    // canonical basis in every group of (nearly) equal eigenvalues
-    canonical_columns(lam, Zv, Lc, vn, Rc);
+        for (int c = 0; c < 8; ++c) Vb[c] = 0.5 * (TV2[c] + TV3[c]);
+    }
+    rmhd_face_modes(G, c0, c1, Vb, mu, Z);
+    bool grouped;
+    lhat = rmhd_face_speed(Vb, mu, at, L, grouped);
+    rmhd_face_columns(G, c0, c1, Vb, mu, Z, grouped, col);
 }
 
-// ES dissipation for RMHD at one face (eq. ESFlux_HO): as face_diss_rhd with
+// A stencil node of the RMHD dissipation: V_1 and what the rest of the entropy
+// variables V = (V_1, beta u, -beta W, beta b) is formed from.
+struct NodeVM {
+    double V0, beta, W, u[3], b[3];
+};
+
+__device__ __forceinline__ void entropy_of(const NodeVM& n, double* V) {
+    V[0] = n.V0;
+    V[4] = -n.beta * n.W;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        V[1 + k] = n.beta * n.u[k];
+        V[5 + k] = n.beta * n.b[k];
+    }
+}
+
+// ES dissipation for RMHD at one face (eq. ESFlux_HO): as face_diss_rhd_fn with
 // T = diag{1, T_0, 1, T_0}, the face state from the mean rotated entropy
 // variables (explicit inverse of V: beta^2 = V_5^2 - |V_2..4|^2, u = V_2..4/beta,
 // W = -V_5/beta, ln rho = V_1 - G/(G-1) - ln(beta)/(G-1) - beta, p = rho/beta,
-// b = V_6..8/beta, b^0 = u.b/W, B = W b - b^0 u), and R from the symmetric pencil
-// (A0, S) of the Godunov-Powell modified Jacobian, with the canonical basis in
-// every group of nearly equal eigenvalues (canonical_columns; the group of v_n
-// holds the entropy and div B waves and is seeded with e_D, e_{B_n}).
-// nodes: the 8 primitive slots of the stencil nodes i-2..i+3.
-// P: the order parameter p (stencil of 2p nodes i-p+1 .. i+p, WENO of order 2p-1).
-template <int DIM, bool MIXED = false, int P = 3>
-__device__ __forceinline__ void face_diss_rmhd(double G, double eps, const double Pn[2 * P][8],
-                                               const double* al, const double* ar, double* d) {
-    constexpr int NS = 2 * P, CI = P - 1;    // stencil size, index of node i
-    double T[3][3], TV[NS][8], lhat, Rc[8][8];
-    face_eigen_rmhd<DIM>(G, Pn[CI], Pn[CI + 1], al, ar, T, TV[CI], TV[CI + 1], lhat, Rc);
-#pragma unroll
-    for (int j = 0; j < NS; ++j) {
-        if (j == CI || j == CI + 1) continue;
-        const StateRMHD<double> s = rmhd_state<double>(G, Pn[j]);
-        double V[8];
-        rmhd_entropy_vars<double>(G, s, V);
-        rotate8<false>(T, V, TV[j]);
-    }
-    double tv2 = 0.0, tv3 = 0.0;
-#pragma unroll
-    for (int c = 0; c < 8; ++c) { tv2 = fmax(tv2, fabs(TV[CI][c])); tv3 = fmax(tv3, fabs(TV[CI + 1][c])); }
-    const double tvmax = tv2 + tv3;
-    // projections, WENO5, the switch and the accumulation: FP64, or FP32 in the
-    // mixed form (the eigen-structure above stays FP64 there)
+// b = V_6..8/beta, b^0 = u.b/W), and R from rmhd_face_columns, with the canonical
+// basis in every group of nearly equal eigenvalues (canonical_basis; the group of
+// v_n holds the entropy and div B waves and is seeded with e_D, e_{B_n}).
+// node(j): the stencil nodes i-p+1..i+p, metric(al, ar): the metrics of nodes i and i+1,
+// both read again where they are used, so that neither is held through the
+// decomposition, nor the columns or the stencil whole (WENO of order 2p-1).  MIXED:
+// projections, WENO, the switch and the accumulation in FP32 (the eigen-structure stays
+// FP64).
+template <int DIM, bool MIXED, int P, typename NodeFn, typename MetricFn>
+__device__ __forceinline__ void face_diss_rmhd_fn(double G, double c0, double c1, double eps, NodeFn&& node,
+                                                  MetricFn&& metric, double* d) {
+    constexpr int NS = 2 * P, CI = P - 1, NA = DIM + 1;    // stencil size, index of node i
     using RW = typename std::conditional<MIXED, float, double>::type;
-    RW TVw[NS][8];
+    double Vb[8], at, L, T[3][3];
+    RW tvmax;
+    {
+        double al[NA], ar[NA];
+        metric(al, ar);
+        face_metric_rmhd<DIM>(al, ar, T, at, L);
+        double V2[8], V3[8], TV2[8], TV3[8], tv2 = 0.0, tv3 = 0.0;
+        entropy_of(node(CI), V2);
+        entropy_of(node(CI + 1), V3);
+        rotate8<false>(T, V2, TV2);
+        rotate8<false>(T, V3, TV3);
 #pragma unroll
-    for (int j = 0; j < NS; ++j)
+        for (int c = 0; c < 8; ++c) {
+            Vb[c] = 0.5 * (TV2[c] + TV3[c]);
+            tv2 = fmax(tv2, fabs(TV2[c]));
+            tv3 = fmax(tv3, fabs(TV3[c]));
+        }
+        tvmax = (RW)(tv2 + tv3);
+    }
+    double mu[6], Z[6][6];
+    rmhd_face_modes(G, c0, c1, Vb, mu, Z);
+    bool grouped;
+    const double lhat = rmhd_face_speed(Vb, mu, at, L, grouped);
+#ifndef ES_OPCOUNT_HOST
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+#endif
+    {
+        double al[NA], ar[NA], atr, Lr;
+        metric(al, ar);
 #pragma unroll
-        for (int c = 0; c < 8; ++c) TVw[j][c] = (RW)TV[j][c];
+        for (int c = 0; c < NA; ++c) {
+            form_here(al[c]);
+            form_here(ar[c]);
+        }
+        face_metric_rmhd<DIM>(al, ar, T, atr, Lr);
+    }
     RW dd[8];
 #pragma unroll
     for (int c = 0; c < 8; ++c) dd[c] = RW(0.0);
+    rmhd_face_columns(G, c0, c1, Vb, mu, Z, grouped, [&](int, const double* rr) {
+        RW r1 = RW(0.0);
 #pragma unroll
-    for (int k = 0; k < 8; ++k) {
+        for (int c = 0; c < 8; ++c) r1 += fabs((RW)rr[c]);
+        // the column in the fixed frame
+        double rf[8];
+        rotate8<true>(T, rr, rf);
         RW r[8];
 #pragma unroll
-        for (int i = 0; i < 8; ++i) r[i] = (RW)Rc[k][i];
+        for (int c = 0; c < 8; ++c) {
+            r[c] = (RW)rf[c];
+            form_here(r[c]);
+        }
+#ifndef ES_OPCOUNT_HOST
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+#endif
         RW vt[NS];
 #pragma unroll
         for (int j = 0; j < NS; ++j) {
+            double V[8];
+            entropy_of(node(j), V);
             RW s = RW(0.0);
 #pragma unroll
-            for (int c = 0; c < 8; ++c) s += r[c] * TVw[j][c];
+            for (int c = 0; c < 8; ++c) s += r[c] * (RW)V[c];
             vt[j] = s;
+            form_here(vt[j]);
         }
         RW jw;
-        if (P == 4)
+        if constexpr (!MIXED) {
+            jw = weno_jump<P, RW>(vt, (RW)eps);
+        } else if (P == 4) {
             jw = weno7(vt[7], vt[6], vt[5], vt[4], vt[3], vt[2], vt[1], (RW)eps) -
                  weno7(vt[0], vt[1], vt[2], vt[3], vt[4], vt[5], vt[6], (RW)eps);
-        else if (P == 3)
+        } else if (P == 3) {
             jw = weno5(vt[5], vt[4], vt[3], vt[2], vt[1], (RW)eps) - weno5(vt[0], vt[1], vt[2], vt[3], vt[4], (RW)eps);
-        else
+        } else {
             jw = weno3(vt[3], vt[2], vt[1], (RW)eps) - weno3(vt[0], vt[1], vt[2], (RW)eps);
-        const RW jp = vt[CI + 1] - vt[CI];
-        RW r1 = RW(0.0);
-#pragma unroll
-        for (int c = 0; c < 8; ++c) r1 += fabs(r[c]);
-        if (jw * jp > RW(0.0) && fabs(jp) > RealTraits<RW>::ytol * r1 * (RW)tvmax) {
-#pragma unroll
-            for (int c = 0; c < 8; ++c) dd[c] += jw * r[c];
         }
-    }
-    double ddd[8], o[8];
+        const RW jp = vt[CI + 1] - vt[CI];
+        const RW on = (jw * jp > RW(0.0) && fabs(jp) > RW(RealTraits<RW>::ytol) * r1 * tvmax) ? jw : RW(0.0);
 #pragma unroll
-    for (int c = 0; c < 8; ++c) ddd[c] = (double)dd[c];
-    rotate8<true>(T, ddd, o);
+        for (int c = 0; c < 8; ++c) {
+            dd[c] += on * r[c];
+            form_here(dd[c]);
+        }
+    });
 #pragma unroll
-    for (int c = 0; c < 8; ++c) d[c] = lhat * o[c];
+    for (int c = 0; c < 8; ++c) d[c] = lhat * (double)dd[c];
+}
+
+// The same from the 8 primitive slots of the stencil nodes.
+template <int DIM, bool MIXED = false, int P = 3>
+__device__ __forceinline__ void face_diss_rmhd(double G, double eps, const double Pn[2 * P][8],
+                                               const double* al, const double* ar, double* d) {
+    face_diss_rmhd_fn<DIM, MIXED, P>(
+        G, G / (G - 1.0), 1.0 / (G - 1.0), eps,
+        [&](int j) {
+            const StateRMHD<double> s = rmhd_state<double>(G, Pn[j]);
+            NodeVM n;
+            n.V0 = (G / (G - 1.0)) + xlog(s.rho) + xlog(s.beta) * (1.0 / (G - 1.0)) + s.beta;
+            n.beta = s.beta;
+            n.W = s.W;
+            for (int k = 0; k < 3; ++k) { n.u[k] = s.u[k]; n.b[k] = s.b[k]; }
+            return n;
+        },
+        [&](double* l, double* r) {
+            for (int c = 0; c <= DIM; ++c) { l[c] = al[c]; r[c] = ar[c]; }
+        },
+        d);
 }
 
 }  // namespace es
