@@ -6,8 +6,8 @@
 // Per direction the cotangent lambda of the residual is pulled back to the
 // primitive states:
 //   * two-point fluxes: F(a, a+n) receives w = alpha_n / dxi (lambda_{a+n} -
-//     lambda_a), times dF/dP of either node (forward-mode dual numbers over the 8
-//     primitive variables of one node at a time);
+//     lambda_a), times dF/dP of either node (pair_vjp_rmhd, one backward
+//     sweep for both);
 //   * Godunov-Powell source -Phi'(V_s) dB~_s/dxi (eq. RMHDSemiU_O2p_ES): the pair
 //     value B~(a, a+n) = 1/4 sum_j (a_j,a + a_j,a+n)(B_j,a + B_j,a+n) receives
 //     alpha_n / dxi (lambda_{a+n}.Phi'_{a+n} - lambda_a.Phi'_a) (linear in the
@@ -15,8 +15,8 @@
 //   * face dissipation d = lambda^ T^T sum_k r_k Y_k <<V~_k>> (eq. ESFlux_HO)
 //     with the face eigen-structure (T, the columns r_k, lambda^) and the switch
 //     Y held at their forward values: the reverse of the accumulation, of the
-//     two WENO5 reconstructions (the gradient written out, as for RHD), of the
-//     projections V~ = r_k . T V_j, and of the rotation, then (dV/dP)^T per node.
+//     jump of the WENO values (weno_jump_grad) and of the projections V~ = (T^T r_k) .
+//     V_j; all of a node's cotangents go through (dP)^T once (node_vjp_rmhd).
 // The face eigen-structure is an eigen-decomposition of a symmetric 6 x 6 matrix; its
 // derivative along the face entropy variables is not carried (it
 // multiplies the WENO jumps, which vanish at the order of the scheme on smooth
@@ -27,6 +27,7 @@
 #include "es_launch.h"
 #include "es_rmhd.h"
 #include "es_dual.h"
+#include "es_pair_vjp_rmhd.h"
 
 namespace es {
 
@@ -35,14 +36,15 @@ namespace {
 constexpr int QSEG = 54;                  // output positions per segment
 constexpr int QHALO = 5;                  // state halo each side
 constexpr int QLOAD = QSEG + 2 * QHALO;   // 64 loaded slots
-constexpr int QLINES = 2;                 // segments per block
+constexpr int QLINES = 4;                 // segments per block
 
-template <int DIM>
+// A line's staged nodes: the quantities of the pair sweep, the metrics, the residual
+// cotangent and (with dissipation) the entropy variables.  The output passes through the
+// first 8 rows.
+template <int DIM, bool ES>
 struct AdjLDSM {
-    static constexpr int NA = DIM + 1, NF = 8 + 2 + NA + 8;   // prims, logs, metrics, Phi'
-    double sd[QLINES][NF][QLOAD];
-    double lam[QLINES][8][QLOAD];
-    double buf[QLINES][6][8][64];
+    enum { RHO, BETA, LR, LB, W, B0, U, b = U + 3, B = b + 3, A = B + 3, LAM = A + DIM + 1, V = LAM + 8, NF = V + (ES ? 8 : 0) };
+    double f[QLINES][NF][QLOAD];
 };
 
 struct AdjPlanM {
@@ -53,9 +55,10 @@ struct AdjPlanM {
 
 // Face eigen-structure of the ES dissipation held by the adjoint: for direction d,
 // interior transverse line l and face f = p + 1 (face p+1/2 between positions p
-// and p + 1 along the line, p = -1 .. n_d - 1), the 64 entries Rc[k][i] (k*8 + i)
-// and lambda^ (entry 64) at eig[base[d] + (e * nlines[d] + l) * nface[d] + f].
-constexpr int NEIG = 65;
+// and p + 1 along the line, p = -1 .. n_d - 1), column k in the fixed frame (entries 9k ..
+// 9k + 7) with the size below which its jump counts as zero (9k + 8), and lambda^ (entry
+// 72) at eig[base[d] + (e * nlines[d] + l) * nface[d] + f].
+constexpr int NEIG = 73;
 struct FaceEigPlan {
     long long base[3];
     long long nlines[3];
@@ -63,6 +66,9 @@ struct FaceEigPlan {
     long long nthreads[3];   // faces of each direction
 };
 
+// One face per lane.  Bound by FP64 issue (13,700 operations a face, 61 us for the 131,600
+// faces of 256^2; their 73 doubles take 15 us to write).  One wavefront per SIMD without
+// spills: held to 256 registers, for two, the 256^2 adjoint takes 811 us instead of 788.
 template <int DIM>
 __global__ void __launch_bounds__(64) k_face_eigen_rmhd(GridDev g, double G, const double* __restrict__ prim,
                                                         const double* __restrict__ met, double* __restrict__ eig,
@@ -91,418 +97,284 @@ __global__ void __launch_bounds__(64) k_face_eigen_rmhd(GridDev g, double G, con
     double lhat;
     double* o = eig + fp.base[d] + l * fp.nface[d] + f;
     const long long es = fp.nlines[d] * fp.nface[d];
-    auto put = [&](int k, const double* r) {
+    auto put = [&](int k, const double* r, double thr) {
 #pragma unroll
-        for (int i = 0; i < 8; ++i) o[(k * 8 + i) * es] = r[i];
+        for (int i = 0; i < 8; ++i) o[(k * 9 + i) * es] = r[i];
+        o[(k * 9 + 8) * es] = thr;
     };
     face_eigen_rmhd<DIM>(G, P2, P3, al, ar, lhat, put);
-    o[64 * es] = lhat;
+    o[72 * es] = lhat;
 }
 
-// Gradient of the WENO5-JS value weno5(a, b, c, d, e) with respect to its five
-// inputs: with w_k = d_k / (eps + beta_k)^2, S = sum_k w_k, v = sum_k w_k q_k / (6 S),
-// dv = [sum_k w_k dq_k + sum_k (q_k - 6 v) dw_k] / (6 S), dw_k = -2 w_k dbeta_k / (eps + beta_k).
-__device__ __forceinline__ void weno5_grad_m(double a, double b, double c, double d, double e, double eps,
-                                             double* gr) {
-    const double q0 = 2.0 * a - 7.0 * b + 11.0 * c;
-    const double q1 = -b + 5.0 * c + 2.0 * d;
-    const double q2 = 2.0 * c + 5.0 * d - e;
-    const double t0 = a - 2.0 * b + c, s0 = a - 4.0 * b + 3.0 * c;
-    const double t1 = b - 2.0 * c + d, s1 = b - d;
-    const double t2 = c - 2.0 * d + e, s2 = 3.0 * c - 4.0 * d + e;
-    const double e0 = eps + (13.0 / 12.0) * t0 * t0 + 0.25 * s0 * s0;
-    const double e1 = eps + (13.0 / 12.0) * t1 * t1 + 0.25 * s1 * s1;
-    const double e2 = eps + (13.0 / 12.0) * t2 * t2 + 0.25 * s2 * s2;
-    const double ie0 = 1.0 / e0, ie1 = 1.0 / e1, ie2 = 1.0 / e2;
-    const double w0 = 0.1 * ie0 * ie0, w1 = 0.6 * ie1 * ie1, w2 = 0.3 * ie2 * ie2;
-    const double S = w0 + w1 + w2;
-    const double iS6 = 1.0 / (6.0 * S);
-    const double v6 = (w0 * q0 + w1 * q1 + w2 * q2) / S;
-    const double c0 = -2.0 * w0 * (q0 - v6) * ie0, c1 = -2.0 * w1 * (q1 - v6) * ie1, c2 = -2.0 * w2 * (q2 - v6) * ie2;
-    const double u0 = c0 * (13.0 / 6.0) * t0, v0 = c0 * 0.5 * s0;
-    const double u1 = c1 * (13.0 / 6.0) * t1, v1 = c1 * 0.5 * s1;
-    const double u2 = c2 * (13.0 / 6.0) * t2, v2 = c2 * 0.5 * s2;
-    gr[0] = (2.0 * w0 + u0 + v0) * iS6;
-    gr[1] = (-7.0 * w0 - w1 - 2.0 * u0 - 4.0 * v0 + u1 + v1) * iS6;
-    gr[2] = (11.0 * w0 + 5.0 * w1 + 2.0 * w2 + u0 + 3.0 * v0 - 2.0 * u1 + u2 + 3.0 * v2) * iS6;
-    gr[3] = (2.0 * w1 + 5.0 * w2 + u1 - v1 - 2.0 * u2 - 4.0 * v2) * iS6;
-    gr[4] = (-w2 + u2 + v2) * iS6;
-}
-
-// Gradient of the WENO3-JS value weno3(a, b, c) = (w0 q0 + w1 q1) / (2 S), q0 = 3b - a,
-// q1 = b + c, w_k = d_k / e_k^2 (d = 1/3, 2/3), e0 = eps + (b - a)^2, e1 = eps + (c - b)^2:
-// dv = [sum_k w_k dq_k + sum_k (q_k - 2 v) dw_k] / (2 S), dw_k = -2 w_k de_k / e_k.
-__device__ __forceinline__ void weno3_grad_m(double a, double b, double c, double eps, double* gr) {
-    const double q0 = 3.0 * b - a, q1 = b + c;
-    const double e0 = eps + (b - a) * (b - a), e1 = eps + (c - b) * (c - b);
-    const double w0 = (1.0 / 3.0) * (e1 * e1), w1 = (2.0 / 3.0) * (e0 * e0);   // both times e0^2 e1^2
-    const double S = w0 + w1;
-    const double v2 = (w0 * q0 + w1 * q1) / S;
-    const double c0 = -4.0 * w0 * (q0 - v2) * (b - a) / e0;
-    const double c1 = -4.0 * w1 * (q1 - v2) * (c - b) / e1;
-    const double i2S = 1.0 / (2.0 * S);
-    gr[0] = (-w0 - c0) * i2S;
-    gr[1] = (3.0 * w0 + w1 + c0 - c1) * i2S;
-    gr[2] = (w1 + c1) * i2S;
-}
-
-// (dF/dP_l)^T w and (dF/dP_r)^T w for the RMHD two-point flux F(l, r).
-template <int DIM, int SIDE>
-__device__ __forceinline__ void pair_vjp_rmhd_side(double G, const double* Pl, const double* Pr, const double* al,
-                                                   const double* ar, const double* w, double* g) {
-    using D = Dual<8>;
-    D Pdl[8], Pdr[8];
-#pragma unroll
-    for (int c = 0; c < 8; ++c) {
-        Pdl[c] = SIDE == 0 ? D::seed(Pl[c], c) : D(Pl[c]);
-        Pdr[c] = SIDE == 1 ? D::seed(Pr[c], c) : D(Pr[c]);
-    }
-    const NodeRMHDT<D> l = node_rmhd<D>(G, Pdl, xlog(Pdl[0]), xlog(Pdl[0] / Pdl[4]));
-    const NodeRMHDT<D> r = node_rmhd<D>(G, Pdr, xlog(Pdr[0]), xlog(Pdr[0] / Pdr[4]));
-    D F[8];
-    double Jt, Bt;
-    pair_flux_rmhd<DIM, D, D>(G, l, r, al, ar, F, Jt, Bt);
-#pragma unroll
-    for (int k = 0; k < 8; ++k) {
-        double s = 0.0;
-#pragma unroll
-        for (int c = 0; c < 8; ++c) s += w[c] * F[c].d[k];
-        g[k] = s;
-    }
-}
-
-// (the side is a template parameter so that the unseeded node's zero tangents
-// fold away)
-template <int DIM>
-__device__ void pair_vjp_rmhd(double G, const double* Pl, const double* Pr, const double* al, const double* ar,
-                              const double* w, double* gl, double* gr) {
-    pair_vjp_rmhd_side<DIM, 0>(G, Pl, Pr, al, ar, w, gl);
-    pair_vjp_rmhd_side<DIM, 1>(G, Pl, Pr, al, ar, w, gr);
-}
-
-// PO: the order parameter p (pairs n = 1..p, face stencils of 2p nodes).
+// Reverse of the residual along DIR for one segment: lane q of a wavefront takes position
+// s0 - QHALO + q of its line as a node, as the left node of its pairs and as face q + 1/2.
+// Bound by FP64 issue at two wavefronts per SIMD: 47 us at 256^2 with its dissipation, where
+// dual numbers through the pair flux and stencil arrays in scratch took 709 (whole
+// adjoint 2820 -> 788 us).  The pair and node sweeps are written out (es_pair_vjp_rmhd.h), what belongs
+// to a right node or to another lane's stencil moves by lane shuffles, a face's columns are
+// read one at a time in the fixed frame; the lines of a block along y and z are neighbours
+// in x and are loaded and stored together (32 bytes a row).  PO: the order parameter p
+// (pairs n = 1..p, face stencils of 2p nodes).
 template <int DIM, int DIR, bool ES, int PO>
 __device__ __forceinline__ void residual_vjp_segment_rmhd(const GridDev& g, double G, double eps,
                                                           const double* __restrict__ prim,
                                                           const double* __restrict__ met,
                                                           const double* __restrict__ lam,
                                                           double* __restrict__ gout, int blk, int nseg,
-                                                          long long nlines, AdjLDSM<DIM>& lds,
+                                                          long long nlines, AdjLDSM<DIM, ES>& lds,
                                                           const double* __restrict__ eig, long long enf) {
-    constexpr int NA = DIM + 1;
-    constexpr int F_LR = 8, F_LB = 9, F_A = 10, F_PP = 10 + NA;
-    auto& sd = lds.sd;
-    auto& sl = lds.lam;
-    auto& buf = lds.buf;
+    using L = AdjLDSM<DIM, ES>;
+    constexpr int NA = DIM + 1, NQ = num_q<DIM>();
     const int lane = threadIdx.x & 63;
-    const int line = threadIdx.x >> 6;
+    const int line = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int cl = DIR == 0 ? line : (int)threadIdx.x % QLINES, cq = DIR == 0 ? lane : (int)threadIdx.x / QLINES;
     const int seg = blk % nseg;
-    const long long lid = (long long)(blk / nseg) * QLINES + line;
-    const bool active = lid < nlines;
+    const long long lid0 = (long long)(blk / nseg) * QLINES;
     const int n = g.n[DIR];
     const int s0 = -NG + seg * QSEG;                 // first output (padded coordinate)
     const int s_end = min(s0 + QSEG, n + NG);
-    int ci = 0, cj = 0, ck = 0;
-    if (active) {
-        if (DIR == 0) { cj = (int)(lid % g.n[1]); ck = (int)(lid / g.n[1]); }
-        else if (DIR == 1) { ci = (int)(lid % g.n[0]); ck = (int)(lid / g.n[0]); }
-        else { ci = (int)(lid % g.n[0]); cj = (int)(lid / g.n[0]); }
-    }
-    const long long pstride = DIR == 0 ? 1 : (DIR == 1 ? (long long)g.P[0] : (long long)g.P[0] * g.P[1]);
-    const long long istride = DIR == 0 ? 1 : (DIR == 1 ? (long long)g.n[0] : (long long)g.n[0] * g.n[1]);
-    const long long pbase = pidx(g, ci, cj, ck);
-    const long long ibase = iidx(g, ci, cj, ck);
     const long long P = g.pnodes, N = g.nodes;
     const double idxi = 1.0 / g.dxi[DIR];
-
-    // ---- states (positions s0 - 5 .. s0 + 58), Phi'(V), residual cotangents
+    const double c0 = G / (G - 1.0), c1 = 1.0 / (G - 1.0);
+    // this thread's position of line cl in memory
+    const int sm = s0 - QHALO + cq;
+    const bool on = lid0 + cl < nlines;
+    long long pat = 0, iat = 0;
     {
-        const int s = s0 - QHALO + lane;
-        double v[10], a[NA];
-#pragma unroll
-        for (int c = 0; c < 10; ++c) v[c] = 0.0;
-        v[0] = 1.0;
-        v[4] = 1.0;
-#pragma unroll
-        for (int c = 0; c < NA; ++c) a[c] = c == 1 ? 1.0 : 0.0;
-        if (active && s >= -NG && s < n + NG) {
-            const long long idx = pbase + (long long)s * pstride;
-#pragma unroll
-            for (int c = 0; c < 10; ++c) v[c] = prim[c * P + idx];
-#pragma unroll
-            for (int c = 0; c < NA; ++c) a[c] = met[(DIR * NA + c) * P + idx];
-        }
-        const StateRMHD<double> st = rmhd_state<double>(G, v);
-        double Pp[8];
-        rmhd_phi_prime<double>(st, Pp);
-#pragma unroll
-        for (int c = 0; c < 10; ++c) sd[line][c][lane] = v[c];
-#pragma unroll
-        for (int c = 0; c < NA; ++c) sd[line][F_A + c][lane] = a[c];
-#pragma unroll
-        for (int c = 0; c < 8; ++c) sd[line][F_PP + c][lane] = Pp[c];
-        const bool in = active && s >= 0 && s < n;
-#pragma unroll
-        for (int c = 0; c < 8; ++c) sl[line][c][lane] = in ? lam[c * N + ibase + (long long)s * istride] : 0.0;
+        const long long lid = on ? lid0 + cl : 0;
+        const int nf = DIR == 0 ? g.n[1] : g.n[0];
+        const int fa = (int)(lid % nf), fb = (int)(lid / nf);
+        const int ci = DIR == 0 ? 0 : fa, cj = DIR == 0 ? fa : (DIR == 1 ? 0 : fb), ck = DIR == 2 ? 0 : fb;
+        pat = pidx(g, ci, cj, ck) + sm * (DIR == 0 ? 1LL : (DIR == 1 ? (long long)g.P[0] : (long long)g.P[0] * g.P[1]));
+        iat = iidx(g, ci, cj, ck) + sm * (DIR == 0 ? 1LL : (DIR == 1 ? (long long)g.n[0] : (long long)g.n[0] * g.n[1]));
     }
-    __syncthreads();
-
-    auto prim_at = [&](int q, double* Pq) {
-#pragma unroll
-        for (int c = 0; c < 8; ++c) Pq[c] = sd[line][c][q];
-    };
-    auto lamPp = [&](int q) {
-        double s = 0.0;
-#pragma unroll
-        for (int c = 0; c < 8; ++c) s += sl[line][c][q] * sd[line][F_PP + c][q];
-        return s;
-    };
-    // B~ pair value of slots (qa, qb)
-    auto bpair = [&](int qa, int qb) {
-        double s = 0.0;
-#pragma unroll
-        for (int j = 0; j < DIM; ++j)
-            s += 0.25 * (sd[line][F_A + 1 + j][qa] + sd[line][F_A + 1 + j][qb]) * (sd[line][5 + j][qa] + sd[line][5 + j][qb]);
-        return s;
-    };
-
-    // ---- pairs (s', s'+n), s' = s0 - 3 + lane, slot of s' = lane + 2
-    const int o = lane;                            // output lane: position s0 + o, slot o + 5
-    double acc[8];
-#pragma unroll
-    for (int c = 0; c < 8; ++c) acc[c] = 0.0;
     {
-        const int ql = lane + 2;
-        double Pl[8], al[NA];
-        if (lane < QSEG + 3) {
-            prim_at(ql, Pl);
+        // states, metrics and cotangents (a position off the line: a state at rest)
+        double v[10], a[NA], lm[8];
+        const bool st = on && sm >= -NG && sm < n + NG, in = on && sm >= 0 && sm < n;
+        const long long ip = st ? pat : 0, ii = in ? iat : 0;
 #pragma unroll
-            for (int c = 0; c < NA; ++c) al[c] = sd[line][F_A + c][ql];
-        }
-#pragma unroll 1
-        for (int nn = 1; nn <= PO; ++nn) {
-            double gl[8], gr[8];
+        for (int c = 0; c < 10; ++c) v[c] = prim[c * P + ip];
 #pragma unroll
-            for (int c = 0; c < 8; ++c) { gl[c] = 0.0; gr[c] = 0.0; }
-            if (active && lane < QSEG + 3) {
-                const int qr = ql + nn;
-                double w[8];
-                bool any = false;
+        for (int c = 0; c < NA; ++c) a[c] = met[(DIR * NA + c) * P + ip];
 #pragma unroll
-                for (int c = 0; c < 8; ++c) {
-                    w[c] = alpha_pn(PO, nn) * idxi * (sl[line][c][qr] - sl[line][c][ql]);
-                    any |= w[c] != 0.0;
-                }
-                double ar[NA];
+        for (int c = 0; c < 8; ++c) lm[c] = lam[c * N + ii];
 #pragma unroll
-                for (int c = 0; c < NA; ++c) ar[c] = sd[line][F_A + c][qr];
-                if (any) {
-                    double Pr[8];
-                    prim_at(qr, Pr);
-                    pair_vjp_rmhd<DIM>(G, Pl, Pr, al, ar, w, gl, gr);
-                }
-                // source pair B~: linear in B_j of both nodes
-                const double wB = alpha_pn(PO, nn) * idxi * (lamPp(qr) - lamPp(ql));
+        for (int c = 0; c < 10; ++c) v[c] = st ? v[c] : (c == 0 || c == 4 ? 1.0 : 0.0);
 #pragma unroll
-                for (int j = 0; j < DIM; ++j) {
-                    const double cb = 0.25 * wB * (al[1 + j] + ar[1 + j]);
-                    gl[5 + j] += cb;
-                    gr[5 + j] += cb;
-                }
-            }
+        for (int c = 0; c < NA; ++c) a[c] = st ? a[c] : (c == 1 ? 1.0 : 0.0);
+        const double W = psqrt(1.0 + v[1] * v[1] + v[2] * v[2] + v[3] * v[3]), iW = frcp(W), beta = v[0] * frcp(v[4]);
+        const double b0 = v[1] * v[5] + v[2] * v[6] + v[3] * v[7];
+        auto f = lds.f[cl];
+        f[L::RHO][cq] = v[0];
+        f[L::BETA][cq] = beta;
+        f[L::LR][cq] = v[8];
+        f[L::LB][cq] = v[9];
+        f[L::W][cq] = W;
+        f[L::B0][cq] = b0;
 #pragma unroll
-            for (int c = 0; c < 8; ++c) {
-                buf[line][nn - 1][c][lane] = gl[c];
-                buf[line][3 + nn - 1][c][lane] = gr[c];
+        for (int k = 0; k < 3; ++k) {
+            const double b = (v[5 + k] + b0 * v[1 + k]) * iW;
+            f[L::U + k][cq] = v[1 + k];
+            f[L::b + k][cq] = b;
+            f[L::B + k][cq] = v[5 + k];
+            if (ES) {
+                f[L::V + (ES ? 1 + k : 0)][cq] = beta * v[1 + k];
+                f[L::V + (ES ? 5 + k : 0)][cq] = beta * b;
             }
         }
-    }
-    __syncthreads();
-    if (o < QSEG) {
+        if (ES) {
+            f[L::V + 0][cq] = c0 + v[8] + v[9] * c1 + beta;
+            f[L::V + (ES ? 4 : 0)][cq] = -beta * W;
+        }
 #pragma unroll
-        for (int nn = 1; nn <= PO; ++nn)
+        for (int c = 0; c < NA; ++c) f[L::A + c][cq] = a[c];
 #pragma unroll
-            for (int c = 0; c < 8; ++c)
-                acc[c] += buf[line][nn - 1][c][o + 3] + buf[line][3 + nn - 1][c][o + 3 - nn];
+        for (int c = 0; c < 8; ++c) f[L::LAM + c][cq] = in ? lm[c] : 0.0;
     }
+    if (DIR == 0) wave_lds_sync();
+    else __syncthreads();
+    const bool active = lid0 + line < nlines;
+    auto f = lds.f[line];
 
     // ---- entropy-variable cotangents of the stencil states from the faces
     double gV[8];
 #pragma unroll
     for (int c = 0; c < 8; ++c) gV[c] = 0.0;
-    if (ES) {
-        __syncthreads();
-        // faces f = s0 - 3 + lane (stencil slots lane + 3 - PO .. lane + 2 + PO, nodes i, i+1 at
-        // lane + 2, lane + 3); stencil node j at slot lane + 3 - PO + j, CI = PO - 1 the node i
-        constexpr int NS = 2 * PO, CI = PO - 1, J0 = 3 - PO;
+    if constexpr (ES) {
+        // stencil node j of face lane + 1/2 at lane - CI + j
+        constexpr int NS = 2 * PO, CI = PO - 1;
         double gw[NS][8];
 #pragma unroll
         for (int j = 0; j < NS; ++j)
 #pragma unroll
             for (int c = 0; c < 8; ++c) gw[j][c] = 0.0;
-        if (active && lane < QSEG + 5) {
+        if (active && lane >= 2 && lane <= 60) {
             double z[8];
             bool any = false;
 #pragma unroll
             for (int c = 0; c < 8; ++c) {
-                z[c] = 0.5 * idxi * (sl[line][c][lane + 2] - sl[line][c][lane + 3]);
+                z[c] = 0.5 * idxi * (f[L::LAM + c][lane] - f[L::LAM + c][lane + 1]);
                 any |= z[c] != 0.0;
             }
             if (any) {
-                double P2[8], P3[8], al[NA], ar[NA];
-                prim_at(lane + 2, P2);
-                prim_at(lane + 3, P3);
-#pragma unroll
-                for (int c = 0; c < NA; ++c) { al[c] = sd[line][F_A + c][lane + 2]; ar[c] = sd[line][F_A + c][lane + 3]; }
                 // the eigen-structure of this face (held at its forward value) from
-                // k_face_eigen_rmhd: face f = p + 1 of line lid, p = s0 - 3 + lane
-                double T[3][3], TV[NS][8], at, L, Rc[8][8];
-                face_frame_rmhd<DIM>(G, P2, P3, al, ar, T, TV[CI], TV[CI + 1], at, L);
-                const double* ef = eig + lid * (n + 1) + (s0 - 2 + lane);
+                // k_face_eigen_rmhd: the face between positions p = s0 - QHALO + lane and
+                // p + 1 has index p + 1
+                const double* ef = eig + (lid0 + line) * (n + 1) + (s0 - QHALO + lane + 1);
+                const double lhat = ef[72 * enf];
+                double nx[9];
 #pragma unroll
-                for (int k = 0; k < 8; ++k)
-#pragma unroll
-                    for (int i = 0; i < 8; ++i) Rc[k][i] = ef[(k * 8 + i) * enf];
-                const double lhat = ef[64 * enf];
-#pragma unroll
-                for (int j = 0; j < NS; ++j) {
-                    if (j == CI || j == CI + 1) continue;
-                    double Pj[8], V[8];
-                    prim_at(lane + J0 + j, Pj);
-                    const StateRMHD<double> st = rmhd_state<double>(G, Pj);
-                    rmhd_entropy_vars<double>(G, st, V);
-                    rotate8<false>(T, V, TV[j]);
-                }
-                double tv2 = 0.0, tv3 = 0.0;
-#pragma unroll
-                for (int c = 0; c < 8; ++c) { tv2 = fmax(tv2, fabs(TV[CI][c])); tv3 = fmax(tv3, fabs(TV[CI + 1][c])); }
-                const double tvmax = tv2 + tv3;
-                // d = lhat T^T dd: cotangent of dd
-                double gdd[8];
-                rotate8<false>(T, z, gdd);
-#pragma unroll
-                for (int c = 0; c < 8; ++c) gdd[c] *= lhat;
-                double gTV[NS][8];
-#pragma unroll
-                for (int j = 0; j < NS; ++j)
-#pragma unroll
-                    for (int c = 0; c < 8; ++c) gTV[j][c] = 0.0;
+                for (int i = 0; i < 9; ++i) nx[i] = ef[i * enf];
 #pragma unroll 1
                 for (int k = 0; k < 8; ++k) {
-                    const double* r = Rc[k];
-                    double vt[NS];
+                    double r[9];
+#pragma unroll
+                    for (int i = 0; i < 9; ++i) r[i] = nx[i];
+                    ef += k < 7 ? 9 * enf : 0;
+#pragma unroll
+                    for (int i = 0; i < 9; ++i) nx[i] = ef[i * enf];
+                    // (the stencil read again for each column, not held through the loop)
+                    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+                    double vt[NS], gj = 0.0;
 #pragma unroll
                     for (int j = 0; j < NS; ++j) {
                         double s = 0.0;
 #pragma unroll
-                        for (int c = 0; c < 8; ++c) s += r[c] * TV[j][c];
+                        for (int c = 0; c < 8; ++c) s = fma(r[c], f[L::V + c][lane - CI + j], s);
                         vt[j] = s;
                     }
-                    double jw;
-                    if (PO == 3)
-                        jw = weno5(vt[5], vt[4], vt[3], vt[2], vt[1], eps) -
-                             weno5(vt[0], vt[1], vt[2], vt[3], vt[4], eps);
-                    else
-                        jw = weno3(vt[3], vt[2], vt[1], eps) - weno3(vt[0], vt[1], vt[2], eps);
+#pragma unroll
+                    for (int c = 0; c < 8; ++c) gj = fma(z[c], r[c], gj);
+                    double dj[NS];
+                    const double jw = weno_jump_grad<PO>(vt, eps, dj);
                     const double jp = vt[CI + 1] - vt[CI];
-                    double r1 = 0.0;
+                    gj = jw * jp > 0.0 && fabs(jp) > r[8] ? gj * lhat : 0.0;
 #pragma unroll
-                    for (int c = 0; c < 8; ++c) r1 += fabs(r[c]);
-                    if (jw * jp > 0.0 && fabs(jp) > RealTraits<double>::ytol * r1 * tvmax) {
-                        double gjw = 0.0;
+                    for (int j = 0; j < NS; ++j) {
+                        const double gv = gj * dj[j];
 #pragma unroll
-                        for (int c = 0; c < 8; ++c) gjw += gdd[c] * r[c];
-                        double djw[NS];
-                        if (PO == 3) {
-                            double gp[5], gm[5];
-                            weno5_grad_m(vt[5], vt[4], vt[3], vt[2], vt[1], eps, gp);
-                            weno5_grad_m(vt[0], vt[1], vt[2], vt[3], vt[4], eps, gm);
-                            djw[0] = -gm[0];
-                            djw[1] = gp[4] - gm[1];
-                            djw[2] = gp[3] - gm[2];
-                            djw[3] = gp[2] - gm[3];
-                            djw[4] = gp[1] - gm[4];
-                            djw[NS - 1] = gp[0];
-                        } else {
-                            double gp[3], gm[3];
-                            weno3_grad_m(vt[3], vt[2], vt[1], eps, gp);
-                            weno3_grad_m(vt[0], vt[1], vt[2], eps, gm);
-                            djw[0] = -gm[0];
-                            djw[1] = gp[2] - gm[1];
-                            djw[2] = gp[1] - gm[2];
-                            djw[NS - 1] = gp[0];
-                        }
-#pragma unroll
-                        for (int j = 0; j < NS; ++j) {
-                            const double gv = gjw * djw[j];
-#pragma unroll
-                            for (int c = 0; c < 8; ++c) gTV[j][c] += gv * r[c];
-                        }
+                        for (int c = 0; c < 8; ++c) gw[j][c] = fma(gv, r[c], gw[j][c]);
                     }
                 }
-                // TV_j = T V_j: cotangent of V_j
-#pragma unroll
-                for (int j = 0; j < NS; ++j) rotate8<true>(T, gTV[j], gw[j]);
             }
         }
 #pragma unroll
         for (int j = 0; j < NS; ++j)
 #pragma unroll
-            for (int c = 0; c < 8; ++c) buf[line][j][c][lane] = gw[j][c];
-        __syncthreads();
-        if (o < QSEG) {
-#pragma unroll
-            for (int j = 0; j < NS; ++j)
-#pragma unroll
-                for (int c = 0; c < 8; ++c) gV[c] += buf[line][j][c][o + 5 - J0 - j];
-        }
+            for (int c = 0; c < 8; ++c) gV[c] += __shfl(gw[j][c], lane + CI - j);
     }
 
-    // ---- node terms: the Godunov-Powell source (Phi'(P_s) against the B~
-    // differences) and the entropy-variable chain, one dual pass over P_s
-    const int s = s0 + o;
-    if (active && o < QSEG && s < s_end) {
-        const int q = o + 5;
-        double dB = 0.0;
+    auto node = [&](int q) {
+        NodeQM x;
+        x.rho = f[L::RHO][q];
+        x.beta = f[L::BETA][q];
+        x.lr = f[L::LR][q];
+        x.lb = f[L::LB][q];
+        x.W = f[L::W][q];
+        x.b0 = f[L::B0][q];
 #pragma unroll
-        for (int nn = 1; nn <= PO; ++nn) dB += alpha_pn(PO, nn) * (bpair(q, q + nn) - bpair(q - nn, q));
-        dB *= idxi;
-        double lq[8];
-#pragma unroll
-        for (int c = 0; c < 8; ++c) lq[c] = sl[line][c][q];
-        using D = Dual<8>;
-        D Pd[8];
-#pragma unroll
-        for (int c = 0; c < 8; ++c) Pd[c] = D::seed(sd[line][c][q], c);
-        const StateRMHD<D> st = rmhd_state<D>(G, Pd);
-        D Pp[8], V[8];
-        rmhd_phi_prime<D>(st, Pp);
-        if (ES) rmhd_entropy_vars<D>(G, st, V);
-#pragma unroll
-        for (int k = 0; k < 8; ++k) {
-            double t = 0.0;
-#pragma unroll
-            for (int c = 0; c < 8; ++c) t -= dB * lq[c] * Pp[c].d[k];
-            if (ES) {
-#pragma unroll
-                for (int c = 0; c < 8; ++c) t += gV[c] * V[c].d[k];
-            }
-            acc[k] += t;
+        for (int k = 0; k < 3; ++k) {
+            x.u[k] = f[L::U + k][q];
+            x.b[k] = f[L::b + k][q];
+            x.B[k] = f[L::B + k][q];
         }
-        const long long idx = pbase + (long long)s * pstride;
+        return x;
+    };
+    double acc[NQ];
+    double lp = 0.0, dB = 0.0;   // W (lambda . Phi'), the B~ differences
+    const NodeQM x = node(lane);
+    const double iW = frcp(x.W);
+    {
+        const double ir = frcp(x.rho);
+        double gb = gV[0] * (c1 * frcp(x.beta) + 1.0) - gV[4] * x.W;
 #pragma unroll
-        for (int c = 0; c < 8; ++c) gout[c * P + idx] = acc[c];
+        for (int c = 0; c < NQ; ++c) acc[c] = 0.0;
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            gb += gV[1 + k] * x.u[k] + gV[5 + k] * x.b[k];
+            acc[Q_U + k] = gV[1 + k] * x.beta;
+            acc[Q_b + k] = gV[5 + k] * x.beta;
+            lp += f[L::LAM + 1 + k][lane] * x.b[k] + f[L::LAM + 5 + k][lane] * x.u[k];
+        }
+        lp += f[L::LAM + 4][lane] * x.b0;
+        acc[Q_RHO] = gV[0] * ir;
+        acc[Q_BETA] = gb;
+        acc[Q_W] = -gV[4] * x.beta;
+    }
+    const double lpW = lp * iW;
+
+    // ---- pairs (lane, lane + nn) and their source pairs B~
+#pragma unroll 1
+    for (int nn = 1; nn <= PO; ++nn) {
+        double gl[NQ], gr[NQ];
+#pragma unroll
+        for (int c = 0; c < NQ; ++c) { gl[c] = 0.0; gr[c] = 0.0; }
+        const double al_n = alpha_pn(PO, nn), wn = al_n * idxi;
+        const int qr = min(lane + nn, QLOAD - 1);
+        double a[NA], ar[NA], w[8], bp = 0.0;
+        bool any = false;
+#pragma unroll
+        for (int c = 0; c < NA; ++c) { a[c] = f[L::A + c][lane]; ar[c] = f[L::A + c][qr]; }
+#pragma unroll
+        for (int c = 0; c < 8; ++c) {
+            w[c] = wn * (f[L::LAM + c][qr] - f[L::LAM + c][lane]);
+            any |= w[c] != 0.0;
+        }
+        if (any && active && lane >= 2 && lane + nn <= 61) pair_vjp_rmhd<DIM>(G, x, node(qr), a, ar, w, gl, gr);
+        const double wB = 0.25 * wn * (__shfl(lpW, lane + nn) - lpW);
+#pragma unroll
+        for (int j = 0; j < DIM; ++j) {
+            const double s = a[1 + j] + ar[1 + j];
+            bp += s * (x.B[j] + f[L::B + j][qr]);
+            gl[Q_B + j] += wB * s;
+            gr[Q_B + j] += wB * s;
+        }
+        bp *= 0.25 * wn;
+        dB += bp - __shfl(bp, lane - nn);
+#pragma unroll
+        for (int c = 0; c < NQ; ++c) acc[c] += gl[c] + __shfl(gr[c], lane - nn);
+    }
+
+    // ---- the Godunov-Powell source: -dB (lambda . Phi'), Phi' = (0, b, b_0, u)/W
+    {
+        const double t = -dB * iW;
+        acc[Q_B0] += t * f[L::LAM + 4][lane];
+        acc[Q_W] -= t * lpW;
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            acc[Q_b + k] += t * f[L::LAM + 1 + k][lane];
+            acc[Q_U + k] += t * f[L::LAM + 5 + k][lane];
+        }
+    }
+    double gP[8];
+    node_vjp_rmhd<DIM>(x, acc, gP);
+    const bool out = on && cq >= QHALO && cq < QHALO + QSEG && sm < s_end;
+    if (DIR == 0) {
+        if (out) {
+#pragma unroll
+            for (int c = 0; c < 8; ++c) gout[c * P + pat] = gP[c];
+        }
+    } else {
+        wave_lds_sync();
+#pragma unroll
+        for (int c = 0; c < 8; ++c) f[c][lane] = gP[c];
+        __syncthreads();
+        if (out) {
+#pragma unroll
+            for (int c = 0; c < 8; ++c) gout[c * P + pat] = lds.f[cl][c][cq];
+        }
     }
 }
 
 template <int DIM, bool ES, int PO>
-__global__ void __launch_bounds__(128) k_residual_vjp_rmhd(GridDev g, double G, double eps,
+__global__ void __launch_bounds__(64 * QLINES) __attribute__((amdgpu_waves_per_eu(2))) k_residual_vjp_rmhd(GridDev g, double G, double eps,
                                                            const double* __restrict__ prim,
                                                            const double* __restrict__ met,
                                                            const double* __restrict__ lam,
                                                            double* __restrict__ gdir, AdjPlanM pl,
                                                            const double* __restrict__ eig, FaceEigPlan fp) {
-    __shared__ AdjLDSM<DIM> lds;
+    __shared__ AdjLDSM<DIM, ES> lds;
     const long long slab = 8LL * g.pnodes;
     int b = xcd_block((int)blockIdx.x, (int)gridDim.x);
     if (b < pl.nblk[0]) {

@@ -145,4 +145,67 @@ __device__ __forceinline__ void pair_vjp_rhd(double G, const double* Pl, const d
     }
 }
 
+// The WENO jump weno_jump<P>(v) (P = 2, 3) with its gradient g over the 2P values.  A side's
+// value is sum_k w_k q_k / (c sum_k w_k) in the differences of v, w_k ~ 1/e_k^2; with om_k =
+// w_k / sum w, its derivative is sum_k om_k dq_k / c + sum_k H_k de_k, H_k = -2 om_k (q_k -
+// sum om q) / (c e_k).  One reciprocal per side.
+template <int P>
+__device__ __forceinline__ double weno_jump_grad(const double* v, double eps, double* g) {
+    static_assert(P == 2 || P == 3, "the adjoint's orders");
+    constexpr int ND = 2 * P - 1;
+    double d[ND], gd[ND];
+#pragma unroll
+    for (int k = 0; k < ND; ++k) { d[k] = v[k + 1] - v[k]; gd[k] = 0.0; }
+    // the value of the side that sees D[0], D[1], ..; gD its negative gradient
+    auto side = [eps](const double* D, double* gD) {
+        if constexpr (P == 2) {
+            const double e0 = fma(D[0], D[0], eps), e1 = fma(D[1], D[1], eps);
+            const double w0 = e1 * e1, w1 = 2.0 * (e0 * e0), S = w0 + w1, E = e0 * e1;
+            const double r = frcp(S * E), iS = E * r, Sr = S * r;
+            const double m0 = w0 * iS, m1 = w1 * iS, q = fma(m0, D[0], m1 * D[1]);
+            gD[0] = m0 * fma(2.0 * (D[0] - q) * (Sr * e1), D[0], -0.5);
+            gD[1] = m1 * fma(2.0 * (D[1] - q) * (Sr * e0), D[1], -0.5);
+            return 0.5 * q;
+        } else {
+            const double t0 = D[1] - D[0], t1 = D[2] - D[1], t2 = D[3] - D[2];
+            const double s0 = fma(3.0, D[1], -D[0]), s1 = D[1] + D[2], s2 = fma(3.0, D[2], -D[3]);
+            const double e0 = fma(s0, s0, fma((13.0 / 3.0) * t0, t0, 4.0 * eps));
+            const double e1 = fma(s1, s1, fma((13.0 / 3.0) * t1, t1, 4.0 * eps));
+            const double e2 = fma(s2, s2, fma((13.0 / 3.0) * t2, t2, 4.0 * eps));
+            const double e01 = e0 * e1, e12 = e1 * e2, e02 = e0 * e2;
+            const double w0 = e12 * e12, w1 = 6.0 * (e02 * e02), w2 = 3.0 * (e01 * e01);
+            const double q0 = fma(5.0, D[1], -2.0 * D[0]), q1 = fma(2.0, D[2], D[1]), q2 = fma(4.0, D[2], -D[3]);
+            const double S = w0 + w1 + w2, E = e01 * e2;
+            const double r = (1.0 / 6.0) * frcp(S * E), iS = E * r, Sr = -2.0 * (S * r);
+            const double m0 = w0 * iS, m1 = w1 * iS, m2 = w2 * iS;      // om_k / 6
+            const double v = fma(m0, q0, fma(m1, q1, m2 * q2)), v6 = 6.0 * v;
+            const double i6 = 6.0 * Sr;
+            const double H0 = m0 * (q0 - v6) * (i6 * e12), H1 = m1 * (q1 - v6) * (i6 * e02), H2 = m2 * (q2 - v6) * (i6 * e01);
+            const double x0 = H0 * (26.0 / 3.0) * t0, x1 = H1 * (26.0 / 3.0) * t1, x2 = H2 * (26.0 / 3.0) * t2;
+            const double y0 = 2.0 * H0 * s0, y1 = 2.0 * H1 * s1, y2 = 2.0 * H2 * s2;
+            gD[0] = fma(2.0, m0, x0 + y0);
+            gD[1] = -fma(5.0, m0, m1) - fma(3.0, y0, x0) + (x1 - y1);
+            gD[2] = -fma(2.0, m1, 4.0 * m2) - (x1 + y1) + fma(-3.0, y2, x2);
+            gD[3] = m2 - (x2 - y2);
+            return v;
+        }
+    };
+    double D[ND - 1], gD[ND - 1];
+    double j = d[P - 1];
+    gd[P - 1] = 1.0;
+#pragma unroll
+    for (int k = 0; k < ND - 1; ++k) D[k] = d[k];
+    j -= side(D, gD);
+#pragma unroll
+    for (int k = 0; k < ND - 1; ++k) { gd[k] += gD[k]; D[k] = d[ND - 1 - k]; }
+    j -= side(D, gD);
+#pragma unroll
+    for (int k = 0; k < ND - 1; ++k) gd[ND - 1 - k] += gD[k];
+    g[0] = -gd[0];
+#pragma unroll
+    for (int k = 1; k < ND; ++k) g[k] = gd[k - 1] - gd[k];
+    g[ND] = gd[ND - 1];
+    return j;
+}
+
 }  // namespace es

@@ -1,0 +1,144 @@
+// Reverse accumulation through the RMHD two-point EC flux (eq. ECFluxCurv with the pair U~,
+// F~_j of pair_flux_rhd's magnetised counterpart), written out.
+//
+// The contraction with the metrics collapses: with the means of the node quantities
+// (e = |b|^2 = sum_k b_k^2 - b_0^2) and
+//   un = a_j u_j, aB = a_j B_j, q = a_t W + un, c = un b_0 + aB, m = -(c + a_t {W b_0}),
+//   n = a_t (rho/beta + (sb + {W b_0^2}/W)/2) + c b_0/W, d = rho/beta + {e}/2,
+//   T_k = (u_k n + b_k m)/W + a_k d,   S_k = q b_k + (m/W) u_k,
+//   Z = a_0 rho^ln q + u.T + b.S - a_t {W e}/2 - a_j {u_j e}/2 + aB b_0,
+// the flux is F = (rho^ln q, u_k F_5/W + T_k, F_5, S_k), F_5 = W Z/(W^2 - |u|^2).  The
+// cotangents of the means go half to either node; the node quantities are taken back to the
+// primitive state once per node (node_vjp_rmhd), after all its pairs, faces and sources.
+#pragma once
+
+#include "es_pair_vjp.h"
+#include "es_rmhd.h"
+
+namespace es {
+
+// Node values of the sweep, and the order of a node's cotangents.
+struct NodeQM {
+    double rho, beta, lr, lb, W, b0, u[3], b[3], B[3];
+};
+enum { Q_RHO, Q_BETA, Q_W, Q_B0, Q_WB0, Q_WB02, Q_SB, Q_E, Q_U, Q_b = Q_U + 3, Q_B = Q_b + 3 };
+template <int DIM>
+constexpr int num_q() { return Q_B + DIM; }
+
+// Cotangents gl, gr (num_q<DIM>() each) of the node quantities of l and r from w of F.
+template <int DIM>
+__device__ __forceinline__ void pair_vjp_rmhd(double G, const NodeQM& l, const NodeQM& r, const double* al,
+                                              const double* ar, const double* w, double* gl, double* gr) {
+    double drl[2], dbl[2];
+    const double rln = log_mean_d(l.rho, r.rho, l.lr, r.lr, drl[0], drl[1]);
+    const double bln = log_mean_d(l.beta, r.beta, l.lb, r.lb, dbl[0], dbl[1]);
+    const double at = 0.5 * (al[0] + ar[0]);
+    const double W = 0.5 * (l.W + r.W), b0 = 0.5 * (l.b0 + r.b0), beta = 0.5 * (l.beta + r.beta);
+    const double Wb0 = 0.5 * (l.W * l.b0 + r.W * r.b0), wb = 0.5 * (l.W * l.b0 * l.b0 + r.W * r.b0 * r.b0);
+    double a[3], u[3], b[3], un = 0.0, aB = 0.0, uu = 0.0, sl = 0.0, sr = 0.0, aul = 0.0, aur = 0.0;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        a[k] = k < DIM ? 0.5 * (al[k < DIM ? 1 + k : 0] + ar[k < DIM ? 1 + k : 0]) : 0.0;
+        u[k] = 0.5 * (l.u[k] + r.u[k]);
+        b[k] = 0.5 * (l.b[k] + r.b[k]);
+        uu += u[k] * u[k];
+        sl += l.b[k] * l.b[k];
+        sr += r.b[k] * r.b[k];
+        if (k < DIM) {
+            un += a[k] * u[k];
+            aB += a[k] * (0.5 * (l.B[k] + r.B[k]));
+            aul += a[k] * l.u[k];
+            aur += a[k] * r.u[k];
+        }
+    }
+    const double sb = 0.5 * (sl + sr), el = sl - l.b0 * l.b0, er = sr - r.b0 * r.b0;
+    double ib, ibl, iW, iden;
+    frcp2((G - 1.0) * bln, beta, ibl, ib);
+    frcp2(W * W - uu, W, iden, iW);
+    const double a0 = 1.0 + ibl, pb = 0.5 * (l.rho + r.rho) * ib;
+    const double q = at * W + un, c = un * b0 + aB, m = -(c + at * Wb0);
+    const double n = at * (pb + 0.5 * (sb + wb * iW)) + c * b0 * iW, d = pb + 0.25 * (el + er);
+    const double S1 = rln * q, miW = m * iW, niW = n * iW;
+    double T[3], S[3];
+    double Z = a0 * S1 + aB * b0 - 0.25 * (el * (at * l.W + aul) + er * (at * r.W + aur)), wu = 0.0;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        T[k] = u[k] * niW + b[k] * miW + a[k] * d;
+        S[k] = q * b[k] + miW * u[k];
+        Z += u[k] * T[k] + b[k] * S[k];
+        wu += w[1 + k] * u[k];
+    }
+    const double F5 = W * iden * Z;
+    // backwards
+    const double g5 = wu * iW + w[4];
+    const double gZ = g5 * W * iden, g5F = g5 * F5;
+    double giW = wu * F5;
+    const double g1 = w[0] + gZ * a0;
+    const double gln = g1 * q;
+    double gu[3], gb[3], hu = 0.0, hb = 0.0, ha = 0.0, su = 0.0, sbb = 0.0;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        const double h = w[1 + k] + gZ * u[k], gs = w[5 + k] + gZ * b[k];
+        hu += h * u[k];
+        hb += h * b[k];
+        if (k < DIM) ha += h * a[k];
+        su += gs * u[k];
+        sbb += gs * b[k];
+        gu[k] = w[1 + k] * (F5 * iW) + gZ * T[k] + niW * h + miW * gs + 2.0 * u[k] * (iden * g5F);
+        gb[k] = gZ * S[k] + miW * h + q * gs;
+    }
+    const double gm = iW * (hb + su), gn = iW * hu, gq = sbb + g1 * rln;
+    giW += hu * n + (hb + su) * m + gn * (0.5 * at * wb + c * b0);
+    const double gc = gn * b0 * iW - gm;
+    const double gun = gc * b0 + gq, gaB = gZ * b0 + gc, gpb = ha + at * gn;
+    const double gW = g5F * iW + at * gq - 2.0 * W * (iden * g5F) - iW * iW * giW;
+    const double hgZ = -0.5 * gZ;
+    double* g[2] = {gl, gr};
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+        const NodeQM& x = t == 0 ? l : r;
+        const double e = t == 0 ? el : er;
+        double* o = g[t];
+        o[Q_RHO] = 0.5 * (gpb * ib) + gln * drl[t];
+        o[Q_BETA] = -0.5 * (gpb * pb * ib) - gZ * S1 * (ibl * ibl * (G - 1.0)) * dbl[t];
+        o[Q_W] = 0.5 * (gW + hgZ * at * e);
+        o[Q_B0] = 0.5 * (gZ * aB + gn * c * iW + gc * un);
+        o[Q_WB0] = -0.5 * (at * gm);
+        o[Q_WB02] = 0.25 * at * iW * gn;
+        o[Q_SB] = 0.25 * at * gn;
+        o[Q_E] = 0.25 * ha + 0.5 * hgZ * (at * x.W + (t == 0 ? aul : aur));
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            o[Q_U + k] = 0.5 * (gu[k] + a[k] * (gun + hgZ * e));
+            o[Q_b + k] = 0.5 * gb[k];
+            if (k < DIM) o[Q_B + k] = 0.5 * (a[k] * gaB);
+        }
+    }
+}
+
+// The cotangent gP of the primitive state (rho, u, p, B) from q of the node quantities.
+template <int DIM>
+__device__ __forceinline__ void node_vjp_rmhd(const NodeQM& x, const double* q, double* gP) {
+    const double iW = frcp(x.W), ip = x.beta * frcp(x.rho);
+    const double gs = 2.0 * (q[Q_SB] + q[Q_E]);
+    double gW = q[Q_W] + (q[Q_WB02] * x.b0 + q[Q_WB0]) * x.b0;
+    double g0 = q[Q_B0] + q[Q_WB0] * x.W + 2.0 * x.b0 * (q[Q_WB02] * x.W - q[Q_E]);
+    double gb[3], gbu = 0.0, gbb = 0.0;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        gb[k] = (q[Q_b + k] + gs * x.b[k]) * iW;      // of W b_k = B_k + b_0 u_k
+        gbu += gb[k] * x.u[k];
+        gbb += gb[k] * x.b[k];
+    }
+    g0 += gbu;
+    gW -= gbb;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        gP[1 + k] = q[Q_U + k] + gb[k] * x.b0 + g0 * x.B[k] + gW * iW * x.u[k];
+        gP[5 + k] = (k < DIM ? q[k < DIM ? Q_B + k : 0] : 0.0) + gb[k] + g0 * x.u[k];
+    }
+    gP[0] = q[Q_RHO] + q[Q_BETA] * ip;
+    gP[4] = -q[Q_BETA] * x.beta * ip;
+}
+
+}  // namespace es

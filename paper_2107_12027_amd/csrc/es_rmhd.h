@@ -804,22 +804,34 @@ __device__ __forceinline__ void face_frame_rmhd(double G, const double* P2, cons
 }
 
 // Eigen-structure of face i+1/2 from the primitive states of nodes i and i+1: lambda^ and
-// the columns, handed to col(k, r) (rotated frame).
+// the columns handed to col(k, r, thr), r in the fixed frame, thr the size below which a jump
+// of V~_k counts as zero (face_diss_rmhd_fn).
 template <int DIM, typename Col>
 __device__ __forceinline__ void face_eigen_rmhd(double G, const double* P2, const double* P3, const double* al,
                                                 const double* ar, double& lhat, Col&& col) {
     const double c0 = G / (G - 1.0), c1 = 1.0 / (G - 1.0);
-    double Vb[8], mu[6], Z[6][6], at, L;
+    double Vb[8], mu[6], Z[6][6], T[3][3], at, L, tvmax;
     {
-        double T[3][3], TV2[8], TV3[8];
+        double TV2[8], TV3[8], tv2 = 0.0, tv3 = 0.0;
         face_frame_rmhd<DIM>(G, P2, P3, al, ar, T, TV2, TV3, at, L);
 #pragma unroll
-        for (int c = 0; c < 8; ++c) Vb[c] = 0.5 * (TV2[c] + TV3[c]);
+        for (int c = 0; c < 8; ++c) {
+            Vb[c] = 0.5 * (TV2[c] + TV3[c]);
+            tv2 = fmax(tv2, fabs(TV2[c]));
+            tv3 = fmax(tv3, fabs(TV3[c]));
+        }
+        tvmax = tv2 + tv3;
     }
     rmhd_face_modes(G, c0, c1, Vb, mu, Z);
     bool grouped;
     lhat = rmhd_face_speed(Vb, mu, at, L, grouped);
-    rmhd_face_columns(G, c0, c1, Vb, mu, Z, grouped, col);
+    rmhd_face_columns(G, c0, c1, Vb, mu, Z, grouped, [&](int k, const double* r) {
+        double r1 = 0.0, rf[8];
+#pragma unroll
+        for (int c = 0; c < 8; ++c) r1 += fabs(r[c]);
+        rotate8<true>(T, r, rf);
+        col(k, rf, RealTraits<double>::ytol * r1 * tvmax);
+    });
 }
 
 // A stencil node of the RMHD dissipation: V_1 and what the rest of the entropy
