@@ -20,6 +20,8 @@
 // of lambda^, the time step, the mesh and its velocity are held fixed.
 #include <math.h>
 
+#include <type_traits>
+
 #include "es_internal.h"
 #include "es_launch.h"
 #include "es_rhd.h"
@@ -31,271 +33,22 @@ namespace es {
 
 namespace {
 
-// Cotangents g[j] (j = 0..5, primitive slots) of the stencil states of one face
-// dissipation d (face_diss_rhd) for the cotangent z of d.
-// Gradient of the WENO5-JS value weno5(a, b, c, d, e) with respect to its five
-// inputs, from the weights w_k = d_k / (eps + beta_k)^2 written out: with
-// S = sum_k w_k and v = sum_k w_k q_k / (6 S) (q_k the six-fold candidate values),
-// dv = [sum_k w_k dq_k + sum_k (q_k - 6 v) dw_k] / (6 S) and
-// dw_k = -2 w_k dbeta_k / (eps + beta_k).
-__device__ __forceinline__ void weno5_grad(double a, double b, double c, double d, double e, double eps,
-                                           double* gr) {
-    const double q0 = 2.0 * a - 7.0 * b + 11.0 * c;
-    const double q1 = -b + 5.0 * c + 2.0 * d;
-    const double q2 = 2.0 * c + 5.0 * d - e;
-    const double t0 = a - 2.0 * b + c, s0 = a - 4.0 * b + 3.0 * c;
-    const double t1 = b - 2.0 * c + d, s1 = b - d;
-    const double t2 = c - 2.0 * d + e, s2 = 3.0 * c - 4.0 * d + e;
-    const double e0 = eps + (13.0 / 12.0) * t0 * t0 + 0.25 * s0 * s0;
-    const double e1 = eps + (13.0 / 12.0) * t1 * t1 + 0.25 * s1 * s1;
-    const double e2 = eps + (13.0 / 12.0) * t2 * t2 + 0.25 * s2 * s2;
-    const double ie0 = 1.0 / e0, ie1 = 1.0 / e1, ie2 = 1.0 / e2;
-    const double w0 = 0.1 * ie0 * ie0, w1 = 0.6 * ie1 * ie1, w2 = 0.3 * ie2 * ie2;
-    const double S = w0 + w1 + w2;
-    const double iS6 = 1.0 / (6.0 * S);
-    const double v6 = (w0 * q0 + w1 * q1 + w2 * q2) / S;      // 6 v
-    // c_k dbeta_k with c_k = -2 w_k (q_k - 6 v) / (eps + beta_k), split over t_k and s_k
-    const double c0 = -2.0 * w0 * (q0 - v6) * ie0, c1 = -2.0 * w1 * (q1 - v6) * ie1, c2 = -2.0 * w2 * (q2 - v6) * ie2;
-    const double u0 = c0 * (13.0 / 6.0) * t0, v0 = c0 * 0.5 * s0;
-    const double u1 = c1 * (13.0 / 6.0) * t1, v1 = c1 * 0.5 * s1;
-    const double u2 = c2 * (13.0 / 6.0) * t2, v2 = c2 * 0.5 * s2;
-    gr[0] = (2.0 * w0 + u0 + v0) * iS6;
-    gr[1] = (-7.0 * w0 - w1 - 2.0 * u0 - 4.0 * v0 + u1 + v1) * iS6;
-    gr[2] = (11.0 * w0 + 5.0 * w1 + 2.0 * w2 + u0 + 3.0 * v0 - 2.0 * u1 + u2 + 3.0 * v2) * iS6;
-    gr[3] = (2.0 * w1 + 5.0 * w2 + u1 - v1 - 2.0 * u2 - 4.0 * v2) * iS6;
-    gr[4] = (-w2 + u2 + v2) * iS6;
-}
-
-// Gradient of the WENO3 value weno3(a, b, c) = (w0 q0 + w1 q1) / (2 S) with
-// q0 = 3b - a, q1 = b + c, w_k = d_k / e_k^2 (d = 1/3, 2/3), e0 = eps + (b - a)^2,
-// e1 = eps + (c - b)^2, S = w0 + w1 (any common factor of the w_k cancels):
-// dv = [w0 dq0 + w1 dq1 + (q0 - 2v) dw0 + (q1 - 2v) dw1] / (2 S), dw_k = -2 w_k de_k / e_k.
-__device__ __forceinline__ void weno3_grad(double a, double b, double c, double eps, double* gr) {
-    const double q0 = 3.0 * b - a, q1 = b + c;
-    const double e0 = eps + (b - a) * (b - a), e1 = eps + (c - b) * (c - b);
-    const double w0 = (1.0 / 3.0) * (e1 * e1), w1 = (2.0 / 3.0) * (e0 * e0);   // both times e0^2 e1^2
-    const double S = w0 + w1;
-    const double v2 = (w0 * q0 + w1 * q1) / S;                                   // 2 v
-    const double c0 = -4.0 * w0 * (q0 - v2) * (b - a) / e0;                     // times (db - da)
-    const double c1 = -4.0 * w1 * (q1 - v2) * (c - b) / e1;                     // times (dc - db)
-    const double i2S = 1.0 / (2.0 * S);
-    gr[0] = (-w0 - c0) * i2S;
-    gr[1] = (3.0 * w0 + w1 + c0 - c1) * i2S;
-    gr[2] = (w1 + c1) * i2S;
-}
-
-// P: the order parameter p (stencil of 2p nodes, WENO of order 2p - 1).
-// gtv(j, c): the accumulator of the cotangent of the rotated entropy variable c of
-// stencil node j (a slot of the caller's LDS, the same slot that out(j, c, .)
-// later receives the primitive cotangent in); keeping these 2p x M sums out of
-// the registers is what lets the 3D kernel hold its column loop without spills.
-// gra(q, c): the cotangent of entry c of eigenvector column q, likewise an LDS
-// slot of the caller (it lives from the column loop through the eigen-structure
-// tangents, whose dual-number arithmetic needs the registers).
-template <int DIM, int P, typename NodeFn, typename Sync, typename GT, typename GRA, typename Out>
-__device__ void face_vjp_rhd(double G, double eps, NodeFn&& node, Sync&& sync, const double* al,
-                             const double* ar, const double* z, GT&& gtv, GRA&& gra, Out&& out) {
-    constexpr int M = DIM + 2;
-    constexpr int NS = 2 * P, CI = P - 1;
-    const double at = 0.5 * (al[0] + ar[0]);
-    double ax[3] = {0.0, 0.0, 0.0};
-#pragma unroll
-    for (int j = 0; j < DIM; ++j) ax[j] = 0.5 * (al[1 + j] + ar[1 + j]);
-    const double L = sqrt(ax[0] * ax[0] + ax[1] * ax[1] + ax[2] * ax[2]);
-    const double iL = frcp(L);
-    double nrm[3] = {ax[0] * iL, ax[1] * iL, ax[2] * iL};
-    double T[3][3];
-    rotation<DIM>(nrm, T);
-    const double c0 = G / (G - 1.0), c1 = 1.0 / (G - 1.0);
-
-    // (the stencil states are read through node(j) here and again at the end, so
-    // that they need not stay in registers in between)
-    double TV[NS][M];
-#pragma unroll
-    for (int j = 0; j < NS; ++j) {
-        const NodeRHD<DIM> q = node(j);
-        TV[j][0] = c0 + q.lr + q.lb * c1 + q.beta;
-#pragma unroll
-        for (int a = 0; a < DIM; ++a) {
-            double s = 0.0;
-#pragma unroll
-            for (int b = 0; b < DIM; ++b) s += T[a][b] * q.u[b];
-            TV[j][1 + a] = q.beta * s;
-        }
-        TV[j][M - 1] = -q.beta * q.W;
-    }
-
-    // forward: the eigen-structure as a matrix (column q in Rm[q])
-    double Rm[M][M];
-    const double lhat = face_eigen_columns<DIM>(G, TV[CI], TV[CI + 1], at, L, [&](const double* r, int q) {
-#pragma unroll
-        for (int c = 0; c < M; ++c) Rm[q][c] = r[c];
-    });
-    double tv2 = 0.0, tv3 = 0.0;
-#pragma unroll
-    for (int c = 0; c < M; ++c) { tv2 = fmax(tv2, fabs(TV[CI][c])); tv3 = fmax(tv3, fabs(TV[CI + 1][c])); }
-    const double tvmax = tv2 + tv3;
-
-    // z in the rotated frame: d = lhat T^T dd, so d(z.d)/d(dd) = lhat T z
-    double zr[M];
-    zr[0] = z[0];
-    zr[M - 1] = z[M - 1];
-#pragma unroll
-    for (int a = 0; a < DIM; ++a) {
-        double s = 0.0;
-#pragma unroll
-        for (int b = 0; b < DIM; ++b) s += T[a][b] * z[1 + b];
-        zr[1 + a] = s;
-    }
-
-    double dd[M];
-#pragma unroll
-    for (int c = 0; c < M; ++c) {
-        dd[c] = 0.0;
-#pragma unroll
-        for (int j = 0; j < NS; ++j) gtv(j, c) = 0.0;
-    }
-#pragma unroll 1
-    for (int q = 0; q < M; ++q) {
-        // column q and its cotangent row through selects (no dynamic register indexing)
-        double r[M], gRq[M];
-#pragma unroll
-        for (int c = 0; c < M; ++c) { r[c] = 0.0; gRq[c] = 0.0; }
-#pragma unroll
-        for (int qq = 0; qq < M; ++qq)
-#pragma unroll
-            for (int c = 0; c < M; ++c) r[c] = qq == q ? Rm[qq][c] : r[c];
-        double vt[NS];
-#pragma unroll
-        for (int j = 0; j < NS; ++j) {
-            double s = 0.0;
-#pragma unroll
-            for (int c = 0; c < M; ++c) s += r[c] * TV[j][c];
-            vt[j] = s;
-        }
-        // the jump and its switch exactly as in the forward dissipation
-        double jwv;
-        if (P == 3)
-            jwv = weno5(vt[5], vt[4], vt[3], vt[2], vt[1], eps) - weno5(vt[0], vt[1], vt[2], vt[3], vt[4], eps);
-        else
-            jwv = weno3(vt[3], vt[2], vt[1], eps) - weno3(vt[0], vt[1], vt[2], eps);
-        const double jp = vt[CI + 1] - vt[CI];
-        double r1 = 0.0;
-#pragma unroll
-        for (int c = 0; c < M; ++c) r1 += fabs(r[c]);
-        if (jwv * jp > 0.0 && fabs(jp) > RealTraits<double>::ytol * r1 * tvmax) {
-            // d(jw)/d(vt_j): the upwind-from-the-right value minus the one from the left
-            double djw[NS];
-            if (P == 3) {
-                double gp[5], gm[5];
-                weno5_grad(vt[5], vt[4], vt[3], vt[2], vt[1], eps, gp);
-                weno5_grad(vt[0], vt[1], vt[2], vt[3], vt[4], eps, gm);
-                djw[0] = -gm[0];
-                djw[1] = gp[4] - gm[1];
-                djw[2] = gp[3] - gm[2];
-                djw[3] = gp[2] - gm[3];
-                djw[4] = gp[1] - gm[4];
-                djw[NS - 1] = gp[0];
-            } else {
-                double gp[3], gm[3];
-                weno3_grad(vt[3], vt[2], vt[1], eps, gp);
-                weno3_grad(vt[0], vt[1], vt[2], eps, gm);
-                djw[0] = -gm[0];
-                djw[1] = gp[2] - gm[1];
-                djw[2] = gp[1] - gm[2];
-                djw[NS - 1] = gp[0];
-            }
-            double rz = 0.0;
-#pragma unroll
-            for (int c = 0; c < M; ++c) { dd[c] += jwv * r[c]; rz += r[c] * zr[c]; }
-            const double gjw = lhat * rz;
-#pragma unroll
-            for (int c = 0; c < M; ++c) gRq[c] += lhat * jwv * zr[c];
-#pragma unroll
-            for (int j = 0; j < NS; ++j) {
-                const double gv = gjw * djw[j];
-#pragma unroll
-                for (int c = 0; c < M; ++c) {
-                    gtv(j, c) += gv * r[c];
-                    gRq[c] += gv * TV[j][c];
-                }
-            }
-        }
-#pragma unroll
-        for (int c = 0; c < M; ++c) gra(q, c) = gRq[c];
-    }
-    double glhat = 0.0;
-#pragma unroll
-    for (int c = 0; c < M; ++c) glhat += zr[c] * dd[c];
-
-    // rotated entropy variables -> primitive (rho, u, p) of stencil node j, handed
-    // to out(j, c, value)
-    auto to_prim = [&](int j) {
-        const NodeRHD<DIM> q = node(j);
-        double gt[M];              // read all of node j's sums before out() reuses the slots
-#pragma unroll
-        for (int c = 0; c < M; ++c) gt[c] = gtv(j, c);
-        const double ip = 1.0 / q.p, irho = 1.0 / q.rho;
-        double su = 0.0;
-#pragma unroll
-        for (int a = 0; a < DIM; ++a) {
-            double tu = 0.0;
-#pragma unroll
-            for (int b = 0; b < DIM; ++b) tu += T[a][b] * q.u[b];
-            su += gt[1 + a] * tu;
-        }
-        const double sbu = q.beta * su;
-        double res[M];
-        res[0] = gt[0] * ((1.0 + c1) * irho + ip) + su * ip - gt[M - 1] * q.W * ip;
-        res[M - 1] = -gt[0] * (c1 + q.beta) * ip - sbu * ip + gt[M - 1] * q.beta * q.W * ip;
-#pragma unroll
-        for (int b = 0; b < DIM; ++b) {
-            double s = 0.0;
-#pragma unroll
-            for (int a = 0; a < DIM; ++a) s += T[a][b] * gt[1 + a];
-            res[1 + b] = q.beta * s - gt[M - 1] * q.beta * q.u[b] / q.W;
-        }
-#pragma unroll
-        for (int c = 0; c < M; ++c) out(j, c, res[c]);
-    };
-    // the outer stencil nodes are complete before the eigen-structure tangents
-    sync();
-#pragma unroll
-    for (int j = 0; j < NS; ++j)
-        if (j != CI && j != CI + 1) to_prim(j);
-
-    // face eigen-structure: one backward sweep from the column and lambda^
-    // cotangents to the face entropy variables, which reach nodes i and i+1
-    // through the face mean
-    double Vb[M], gVb[M];
-#pragma unroll
-    for (int c = 0; c < M; ++c) Vb[c] = 0.5 * (TV[CI][c] + TV[CI + 1][c]);
-    face_eigen_vjp<DIM>(G, Vb, at, L, gra, glhat, gVb);
-#pragma unroll
-    for (int c = 0; c < M; ++c) {
-        gtv(CI, c) += 0.5 * gVb[c];
-        gtv(CI + 1, c) += 0.5 * gVb[c];
-    }
-    sync();
-    to_prim(CI);
-    to_prim(CI + 1);
-}
-
 // ---------------------------------------------------------------------------
 // residual VJP: one wavefront per segment of padded positions along a line
 // ---------------------------------------------------------------------------
 constexpr int ASEG = 54;                  // output positions per segment
 constexpr int AHALO = 5;                  // state halo each side
 constexpr int ALOAD = ASEG + 2 * AHALO;   // 64 loaded slots
-constexpr int ALINES = 2;                 // segments per block
+constexpr int ALINES = 4;                 // segments per block
 
-template <int DIM>
+// A line's staged nodes: the quantities of the pair sweep, the metrics, the residual
+// cotangent and (with dissipation) the entropy variables.  The output passes through the
+// first rows.
+template <int DIM, bool ES>
 struct AdjLDS {
-    static constexpr int NU = DIM, M = DIM + 2, NA = DIM + 1, NF = 6 + NU + NA;
-    double sd[ALINES][NF][ALOAD];
-    double lam[ALINES][M][ALOAD];
-    double buf[ALINES][6][M][64];
-    double gr[ALINES][M][M][64];     // cotangents of the face eigenvector columns
+    static constexpr int M = DIM + 2;
+    enum { RHO, BETA, LR, LB, W, U, A = U + DIM, LAM = A + DIM + 1, V = LAM + M, NF = V + (ES ? M : 0) };
+    double f[ALINES][NF][ALOAD];
 };
 
 struct AdjPlan {
@@ -306,205 +59,337 @@ struct AdjPlan {
     long long nlines[3];
 };
 
+// Frame of a face from its two nodes' metrics (A(side, c), side 0 or 1): the rotation T of the
+// mean normal, a_t, the length of the normal, and the face's mean entropy variables Vb in
+// the frame.
+template <int DIM, typename VFn, typename AFn>
+__device__ __forceinline__ void face_frame_rhd(VFn&& V, AFn&& A, double T[3][3], double& at, double& L, double* Vb) {
+    constexpr int M = DIM + 2;
+    at = 0.5 * (A(0, 0) + A(1, 0));
+    double ax[3] = {0.0, 0.0, 0.0}, L2 = 0.0;
+#pragma unroll
+    for (int j = 0; j < DIM; ++j) {
+        ax[j] = 0.5 * (A(0, 1 + j) + A(1, 1 + j));
+        L2 += ax[j] * ax[j];
+    }
+    const double iL = frsqrt(L2);
+    L = L2 * iL;
+    const double nrm[3] = {ax[0] * iL, ax[1] * iL, ax[2] * iL};
+    rotation<DIM>(nrm, T);
+    double Vm[M];
+#pragma unroll
+    for (int c = 0; c < M; ++c) Vm[c] = 0.5 * (V(0, c) + V(1, c));
+    Vb[0] = Vm[0];
+    Vb[M - 1] = Vm[M - 1];
+#pragma unroll
+    for (int a = 0; a < DIM; ++a) {
+        Vb[1 + a] = 0.0;
+#pragma unroll
+        for (int b = 0; b < DIM; ++b) Vb[1 + a] += T[a][b] * Vm[1 + b];
+    }
+}
+
+// Face dissipation: the cotangents gw[j] of the entropy variables of the stencil nodes j =
+// 0 .. 2P-1 (read by V(j, c)) for the cotangent z of d (read by Z(c)) (face_diss_rhd_fn).  The
+// columns are formed one at a time; each one's cotangent goes at once into the few scalars
+// of the face state that the columns are made of (es_eigen_vjp.h), which one backward sweep
+// takes to the face's entropy variables, the mean of the two middle nodes'.  V, A and Z are
+// read again where they are used (fences) instead of being held.
+template <int DIM, int P, typename VFn, typename AFn, typename ZFn>
+__device__ __forceinline__ void face_vjp_rhd(double G, double c0, double c1, double eps, VFn&& V, AFn&& A, ZFn&& Z,
+                                             double gw[2 * P][DIM + 2]) {
+    constexpr int M = DIM + 2, NS = 2 * P, CI = P - 1;
+    auto Vc = [&](int side, int c) { return V(CI + side, c); };
+    double T[3][3], v[3] = {0.0, 0.0, 0.0}, ytv = 0.0;
+    double Vb[M], at, L;
+    face_frame_rhd<DIM>(Vc, A, T, at, L, Vb);
+    ytv = RealTraits<double>::ytol * (fmax(fabs(Vc(0, 0)), -Vc(0, M - 1)) + fmax(fabs(Vc(1, 0)), -Vc(1, M - 1)));
+    FaceCoef<double> k;
+    double lhat;
+    {
+        const double iVE = -frcp(Vb[M - 1]);
+        double vu2 = 0.0;
+#pragma unroll
+        for (int a = 0; a < DIM; ++a) {
+            v[a] = Vb[1 + a] * iVE;
+            vu2 += Vb[1 + a] * Vb[1 + a];
+        }
+        k = face_coefficients<DIM, double>(G, c0, c1, Vb[0], Vb[M - 1] * Vb[M - 1] - vu2, iVE, v[0], v[1], v[2]);
+        lhat = fmax(fabs(at + L * k.lam[0]), fmax(fabs(at + L * k.vn), fabs(at + L * k.lam[1])));
+    }
+    FaceCoefBar o;
+    double glhat = 0.0;
+    auto column = [&](auto qc) {
+        constexpr int Q = decltype(qc)::value;
+        double r[M], r1 = 0.0, rf[M];
+        face_column<DIM, Q>(k, v, r);
+#pragma unroll
+        for (int c = 0; c < M; ++c) r1 += fabs(r[c]);
+        rf[0] = r[0];
+        rf[M - 1] = r[M - 1];
+#pragma unroll
+        for (int b = 0; b < DIM; ++b) {
+            rf[1 + b] = 0.0;
+#pragma unroll
+            for (int a = 0; a < DIM; ++a) rf[1 + b] += T[a][b] * r[1 + a];
+        }
+        // (the stencil read again for each column, not held through them)
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        double vt[NS], dj[NS], rz = 0.0;
+#pragma unroll
+        for (int j = 0; j < NS; ++j) {
+            vt[j] = 0.0;
+#pragma unroll
+            for (int c = 0; c < M; ++c) vt[j] = fma(rf[c], V(j, c), vt[j]);
+        }
+#pragma unroll
+        for (int c = 0; c < M; ++c) rz = fma(rf[c], Z(c), rz);
+        // the jump and its switch as in the forward dissipation
+        double jw = weno_jump_grad<P>(vt, eps, dj);
+        const double jp = vt[CI + 1] - vt[CI];
+        const bool on = jw * jp > 0.0 && fabs(jp) > ytv * r1;
+        jw = on ? jw : 0.0;
+        const double gj = on ? lhat * rz : 0.0;
+        glhat = fma(jw, rz, glhat);
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        double gc[M], gr[M];
+#pragma unroll
+        for (int c = 0; c < M; ++c) gc[c] = lhat * jw * Z(c);
+#pragma unroll
+        for (int j = 0; j < NS; ++j) {
+            const double gv = gj * dj[j];
+#pragma unroll
+            for (int c = 0; c < M; ++c) {
+                gc[c] = fma(gv, V(j, c), gc[c]);
+                gw[j][c] = fma(gv, rf[c], gw[j][c]);
+            }
+        }
+        gr[0] = gc[0];
+        gr[M - 1] = gc[M - 1];
+#pragma unroll
+        for (int a = 0; a < DIM; ++a) {
+            gr[1 + a] = 0.0;
+#pragma unroll
+            for (int b = 0; b < DIM; ++b) gr[1 + a] += T[a][b] * gc[1 + b];
+        }
+        face_column_vjp<DIM, Q>(k, v, gr, o);
+        // one column at a time
+#pragma unroll
+        for (int j = 0; j < NS; ++j)
+#pragma unroll
+            for (int c = 0; c < M; ++c) form_here(gw[j][c]);
+        double* b = &o.f[0];
+#pragma unroll
+        for (int c = 0; c < (int)(sizeof(FaceCoefBar) / sizeof(double)); ++c) form_here(b[c]);
+        form_here(glhat);
+    };
+    column(std::integral_constant<int, 0>{});
+    column(std::integral_constant<int, 1>{});
+    column(std::integral_constant<int, 2>{});
+    column(std::integral_constant<int, 3>{});
+    if constexpr (DIM == 3) column(std::integral_constant<int, 4>{});
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    face_frame_rhd<DIM>(Vc, A, T, at, L, Vb);
+    double gVb[M];
+    face_coefficients_vjp<DIM>(G, c0, c1, Vb, at, L, o, glhat, gVb);
+#pragma unroll
+    for (int b = 0; b < DIM; ++b) {
+        double s = 0.0;
+#pragma unroll
+        for (int a = 0; a < DIM; ++a) s += T[a][b] * gVb[1 + a];
+        gw[CI][1 + b] += 0.5 * s;
+        gw[CI + 1][1 + b] += 0.5 * s;
+    }
+    gw[CI][0] += 0.5 * gVb[0];
+    gw[CI + 1][0] += 0.5 * gVb[0];
+    gw[CI][M - 1] += 0.5 * gVb[M - 1];
+    gw[CI + 1][M - 1] += 0.5 * gVb[M - 1];
+}
+
+// Bound by FP64 issue at two wavefronts per SIMD (250 registers in 3D: the 30 sums of gw and 16 of the
+// face scalars besides the column at hand): 160 us at 72x64x56, where the
+// Gram-Schmidt sequence's backward sweep, cotangents kept in LDS and pairs with their own
+// logarithms took 483 (whole adjoint 2.36 -> 1.38 ms; 96^3 6.84 -> 3.54 ms).
+//
+// Reverse of the residual along DIR for one segment: lane q of a wavefront takes position
+// w ASEG - AHALO + q of its sequence as a node, as the left node of its pairs and as face
+// q + 1/2.  What belongs to a right node or to another lane's stencil moves by lane
+// shuffles; the node quantities are taken back to the primitive state once per node.  The
+// lines of a block along y and z are neighbours in x and are loaded and stored together
+// (32 bytes a row).
+//
+// Segment w of a sequence (the lines dealt to ALINES sequences, es_seq.h) outputs ASEG
+// consecutive positions.  Flat layout: the padded node sequences (n + 2 NG nodes per line)
+// laid end to end, a pair or face across two lines joining ghost nodes of both, whose
+// residual cotangents are zero, so that it contributes nothing; aligned: ceil((n + 2 NG) /
+// ASEG) segments per line.  A segment past the sweep's last one runs with no active lane
+// (the block synchronises).
 template <int DIM, int DIR, bool ES, int PO>
 __device__ __forceinline__ void residual_vjp_segment(const GridDev& g, double G, double eps,
                                                      const double* __restrict__ prim,
                                                      const double* __restrict__ met,
                                                      const double* __restrict__ lam,
                                                      double* __restrict__ gout, int blk, int nseg,
-                                                     long long nlines, bool flat, int nsl, AdjLDS<DIM>& lds) {
-    constexpr int NU = DIM, M = DIM + 2, NA = DIM + 1;
-    constexpr int F_RHO = 0, F_P = 1, F_BETA = 2, F_W = 3, F_LR = 4, F_LB = 5, F_U = 6, F_A = 6 + NU;
-    auto& sd = lds.sd;
-    auto& sl = lds.lam;
-    auto& buf = lds.buf;
+                                                     long long nlines, bool flat, int nsl, AdjLDS<DIM, ES>& lds) {
+    using L = AdjLDS<DIM, ES>;
+    constexpr int NU = DIM, M = DIM + 2, NA = DIM + 1, NQ = NU + 3;
     const int lane = threadIdx.x & 63;
-    const int line = threadIdx.x >> 6;
-    // segment w of sequence `line` (the lines dealt to ALINES sequences, es_seq.h)
-    // outputs ASEG consecutive positions.  Flat layout: the padded node sequences
-    // (n + 2 NG nodes per line) laid end to end, a pair or face across two lines
-    // joining ghost nodes of both, whose residual cotangents are zero, so that it
-    // contributes nothing; aligned: ceil((n + 2 NG) / ASEG) segments per line.  A
-    // segment past the sweep's last one runs with no active lane (the block
-    // synchronises).
+    const int line = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int cl = DIR == 0 ? line : (int)threadIdx.x % ALINES, cq = DIR == 0 ? lane : (int)threadIdx.x / ALINES;
     const long long w = blk;
     const int n = g.n[DIR];
     const int PL = n + 2 * NG;
-    const long long pstride = DIR == 0 ? 1 : (DIR == 1 ? (long long)g.P[0] : (long long)g.P[0] * g.P[1]);
-    const long long istride = DIR == 0 ? 1 : (DIR == 1 ? (long long)g.n[0] : (long long)g.n[0] * g.n[1]);
     const long long P = g.pnodes, N = g.nodes;
     const double idxi = 1.0 / g.dxi[DIR];
-    // line (nlines if none) and padded coordinate s of sequence position
-    // w ASEG - AHALO + q, and the padded / interior index of the line's node 0
-    const int nf = DIR == 0 ? g.n[1] : g.n[0];
-    const SeqBase sb = flat ? seq_base(w * ASEG - AHALO, PL, NG, nf, ALINES, line)
-                            : seq_base_aligned(w, nsl, ASEG, AHALO, NG, nf, ALINES, line);
-    auto locate = [&](int q, long long& lid, int& s, long long& pbase, long long& ibase) {
+    const double c0 = G / (G - 1.0), c1 = 1.0 / (G - 1.0);
+    // this thread's position of sequence cl: its line (on) and along-coordinate sm, in memory
+    int sm;
+    bool on;
+    long long pat, iat;
+    {
+        const int nf = DIR == 0 ? g.n[1] : g.n[0];
+        const SeqBase sb = flat ? seq_base(w * ASEG - AHALO, PL, NG, nf, ALINES, cl)
+                                : seq_base_aligned(w, nsl, ASEG, AHALO, NG, nf, ALINES, cl);
+        long long lid;
         int fa, fb;
-        seq_at(sb, q, flat, PL, NG, nf, ALINES, line, lid, s, fa, fb);
-        if (w >= nseg || lid < 0 || s < -NG || s >= n + NG) lid = nlines;
+        seq_at(sb, cq, flat, PL, NG, nf, ALINES, cl, lid, sm, fa, fb);
+        on = w < nseg && lid >= 0 && lid < nlines && sm >= -NG && sm < n + NG;
         const int ci = DIR == 0 ? 0 : fa, cj = DIR == 0 ? fa : (DIR == 1 ? 0 : fb), ck = DIR == 2 ? 0 : fb;
-        pbase = pidx(g, ci, cj, ck);
-        ibase = iidx(g, ci, cj, ck);
-    };
-    const bool active = w < nseg;
-
-    // ---- states (positions w ASEG - 5 .. w ASEG + 58) and residual cotangents
-    {
-        long long lid, pbase, ibase;
-        int s;
-        locate(lane, lid, s, pbase, ibase);
-        double rho = 1.0, p = 1.0, lr = 0.0, lb = 0.0, u[NU], a[NA];
-#pragma unroll
-        for (int c = 0; c < NU; ++c) u[c] = 0.0;
-#pragma unroll
-        for (int c = 0; c < NA; ++c) a[c] = c == 1 ? 1.0 : 0.0;
-        if (lid < nlines) {
-            const long long idx = pbase + (long long)s * pstride;
-            rho = prim[idx];
-#pragma unroll
-            for (int c = 0; c < NU; ++c) u[c] = prim[(1 + c) * P + idx];
-            p = prim[(M - 1) * P + idx];
-            lr = prim[M * P + idx];
-            lb = prim[(M + 1) * P + idx];
-#pragma unroll
-            for (int c = 0; c < NA; ++c) a[c] = met[(DIR * NA + c) * P + idx];
-        }
-        double uu = 0.0;
-#pragma unroll
-        for (int c = 0; c < NU; ++c) uu += u[c] * u[c];
-        sd[line][F_RHO][lane] = rho;
-        sd[line][F_P][lane] = p;
-        sd[line][F_BETA][lane] = rho / p;
-        sd[line][F_W][lane] = sqrt(1.0 + uu);
-        sd[line][F_LR][lane] = lr;
-        sd[line][F_LB][lane] = lb;
-#pragma unroll
-        for (int c = 0; c < NU; ++c) sd[line][F_U + c][lane] = u[c];
-#pragma unroll
-        for (int c = 0; c < NA; ++c) sd[line][F_A + c][lane] = a[c];
-        const bool in = lid < nlines && s >= 0 && s < n;
-#pragma unroll
-        for (int c = 0; c < M; ++c) sl[line][c][lane] = in ? lam[c * N + ibase + (long long)s * istride] : 0.0;
+        pat = pidx(g, ci, cj, ck) + sm * (DIR == 0 ? 1LL : (DIR == 1 ? (long long)g.P[0] : (long long)g.P[0] * g.P[1]));
+        iat = iidx(g, ci, cj, ck) + sm * (DIR == 0 ? 1LL : (DIR == 1 ? (long long)g.n[0] : (long long)g.n[0] * g.n[1]));
     }
-    __syncthreads();
-
-    auto prim_at = [&](int q, double* Pq) {
-        Pq[0] = sd[line][F_RHO][q];
-#pragma unroll
-        for (int c = 0; c < NU; ++c) Pq[1 + c] = sd[line][F_U + c][q];
-        Pq[M - 1] = sd[line][F_P][q];
-    };
-    auto node_at = [&](int q) {
-        NodeRHD<NU> nd;
-        nd.rho = sd[line][F_RHO][q];
-        nd.p = sd[line][F_P][q];
-        nd.beta = sd[line][F_BETA][q];
-        nd.W = sd[line][F_W][q];
-        nd.lr = sd[line][F_LR][q];
-        nd.lb = sd[line][F_LB][q];
-#pragma unroll
-        for (int c = 0; c < NU; ++c) nd.u[c] = sd[line][F_U + c][q];
-        return nd;
-    };
-
-    // ---- pairs (s', s'+n), s' = w ASEG - 3 + lane, slot of s' = lane + 2
-    const int o = lane;                            // output lane: position w ASEG + o
-    double acc[M];
-#pragma unroll
-    for (int c = 0; c < M; ++c) acc[c] = 0.0;
     {
-        const int ql = lane + 2;
-        double Pl[M], al[NA];
-        if (lane < ASEG + 3) {
-            prim_at(ql, Pl);
+        // states, metrics and cotangents (a position off the lines: a state at rest)
+        const bool in = on && sm >= 0 && sm < n;
+        const long long ip = on ? pat : 0, ii = in ? iat : 0;
+        double v[M + 2], a[NA], lm[M];
 #pragma unroll
-            for (int c = 0; c < NA; ++c) al[c] = sd[line][F_A + c][ql];
+        for (int c = 0; c < M + 2; ++c) v[c] = prim[c * P + ip];
+#pragma unroll
+        for (int c = 0; c < NA; ++c) a[c] = met[(DIR * NA + c) * P + ip];
+#pragma unroll
+        for (int c = 0; c < M; ++c) lm[c] = lam[c * N + ii];
+#pragma unroll
+        for (int c = 0; c < M + 2; ++c) v[c] = on ? v[c] : (c == 0 || c == M - 1 ? 1.0 : 0.0);
+#pragma unroll
+        for (int c = 0; c < NA; ++c) a[c] = on ? a[c] : (c == 1 ? 1.0 : 0.0);
+        double uu = 1.0;
+#pragma unroll
+        for (int c = 0; c < NU; ++c) uu += v[1 + c] * v[1 + c];
+        const double W = psqrt(uu), beta = v[0] * frcp(v[M - 1]);
+        auto f = lds.f[cl];
+        f[L::RHO][cq] = v[0];
+        f[L::BETA][cq] = beta;
+        f[L::LR][cq] = v[M];
+        f[L::LB][cq] = v[M + 1];
+        f[L::W][cq] = W;
+#pragma unroll
+        for (int c = 0; c < NU; ++c) f[L::U + c][cq] = v[1 + c];
+#pragma unroll
+        for (int c = 0; c < NA; ++c) f[L::A + c][cq] = a[c];
+#pragma unroll
+        for (int c = 0; c < M; ++c) f[L::LAM + c][cq] = in ? lm[c] : 0.0;
+        if constexpr (ES) {
+            f[L::V][cq] = c0 + v[M] + v[M + 1] * c1 + beta;
+#pragma unroll
+            for (int c = 0; c < NU; ++c) f[L::V + 1 + c][cq] = beta * v[1 + c];
+            f[L::V + M - 1][cq] = -beta * W;
         }
+    }
+    if (DIR == 0) wave_lds_sync();
+    else __syncthreads();
+    auto f = lds.f[line];
+
+    // ---- entropy-variable cotangents of the stencil states from the faces
+    double gV[M];
+#pragma unroll
+    for (int c = 0; c < M; ++c) gV[c] = 0.0;
+    if constexpr (ES) {
+        // stencil node j of face lane + 1/2 at lane - CI + j
+        constexpr int NS = 2 * PO, CI = PO - 1;
+        double gw[NS][M];
+#pragma unroll
+        for (int j = 0; j < NS; ++j)
+#pragma unroll
+            for (int c = 0; c < M; ++c) gw[j][c] = 0.0;
+        if (lane >= 2 && lane <= 60) {
+            auto Z = [&](int c) { return 0.5 * idxi * (f[L::LAM + c][lane] - f[L::LAM + c][lane + 1]); };
+            bool any = false;
+#pragma unroll
+            for (int c = 0; c < M; ++c) any |= Z(c) != 0.0;
+            if (any)
+                face_vjp_rhd<DIM, PO>(
+                    G, c0, c1, eps, [&](int j, int c) { return f[L::V + c][lane - CI + j]; },
+                    [&](int side, int c) { return f[L::A + c][lane + side]; }, Z, gw);
+        }
+#pragma unroll
+        for (int j = 0; j < NS; ++j)
+#pragma unroll
+            for (int c = 0; c < M; ++c) gV[c] += __shfl(gw[j][c], lane + CI - j);
+    }
+
+    auto node = [&](int q) {
+        NodeQ<NU> x;
+        x.rho = f[L::RHO][q];
+        x.beta = f[L::BETA][q];
+        x.lr = f[L::LR][q];
+        x.lb = f[L::LB][q];
+        x.W = f[L::W][q];
+#pragma unroll
+        for (int k = 0; k < NU; ++k) x.u[k] = f[L::U + k][q];
+        return x;
+    };
+    const NodeQ<NU> x = node(lane);
+    double acc[NQ];
+    {
+        double gb = gV[0] * (c1 * frcp(x.beta) + 1.0) - gV[M - 1] * x.W;
+#pragma unroll
+        for (int k = 0; k < NU; ++k) {
+            gb += gV[1 + k] * x.u[k];
+            acc[3 + k] = gV[1 + k] * x.beta;
+        }
+        acc[0] = gV[0] * frcp(x.rho);
+        acc[1] = gb;
+        acc[2] = -gV[M - 1] * x.beta;
+    }
+
+    // ---- pairs (lane, lane + nn)
 #pragma unroll 1
-        for (int nn = 1; nn <= PO; ++nn) {
-            double gl[M], gr[M];
+    for (int nn = 1; nn <= PO; ++nn) {
+        double gl[NQ], gr[NQ], a[NA], ar[NA], wc[M];
 #pragma unroll
-            for (int c = 0; c < M; ++c) { gl[c] = 0.0; gr[c] = 0.0; }
-            if (active && lane < ASEG + 3) {
-                const int qr = ql + nn;
-                double w[M];
-                bool any = false;
-#pragma unroll
-                for (int c = 0; c < M; ++c) {
-                    w[c] = alpha_pn(PO, nn) * idxi * (sl[line][c][qr] - sl[line][c][ql]);
-                    any |= w[c] != 0.0;
-                }
-                if (any) {
-                    double Pr[M], ar[NA];
-                    prim_at(qr, Pr);
-#pragma unroll
-                    for (int c = 0; c < NA; ++c) ar[c] = sd[line][F_A + c][qr];
-                    pair_vjp_rhd<NU>(G, Pl, Pr, al, ar, w, gl, gr);
-                }
-            }
-#pragma unroll
-            for (int c = 0; c < M; ++c) {
-                buf[line][nn - 1][c][lane] = gl[c];
-                buf[line][3 + nn - 1][c][lane] = gr[c];
-            }
-        }
-    }
-    __syncthreads();
-    if (o < ASEG) {
-#pragma unroll
-        for (int nn = 1; nn <= PO; ++nn)
-#pragma unroll
-            for (int c = 0; c < M; ++c)
-                acc[c] += buf[line][nn - 1][c][o + 3] + buf[line][3 + nn - 1][c][o + 3 - nn];
-    }
-
-    if (ES) {
-        __syncthreads();
-        // ---- faces f = w ASEG - 3 + lane (stencil slots lane + 3 - PO .. lane + 2 + PO); the
-        // cotangents of the 2 PO stencil states go to buf[j][.][lane]
+        for (int c = 0; c < NQ; ++c) { gl[c] = 0.0; gr[c] = 0.0; }
+        const double wn = alpha_pn(PO, nn) * idxi;
+        const int qr = min(lane + nn, ALOAD - 1);
         bool any = false;
-        double z[M];
-        if (active && lane < ASEG + 5) {
 #pragma unroll
-            for (int c = 0; c < M; ++c) {
-                z[c] = 0.5 * idxi * (sl[line][c][lane + 2] - sl[line][c][lane + 3]);
-                any |= z[c] != 0.0;
-            }
+        for (int c = 0; c < NA; ++c) { a[c] = f[L::A + c][lane]; ar[c] = f[L::A + c][qr]; }
+#pragma unroll
+        for (int c = 0; c < M; ++c) {
+            wc[c] = wn * (f[L::LAM + c][qr] - f[L::LAM + c][lane]);
+            any |= wc[c] != 0.0;
         }
-        if (any) {
-            double al[NA], ar[NA];
+        if (any && lane >= 2 && lane + nn <= 61) pair_vjp_rhd_nodes<NU>(G, x, node(qr), a, ar, wc, gl, gr);
 #pragma unroll
-            for (int c = 0; c < NA; ++c) { al[c] = sd[line][F_A + c][lane + 2]; ar[c] = sd[line][F_A + c][lane + 3]; }
-            // the fence makes the later stages reread the stencil from LDS
-            face_vjp_rhd<DIM, PO>(G, eps, [&](int j) { return node_at(lane + 3 - PO + j); },
-                              [] { __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront"); }, al, ar, z,
-                              [&](int j, int c) -> double& { return buf[line][j][c][lane]; },
-                              [&](int q, int c) -> double& { return lds.gr[line][q][c][lane]; },
-                              [&](int j, int c, double v) { buf[line][j][c][lane] = v; });
-        } else {
-#pragma unroll
-            for (int j = 0; j < 2 * PO; ++j)
-#pragma unroll
-                for (int c = 0; c < M; ++c) buf[line][j][c][lane] = 0.0;
-        }
-        __syncthreads();
-        if (o < ASEG) {
-#pragma unroll
-            for (int j = 0; j < 2 * PO; ++j)
-#pragma unroll
-                for (int c = 0; c < M; ++c) acc[c] += buf[line][j][c][o + 2 + PO - j];
-        }
+        for (int c = 0; c < NQ; ++c) acc[c] += gl[c] + __shfl(gr[c], lane - nn);
     }
-
-    long long lid_out, pbase_out, ibase_out;
-    int s_out;
-    locate(AHALO + o, lid_out, s_out, pbase_out, ibase_out);
-    (void)ibase_out;
-    if (o < ASEG && lid_out < nlines) {
-        const long long idx = pbase_out + (long long)s_out * pstride;
+    double gP[M];
+    node_vjp_rhd<NU>(x, acc, gP);
+    const bool out = on && cq >= AHALO && cq < AHALO + ASEG;
+    if (DIR == 0) {
+        if (out) {
 #pragma unroll
-        for (int c = 0; c < M; ++c) gout[c * P + idx] = acc[c];
+            for (int c = 0; c < M; ++c) gout[c * P + pat] = gP[c];
+        }
+    } else {
+        wave_lds_sync();
+#pragma unroll
+        for (int c = 0; c < M; ++c) f[c][lane] = gP[c];
+        __syncthreads();
+        if (out) {
+#pragma unroll
+            for (int c = 0; c < M; ++c) gout[c * P + pat] = lds.f[cl][c][cq];
+        }
     }
 }
 
@@ -512,13 +397,13 @@ __device__ __forceinline__ void residual_vjp_segment(const GridDev& g, double G,
 // per direction; only positions along lines through interior transverse
 // coordinates are written.
 template <int DIM, bool ES, int PO>
-__global__ void __launch_bounds__(128) k_residual_vjp(GridDev g, double G, double eps,
+__global__ void __launch_bounds__(64 * ALINES) __attribute__((amdgpu_waves_per_eu(2))) k_residual_vjp(GridDev g, double G, double eps,
                                                       const double* __restrict__ prim,
                                                       const double* __restrict__ met,
                                                       const double* __restrict__ lam,
                                                       double* __restrict__ gdir, AdjPlan pl) {
     constexpr int M = DIM + 2;
-    __shared__ AdjLDS<DIM> lds;
+    __shared__ AdjLDS<DIM, ES> lds;
     const long long slab = (long long)M * g.pnodes;
     int b = xcd_block((int)blockIdx.x, (int)gridDim.x);
     if (b < pl.nblk[0]) {

@@ -21,7 +21,7 @@ __device__ __forceinline__ double log_mean_d(double al, double ar, double lnal, 
     const double s = al + ar;
     const double dif = al - ar;
     if (dif * dif < 1e-2 * (s * s)) {
-        const double is = 1.0 / s;
+        const double is = frcp(s);
         const double f = dif * is;
         const double u = f * f;
         double F = 1.0 / 15.0, dF = 0.0;
@@ -31,124 +31,109 @@ __device__ __forceinline__ double log_mean_d(double al, double ar, double lnal, 
             dF = fma(dF, u, F);
             F = fma(F, u, c[k]);
         }
-        const double iF = 1.0 / F;
+        const double iF = frcp(F);
         const double q = -2.0 * f * dF * iF * iF * is;
         dl = 0.5 * iF + q * ar;
         dr = 0.5 * iF - q * al;
         return 0.5 * s * iF;
     }
-    const double iD = 1.0 / (lnal - lnar);
+    const double iD = frcp(lnal - lnar);
     const double L = dif * iD;
-    dl = (1.0 - L / al) * iD;
-    dr = (L / ar - 1.0) * iD;
+    dl = (1.0 - fdiv(L, al)) * iD;
+    dr = (fdiv(L, ar) - 1.0) * iD;
     return L;
+}
+
+// Node values of the sweep, and the order of a node's cotangents: rho, beta, W, u.
+template <int NU>
+struct NodeQ {
+    double rho, beta, lr, lb, W, u[NU];
+};
+
+// Cotangents gl, gr (rho, beta, W, u_1..u_NU) of the node quantities of l and r from w of
+// F.  With the means of the node quantities, un = a_j u_j and q = a_t W + un the flux is
+//   F = (rho^ln q, u_k X + a_k rho/beta, W X - a_t rho/beta),
+//   X = q (a_0 rho^ln + rho/beta)/(W^2 - |u|^2).
+template <int NU>
+__device__ __forceinline__ void pair_vjp_rhd_nodes(double G, const NodeQ<NU>& l, const NodeQ<NU>& r, const double* al,
+                                                   const double* ar, const double* w, double* gl, double* gr) {
+    constexpr int M = NU + 2;
+    double drl[2], dbl[2];
+    const double rln = log_mean_d(l.rho, r.rho, l.lr, r.lr, drl[0], drl[1]);
+    const double bln = log_mean_d(l.beta, r.beta, l.lb, r.lb, dbl[0], dbl[1]);
+    const double W = 0.5 * (l.W + r.W), beta = 0.5 * (l.beta + r.beta), at = 0.5 * (al[0] + ar[0]);
+    double a[NU], u[NU], uu = 0.0, un = 0.0, wu = 0.0, aw = 0.0;
+#pragma unroll
+    for (int k = 0; k < NU; ++k) {
+        a[k] = 0.5 * (al[1 + k] + ar[1 + k]);
+        u[k] = 0.5 * (l.u[k] + r.u[k]);
+        uu += u[k] * u[k];
+        un += a[k] * u[k];
+        wu += w[1 + k] * u[k];
+        aw += w[1 + k] * a[k];
+    }
+    double ib, ibl;
+    frcp2((G - 1.0) * bln, beta, ibl, ib);
+    const double iden = frcp(W * W - uu), pb = 0.5 * (l.rho + r.rho) * ib, a0 = 1.0 + ibl, q = at * W + un;
+    const double A = a0 * rln + pb, X = A * iden * q;
+    // backwards
+    const double gX = wu + w[M - 1] * W, gXi = gX * iden, gA = gXi * q;
+    const double gq = gXi * A + w[0] * rln, gln = w[0] * q + gA * a0, t = gXi * X;
+    const double gpb = aw - w[M - 1] * at + gA;
+    const double g_W = 0.5 * (w[M - 1] * X + at * gq) - W * t;
+    const double g_r = 0.5 * (gpb * ib), g_b = -g_r * pb, g_bln = -gA * rln * (ibl * ibl * (G - 1.0));
+    gl[0] = g_r + gln * drl[0];
+    gr[0] = g_r + gln * drl[1];
+    gl[1] = g_b + g_bln * dbl[0];
+    gr[1] = g_b + g_bln * dbl[1];
+    gl[2] = gr[2] = g_W;
+#pragma unroll
+    for (int k = 0; k < NU; ++k) gl[3 + k] = gr[3 + k] = 0.5 * (w[1 + k] * X + a[k] * gq) + u[k] * t;
+}
+
+// The cotangent gP of the primitive state (rho, u, p) from q = (rho, beta, W, u) of the node
+// quantities.
+template <int NU>
+__device__ __forceinline__ void node_vjp_rhd(const NodeQ<NU>& x, const double* q, double* gP) {
+    const double iW = frcp(x.W), ip = x.beta * frcp(x.rho);
+    gP[0] = q[0] + q[1] * ip;
+#pragma unroll
+    for (int k = 0; k < NU; ++k) gP[1 + k] = q[3 + k] + q[2] * iW * x.u[k];
+    gP[NU + 1] = -q[1] * x.beta * ip;
 }
 
 // gl = (dF/dP_l)^T w, gr = (dF/dP_r)^T w for the pair flux of pair_flux_rhd.
 template <int NU>
 __device__ __forceinline__ void pair_vjp_rhd(double G, const double* Pl, const double* Pr, const double* al,
                                              const double* ar, const double* w, double* gl, double* gr) {
-    constexpr int M = NU + 2;
-    const double* Pq[2] = {Pl, Pr};
-    double rho[2], p[2], u[2][NU], W[2], beta[2], lr[2], lb[2];
+    const double* P[2] = {Pl, Pr};
+    NodeQ<NU> x[2];
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
-        rho[t] = Pq[t][0];
-        p[t] = Pq[t][M - 1];
-        double uu = 0.0;
+        double uu = 1.0;
 #pragma unroll
-        for (int k = 0; k < NU; ++k) { u[t][k] = Pq[t][1 + k]; uu += u[t][k] * u[t][k]; }
-        W[t] = sqrt(1.0 + uu);
-        beta[t] = rho[t] / p[t];
-        lr[t] = log(rho[t]);
-        lb[t] = log(beta[t]);
+        for (int k = 0; k < NU; ++k) {
+            x[t].u[k] = P[t][1 + k];
+            uu += x[t].u[k] * x[t].u[k];
+        }
+        x[t].rho = P[t][0];
+        x[t].beta = fdiv(P[t][0], P[t][NU + 1]);
+        x[t].W = psqrt(uu);
+        x[t].lr = xlog(x[t].rho);
+        x[t].lb = xlog(x[t].beta);
     }
-    // forward values
-    double drl[2], dbl[2];
-    const double rho_ln = log_mean_d(rho[0], rho[1], lr[0], lr[1], drl[0], drl[1]);
-    const double beta_ln = log_mean_d(beta[0], beta[1], lb[0], lb[1], dbl[0], dbl[1]);
-    const double rho_m = 0.5 * (rho[0] + rho[1]);
-    const double beta_m = 0.5 * (beta[0] + beta[1]);
-    const double W_m = 0.5 * (W[0] + W[1]);
-    const double at = 0.5 * (al[0] + ar[0]);
-    double um[NU], ab[NU];
-    double uu = 0.0, un = 0.0;
-#pragma unroll
-    for (int k = 0; k < NU; ++k) {
-        um[k] = 0.5 * (u[0][k] + u[1][k]);
-        ab[k] = 0.5 * (al[1 + k] + ar[1 + k]);
-        uu += um[k] * um[k];
-        un += ab[k] * um[k];
-    }
-    const double ibg = 1.0 / ((G - 1.0) * beta_ln);
-    const double a0 = 1.0 + ibg;
-    const double iden = 1.0 / (W_m * W_m - uu);
-    const double ibm = 1.0 / beta_m;
-    const double pb = rho_m * ibm;
-    const double U1 = rho_ln * W_m;
-    const double B = a0 * U1 * W_m + pb * uu;
-    const double U5 = B * iden;
-    const double A = a0 * rho_ln + pb;
-    const double C = W_m * A * iden;
-    const double iW = 1.0 / W_m;
-    const double s = (at * (U5 + pb) + C * un) * iW;
-    // backward sweep
-    double g_s = 0.0, g_pb = 0.0, g_um[NU];
-#pragma unroll
-    for (int k = 0; k < NU; ++k) {
-        g_s += w[1 + k] * um[k];
-        g_um[k] = w[1 + k] * s;
-        g_pb += w[1 + k] * ab[k];
-    }
-    double g_U5 = w[M - 1] * at, g_C = w[M - 1] * un, g_un = w[M - 1] * C;
-    const double g_X = g_s * iW;
-    double g_Wm = -g_s * s * iW;
-    g_U5 += g_X * at;
-    g_pb += g_X * at;
-    g_C += g_X * un;
-    g_un += g_X * C;
-    double g_rln = w[0] * (at * W_m + un);
-    g_Wm += w[0] * rho_ln * at;
-    g_un += w[0] * rho_ln;
-    g_Wm += g_C * A * iden;
-    const double g_A = g_C * W_m * iden;
-    double g_iden = g_C * W_m * A;
-    double g_a0 = g_A * rho_ln;
-    g_rln += g_A * a0;
-    g_pb += g_A;
-    const double g_B = g_U5 * iden;
-    g_iden += g_U5 * B;
-    g_a0 += g_B * U1 * W_m;
-    const double g_U1 = g_B * a0 * W_m;
-    g_Wm += g_B * a0 * U1;
-    g_pb += g_B * uu;
-    double g_uu = g_B * pb;
-    g_rln += g_U1 * W_m;
-    g_Wm += g_U1 * rho_ln;
-    const double g_rm = g_pb * ibm;
-    const double g_bm = -g_pb * pb * ibm;
-    g_Wm += -2.0 * W_m * iden * iden * g_iden;
-    g_uu += iden * iden * g_iden;
-    const double g_bln = -g_a0 * ibg / beta_ln;
-#pragma unroll
-    for (int k = 0; k < NU; ++k) g_um[k] += 2.0 * um[k] * g_uu + ab[k] * g_un;
-    double* gq[2] = {gl, gr};
-#pragma unroll
-    for (int t = 0; t < 2; ++t) {
-        const double g_beta = 0.5 * g_bm + g_bln * dbl[t];
-        const double g_W = 0.5 * g_Wm;
-        const double iWt = 1.0 / W[t];
-        gq[t][0] = 0.5 * g_rm + g_rln * drl[t] + g_beta / p[t];
-#pragma unroll
-        for (int k = 0; k < NU; ++k) gq[t][1 + k] = 0.5 * g_um[k] + g_W * u[t][k] * iWt;
-        gq[t][M - 1] = -g_beta * beta[t] / p[t];
-    }
+    double ql[NU + 3], qr[NU + 3];
+    pair_vjp_rhd_nodes<NU>(G, x[0], x[1], al, ar, w, ql, qr);
+    node_vjp_rhd<NU>(x[0], ql, gl);
+    node_vjp_rhd<NU>(x[1], qr, gr);
 }
 
 // The WENO jump weno_jump<P>(v) (P = 2, 3) with its gradient g over the 2P values.  A side's
 // value is sum_k w_k q_k / (c sum_k w_k) in the differences of v, w_k ~ 1/e_k^2; with om_k =
 // w_k / sum w, its derivative is sum_k om_k dq_k / c + sum_k H_k de_k, H_k = -2 om_k (q_k -
-// sum om q) / (c e_k).  One reciprocal per side.
+// sum om q) / (c e_k).  The 1/e_k come from their product's reciprocal (e^3, and e^4 in the
+// common denominator of the weights, as in the forward value, stay in range for any eps
+// above 1e-77).
 template <int P>
 __device__ __forceinline__ double weno_jump_grad(const double* v, double eps, double* g) {
     static_assert(P == 2 || P == 3, "the adjoint's orders");
@@ -161,10 +146,10 @@ __device__ __forceinline__ double weno_jump_grad(const double* v, double eps, do
         if constexpr (P == 2) {
             const double e0 = fma(D[0], D[0], eps), e1 = fma(D[1], D[1], eps);
             const double w0 = e1 * e1, w1 = 2.0 * (e0 * e0), S = w0 + w1, E = e0 * e1;
-            const double r = frcp(S * E), iS = E * r, Sr = S * r;
+            const double iS = frcp(S), iE = frcp(E);
             const double m0 = w0 * iS, m1 = w1 * iS, q = fma(m0, D[0], m1 * D[1]);
-            gD[0] = m0 * fma(2.0 * (D[0] - q) * (Sr * e1), D[0], -0.5);
-            gD[1] = m1 * fma(2.0 * (D[1] - q) * (Sr * e0), D[1], -0.5);
+            gD[0] = m0 * fma(2.0 * (D[0] - q) * (iE * e1), D[0], -0.5);
+            gD[1] = m1 * fma(2.0 * (D[1] - q) * (iE * e0), D[1], -0.5);
             return 0.5 * q;
         } else {
             const double t0 = D[1] - D[0], t1 = D[2] - D[1], t2 = D[3] - D[2];
@@ -176,11 +161,10 @@ __device__ __forceinline__ double weno_jump_grad(const double* v, double eps, do
             const double w0 = e12 * e12, w1 = 6.0 * (e02 * e02), w2 = 3.0 * (e01 * e01);
             const double q0 = fma(5.0, D[1], -2.0 * D[0]), q1 = fma(2.0, D[2], D[1]), q2 = fma(4.0, D[2], -D[3]);
             const double S = w0 + w1 + w2, E = e01 * e2;
-            const double r = (1.0 / 6.0) * frcp(S * E), iS = E * r, Sr = -2.0 * (S * r);
+            const double iS = (1.0 / 6.0) * frcp(S), iE = -2.0 * frcp(E);
             const double m0 = w0 * iS, m1 = w1 * iS, m2 = w2 * iS;      // om_k / 6
             const double v = fma(m0, q0, fma(m1, q1, m2 * q2)), v6 = 6.0 * v;
-            const double i6 = 6.0 * Sr;
-            const double H0 = m0 * (q0 - v6) * (i6 * e12), H1 = m1 * (q1 - v6) * (i6 * e02), H2 = m2 * (q2 - v6) * (i6 * e01);
+            const double H0 = m0 * (q0 - v6) * (iE * e12), H1 = m1 * (q1 - v6) * (iE * e02), H2 = m2 * (q2 - v6) * (iE * e01);
             const double x0 = H0 * (26.0 / 3.0) * t0, x1 = H1 * (26.0 / 3.0) * t1, x2 = H2 * (26.0 / 3.0) * t2;
             const double y0 = 2.0 * H0 * s0, y1 = 2.0 * H1 * s1, y2 = 2.0 * H2 * s2;
             gD[0] = fma(2.0, m0, x0 + y0);
@@ -197,7 +181,7 @@ __device__ __forceinline__ double weno_jump_grad(const double* v, double eps, do
     for (int k = 0; k < ND - 1; ++k) D[k] = d[k];
     j -= side(D, gD);
 #pragma unroll
-    for (int k = 0; k < ND - 1; ++k) { gd[k] += gD[k]; D[k] = d[ND - 1 - k]; }
+    for (int k = 0; k < ND - 1; ++k) { gd[k] += gD[k]; form_here(gd[k]); D[k] = d[ND - 1 - k]; }   // one side at a time
     j -= side(D, gD);
 #pragma unroll
     for (int k = 0; k < ND - 1; ++k) gd[ND - 1 - k] += gD[k];
