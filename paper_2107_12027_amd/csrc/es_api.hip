@@ -170,7 +170,6 @@ es_status es_create(const es_grid* grid, const es_scheme* scheme, const es_monit
     if (e == hipSuccess) e = alloc(&c->wb, N);
     if (e == hipSuccess) e = alloc(&c->xe, (size_t)g.enodes * d);
     if (e == hipSuccess) e = alloc(&c->ve, (size_t)g.enodes * d);
-    if (e == hipSuccess && grid->dim == 3) e = alloc(&c->pi, (size_t)g.enodes * 9);
     if (e == hipSuccess) e = alloc(&c->red, (size_t)c->red_blocks * (3 + 8));
     if (e == hipSuccess) e = alloc(&c->scal, (size_t)es::NSCAL);
     if (e == hipSuccess) e = alloc(&c->fail, (size_t)(es::FAIL_SLOTS * es::FAIL_STRIDE));
@@ -192,7 +191,7 @@ es_status es_create(const es_grid* grid, const es_scheme* scheme, const es_monit
 es_status es_destroy(es_ctx* c) {
     if (c == nullptr) return ES_EINVAL;
     void* bufs[] = {c->prim, c->met, c->met1, c->met2, c->L, c->Us, c->Js, c->Us2, c->Js2, c->xnew, c->xa, c->xb,
-                    c->wa, c->wb, c->xe, c->ve, c->pi, c->red, c->scal, c->fail,
+                    c->wa, c->wb, c->xe, c->ve, c->red, c->scal, c->fail,
                     c->adj_lamU, c->adj_lamJ, c->adj_lamL, c->adj_accU, c->adj_accJ,
                     c->adj_gU, c->adj_gJ, c->gdir, c->adj_eig};
     if (c->gexec != nullptr) (void)hipGraphExecDestroy(c->gexec);

@@ -32,8 +32,6 @@ struct es_ctx {
     double* wb;     // interior (monitor pong)
     double* xe;     // stage mesh on the extension box (d comps)
     double* ve;     // mesh velocity on the extension box (d comps)
-    double* pi;     // 3D: conservative-metric products on the extension box (9 comps; the
-                    // metrics with J^0)
     double* red;    // reduction partials
     double* scal;   // device scalars: [0] dt, [1] gmax, [2] dtau, [3..] spare
     unsigned long long* fail;   // FAIL_SLOTS failure records (es_common.h)

@@ -298,95 +298,12 @@ __global__ void __launch_bounds__(MTX * MSY) k_metrics2d_stages(GridDev g, const
 
 // 3D conservative metric method (eq. SCLCoeff): with the products
 //   Pi_{a,j} = delta_a[x_{j+1}] x_{j+2}   (indices mod 3)
-// on the extension box, J dxi_k/dx_j = (delta_{k+2}[Pi_{k+1,j}] - delta_{k+1}[Pi_{k+2,j}])
-// / (dxi_{k+1} dxi_{k+2}).  Pi_{a,.} is formed where the a-coordinate lies within
-// 3 layers of the interior (the metric differences never read it elsewhere).
-__global__ void k_cmm_products(GridDev g, const double* __restrict__ xe, double* __restrict__ pi) {
-    int i, j, k;
-    if (!plane_cell_xcd(g.E[0], g.E[1], i, j, k)) return;
-    i -= 2 * g.ng; j -= 2 * g.ng; k -= 2 * g.ng;
-    const long long e = eidx(g, i, j, k);
-    const long long EN = g.enodes;
-    const int c[3] = {i, j, k};
-    const long long st[3] = {1, (long long)g.E[0], (long long)g.E[0] * g.E[1]};
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-        const bool valid = c[a] >= -g.ng && c[a] < g.n[a] + g.ng;
-#pragma unroll
-        for (int jj = 0; jj < 3; ++jj) {
-            const int j1 = (jj + 1) % 3, j2 = (jj + 2) % 3;
-            double v = 0.0;
-            if (valid) {
-                const double* xc = xe + j1 * EN + e;
-                double d = 0.0;
-#pragma unroll
-                for (int n = 1; n <= NG_MAX; ++n)
-                    if (n <= g.p) d += 0.5 * alpha_pn(g.p, n) * (xc[n * st[a]] - xc[-n * st[a]]);
-                v = d * xe[j2 * EN + e];
-            }
-            pi[(a * 3 + jj) * EN + e] = v;
-        }
-    }
-}
-
-__global__ void k_metrics3d(GridDev g, const double* __restrict__ xe, const double* __restrict__ ve,
-                            const double* __restrict__ pi, double* __restrict__ met,
-                            double* __restrict__ J0) {
-    int i, j, k;
-    if (!box_ijk_xcd(-g.ng, -g.ng, -g.ng, g.P[0], g.P[1], i, j, k)) return;
-    const long long t = pidx(g, i, j, k);
-    const long long e = eidx(g, i, j, k);
-    const long long EN = g.enodes;
-    const long long P = g.pnodes;
-    const long long st[3] = {1, (long long)g.E[0], (long long)g.E[0] * g.E[1]};
-    double m[3][3];
-#pragma unroll
-    for (int kk = 0; kk < 3; ++kk) {
-        const int k1 = (kk + 1) % 3, k2 = (kk + 2) % 3;
-#pragma unroll
-        for (int jj = 0; jj < 3; ++jj) {
-            const double* pa = pi + (k1 * 3 + jj) * EN + e;   // Pi_{k1, j}, differenced along k2
-            const double* pb = pi + (k2 * 3 + jj) * EN + e;   // Pi_{k2, j}, differenced along k1
-            double ta = 0.0, tb = 0.0;
-#pragma unroll
-            for (int n = 1; n <= NG_MAX; ++n) {
-                if (n > g.p) break;
-                const double a = 0.5 * alpha_pn(g.p, n);
-                ta += a * (pa[n * st[k2]] - pa[-n * st[k2]]);
-                tb += a * (pb[n * st[k1]] - pb[-n * st[k1]]);
-            }
-            m[kk][jj] = (ta - tb) / (g.dxi[k1] * g.dxi[k2]);
-        }
-    }
-#pragma unroll
-    for (int kk = 0; kk < 3; ++kk) {
-        double at = 0.0;
-        if (ve != nullptr) {
-#pragma unroll
-            for (int jj = 0; jj < 3; ++jj) at -= ve[jj * EN + e] * m[kk][jj];
-        }
-        met[(kk * 4) * P + t] = at;
-#pragma unroll
-        for (int jj = 0; jj < 3; ++jj) met[(kk * 4 + 1 + jj) * P + t] = m[kk][jj];
-    }
-    if (J0 != nullptr && i >= 0 && i < g.n[0] && j >= 0 && j < g.n[1] && k >= 0 && k < g.n[2]) {
-        // J = sum_k (J dxi_k/dx_1) delta_k[x_1] / dxi_k
-        double Jv = 0.0;
-#pragma unroll
-        for (int kk = 0; kk < 3; ++kk) {
-            double d = 0.0;
-#pragma unroll
-            for (int n = 1; n <= NG_MAX; ++n)
-                if (n <= g.p) d += 0.5 * alpha_pn(g.p, n) * (xe[e + n * st[kk]] - xe[e - n * st[kk]]);
-            Jv += m[kk][0] * d / g.dxi[kk];
-        }
-        J0[iidx(g, i, j, k)] = Jv;
-    }
-}
-
+// J dxi_k/dx_j = (delta_{k+2}[Pi_{k+1,j}] - delta_{k+1}[Pi_{k+2,j}]) / (dxi_{k+1} dxi_{k+2}).
+//
 // The 3D metric differences in one pass after the stage mesh is extended: from the
 // extended stage mesh (and mesh velocity) straight to the 12 padded metric
-// components, the CMM products (eq. SCLCoeff) formed on the fly instead of in HBM.
+// components, the products formed on the fly instead of in HBM, and with JAC the Jacobian J^0 = sum_k (J dxi_k/dx_1) delta_k[x_1] / dxi_k of the interior nodes
+// as well (x_1's differences are those the products take).
 // A block owns a 16 x 16 tile of padded (i, j) columns and marches through kz
 // planes, with three threads per column, one per mesh component c (and, for the
 // products Pi_{a,jj}, one per jj = c).  Each thread keeps its component of the stage
@@ -399,13 +316,13 @@ __global__ void k_metrics3d(GridDev g, const double* __restrict__ xe, const doub
 // Pi_{0,.} (tile and xi_2 strips) and Pi_{1,.} (tile and xi_1 strips) at the centre
 // plane; the temporal part J dxi_k/dt = -sum_jj xdot_jj (J dxi_k/dx_jj) is summed
 // from the row of spatial metrics left in LDS, at the start of the next plane.  The
-// sums (in n order), the products and the temporal sum (in jj order) are those of
-// k_cmm_products + k_metrics3d; the metric differences are scaled by the reciprocal
-// of dxi_{k+1} dxi_{k+2}.  Every global load of a plane is issued one plane ahead,
-// from clamped (always valid) addresses and outside any branch, so that its wait
-// falls in the next plane.  The kernel is bound by LDS traffic (about 1.5 KB per
+// metric differences are scaled by the reciprocal of dxi_{k+1}
+// dxi_{k+2}.  Every global load of a plane is issued one plane ahead, from clamped
+// (always valid) addresses and outside any branch, so that its wait falls in the next
+// plane.  The kernel is bound by LDS traffic (about 1.5 KB per
 // node and plane); the three-kernel form it replaces (products in HBM, then a
-// marching difference kernel reading them through L1/L2) took about twice as long.
+// marching difference kernel reading them through L1/L2) took about twice as long
+// (128^3 with J^0, mesh extension and U(P): 479 us, 210 here).
 constexpr int MT = 16;
 constexpr int MT_THREADS = 3 * MT * MT;
 
@@ -426,11 +343,11 @@ __device__ __forceinline__ long long eidx_clamped(const GridDev& g, int i, int j
     return eidx(g, min(max(i, -e), g.n[0] + e - 1), min(max(j, -e), g.n[1] + e - 1), 0);
 }
 
-template <int H>
+template <int H, bool JAC>
 __global__ void __launch_bounds__(MT_THREADS) k_metrics3d_tile(GridDev g, const double* __restrict__ xe,
                                                                const double* __restrict__ ve,
-                                                               double* __restrict__ met, int kz, int tiles0,
-                                                               int tiles1) {
+                                                               double* __restrict__ met, double* __restrict__ J0,
+                                                               int kz, int tiles0, int tiles1) {
     constexpr int NCROSS = 4 * H * MT;
     constexpr int NCORNER = 4 * H * H;
     static_assert(NCROSS <= MT * MT && NCORNER <= MT * MT, "one halo position of each kind per thread");
@@ -604,6 +521,16 @@ __global__ void __launch_bounds__(MT_THREADS) k_metrics3d_tile(GridDev g, const 
             __builtin_nontemporal_store(m0, &met[(0 * 4 + 1 + c) * P + tout]);
             __builtin_nontemporal_store(m1, &met[(1 * 4 + 1 + c) * P + tout]);
             __builtin_nontemporal_store(m2, &met[(2 * 4 + 1 + c) * P + tout]);
+            if (JAC && c == 0 && oi >= 0 && oi < g.n[0] && oj >= 0 && oj < g.n[1] && k >= 0 && k < g.n[2]) {
+                double d0 = 0.0, d1 = 0.0, d2 = 0.0;
+#pragma unroll
+                for (int n = 1; n <= H; ++n) {
+                    d0 += a[n] * (sm.xc[0][H + ty][H + tx + n] - sm.xc[0][H + ty][H + tx - n]);
+                    d1 += a[n] * (sm.xc[0][H + ty + n][H + tx] - sm.xc[0][H + ty - n][H + tx]);
+                    d2 += a[n] * (wo[H + n] - wo[H - n]);
+                }
+                J0[iidx(g, oi, oj, k)] = m0 * d0 / g.dxi[0] + m1 * d1 / g.dxi[1] + m2 * d2 / g.dxi[2];
+            }
         }
         if (centre) {
             tout += tz;
@@ -1829,6 +1756,16 @@ hipError_t launch_temporal_metrics3d(const es_ctx* c, const double* xdot, double
     return hipGetLastError();
 }
 
+template <int H>
+static void metrics3d_tile(const es_ctx* c, const double* ve, double* met, double* J0, hipStream_t s) {
+    const GridDev& g = c->g;
+    const int t0 = (g.P[0] + MT - 1) / MT, t1 = (g.P[1] + MT - 1) / MT;
+    const int kz = metric_tile_planes(g);
+    const unsigned nb = (unsigned)(t0 * t1 * ((g.P[2] + kz - 1) / kz));
+    if (J0 != nullptr) k_metrics3d_tile<H, true><<<nb, MT_THREADS, 0, s>>>(g, c->xe, ve, met, J0, kz, t0, t1);
+    else k_metrics3d_tile<H, false><<<nb, MT_THREADS, 0, s>>>(g, c->xe, ve, met, nullptr, kz, t0, t1);
+}
+
 hipError_t launch_metrics(const es_ctx* c, const double* x, const double* xdot,
                           const double* dt_dev, double coef, double* met, double* J0,
                           hipStream_t s, bool ve_ready) {
@@ -1840,20 +1777,10 @@ hipError_t launch_metrics(const es_ctx* c, const double* x, const double* xdot,
         const dim3 gm((unsigned)((g.P[0] + MTX - 1) / MTX), (unsigned)((g.P[1] + MTY - 1) / MTY), 1);
         k_metrics2d_fused<<<gm, dim3(MTX, MBY, 1), 0, s>>>(g, x, xdot, dt_dev, coef, met, J0);
     } else {
-        if (J0 != nullptr) {
-            // with the Jacobian J^0 (set-up, not a stage): extended mesh and products in HBM
-            k_mesh_extend<3><<<ge, TPB, 0, s>>>(g, x, xdot, dt_dev, coef, c->xe, ve);
-            k_cmm_products<<<ge, TPB, 0, s>>>(g, c->xe, c->pi);
-            k_metrics3d<<<box_grid(g.P[0], g.P[1], g.P[2]), box_block(), 0, s>>>(g, c->xe, ve, c->pi, met, J0);
-        } else {
-            // the extended mesh velocity is left in c->ve by an earlier call with the same xdot
-            k_mesh_extend<3><<<ge, TPB, 0, s>>>(g, x, xdot, dt_dev, coef, c->xe, ve_ready ? nullptr : ve);
-            const int t0 = (g.P[0] + MT - 1) / MT, t1 = (g.P[1] + MT - 1) / MT;
-            const int kz = metric_tile_planes(g);
-            const unsigned nb = (unsigned)(t0 * t1 * ((g.P[2] + kz - 1) / kz));
-            if (g.ng == 4) k_metrics3d_tile<4><<<nb, MT_THREADS, 0, s>>>(g, c->xe, ve, met, kz, t0, t1);
-            else k_metrics3d_tile<3><<<nb, MT_THREADS, 0, s>>>(g, c->xe, ve, met, kz, t0, t1);
-        }
+        // the extended mesh velocity is left in c->ve by an earlier call with the same xdot
+        k_mesh_extend<3><<<ge, TPB, 0, s>>>(g, x, xdot, dt_dev, coef, c->xe, ve_ready ? nullptr : ve);
+        if (g.ng == 4) metrics3d_tile<4>(c, ve, met, J0, s);
+        else metrics3d_tile<3>(c, ve, met, J0, s);
     }
     return hipGetLastError();
 }
