@@ -96,12 +96,12 @@ __global__ void k_con2prim_rhd(GridDev g, double G, StateSrc ss, double* prim, i
         for (int c = 0; c < M; ++c) ss.Uout[c * N + src] = Uc[c];
         ss.Jout[src] = Uc[M];
     }
-    const double Jv = Uc[M];
-    const double D = Uc[0] / Jv;
+    const double Jv = Uc[M], iJ = frcp(Jv);
+    const double D = quotient(Uc[0], Jv, iJ);
     double m[DIM];
 #pragma unroll
-    for (int c = 0; c < DIM; ++c) m[c] = Uc[1 + c] / Jv;
-    const double E = Uc[M - 1] / Jv;
+    for (int c = 0; c < DIM; ++c) m[c] = quotient(Uc[1 + c], Jv, iJ);
+    const double E = quotient(Uc[M - 1], Jv, iJ);
     double rho, p, u[DIM];
     const double guess = use_guess ? prim[(M - 1) * P + t] : -1.0;
     // a non-positive (or non-finite) Jacobian is a tangled mesh: recorded as such
@@ -302,8 +302,9 @@ __global__ void __launch_bounds__(MTX * MSY) k_metrics2d_stages(GridDev g, const
 //
 // The 3D metric differences in one pass after the stage mesh is extended: from the
 // extended stage mesh (and mesh velocity) straight to the 12 padded metric
-// components, the products formed on the fly instead of in HBM, and with JAC the Jacobian J^0 = sum_k (J dxi_k/dx_1) delta_k[x_1] / dxi_k of the interior nodes
-// as well (x_1's differences are those the products take).
+// components, the products formed on the fly instead of in HBM, and with JAC the
+// Jacobian J^0 = sum_k (J dxi_k/dx_1) delta_k[x_1] / dxi_k of the interior nodes as well
+// (x_1's differences are those the products take).
 // A block owns a 16 x 16 tile of padded (i, j) columns and marches through kz
 // planes, with three threads per column, one per mesh component c (and, for the
 // products Pi_{a,jj}, one per jj = c).  Each thread keeps its component of the stage
