@@ -50,12 +50,12 @@ PEAK_HBM = 8.0e12                # B/s
 # preparation (6) and the flux-difference accumulation (66): 1269.1; two directions: 2538.2.
 # 3D RHD ES: 1640.6 per direction, 4921.7 for the three.  RMHD ES, p = 3 (the
 # face eigen-structure dominates: about 13,700 per face; averaged over
-# smooth states with well-separated eigenvalues): 30482.9 per node in 2D, 46611.9
+# smooth states with well-separated eigenvalues): 29150.9 per node in 2D, 43857.9
 # in 3D.
 RESIDUAL_FLOPS_PER_NODE_2D_RHD = 2538.2
 RESIDUAL_FLOPS_PER_NODE_3D_RHD = 4921.7
-RESIDUAL_FLOPS_PER_NODE_2D_RMHD = 30482.9
-RESIDUAL_FLOPS_PER_NODE_3D_RMHD = 46611.9
+RESIDUAL_FLOPS_PER_NODE_2D_RMHD = 29150.9
+RESIDUAL_FLOPS_PER_NODE_3D_RMHD = 43857.9
 
 # HBM bytes of one es_residual call, from the FETCH_SIZE and WRITE_SIZE counters
 # (rocprofv3 --pmc, one counter per run) of the residual kernel and k_sum_dirs,
