@@ -63,9 +63,9 @@ RESIDUAL_FLOPS_PER_NODE_3D_RMHD = 43857.9
 # WRITE x 1.000).  Valid for the kernels as they were measured; the summaries
 # with their commands are the es_residual_hbm_counters_* files under profiles/.
 RESIDUAL_TRAFFIC_BYTES = {
-    "rhd2d_quadrant_riemann_400_seed2": 57.85e6,
-    "rhd3d_blast_128": 1329.3e6,
-    "rmhd2d_rotor_512": 1483.2e6,
+    "rhd2d_quadrant_riemann_400_seed2": 57.69e6,
+    "rhd3d_blast_128": 1314.4e6,
+    "rmhd2d_rotor_512": 2111.9e6,
 }
 
 

@@ -96,12 +96,12 @@ __global__ void k_con2prim_rhd(GridDev g, double G, StateSrc ss, double* prim, i
         for (int c = 0; c < M; ++c) ss.Uout[c * N + src] = Uc[c];
         ss.Jout[src] = Uc[M];
     }
-    const double Jv = Uc[M], iJ = frcp(Jv);
-    const double D = quotient(Uc[0], Jv, iJ);
+    const double Jv = Uc[M];
+    const double D = Uc[0] / Jv;
     double m[DIM];
 #pragma unroll
-    for (int c = 0; c < DIM; ++c) m[c] = quotient(Uc[1 + c], Jv, iJ);
-    const double E = quotient(Uc[M - 1], Jv, iJ);
+    for (int c = 0; c < DIM; ++c) m[c] = Uc[1 + c] / Jv;
+    const double E = Uc[M - 1] / Jv;
     double rho, p, u[DIM];
     const double guess = use_guess ? prim[(M - 1) * P + t] : -1.0;
     // a non-positive (or non-finite) Jacobian is a tangled mesh: recorded as such

@@ -75,12 +75,6 @@ __device__ __forceinline__ double fdiv(double a, double b) {
 #endif
 }
 
-// a / b given the reciprocal r of b, rounded as the division is (to the last place or so).
-__device__ __forceinline__ double quotient(double a, double b, double r) {
-    const double q = a * r;
-    return fma(fma(-b, q, a), r, q);
-}
-
 // Logarithmic mean [a]/[ln a] (cited in Section 3.1 to Ismail & Roe) from the
 // values and their precomputed logarithms.  With f = (al - ar)/(al + ar) and
 // u = f^2 it is (al + ar)/2 times f/artanh(f): for u < 1e-2 the series of that
@@ -389,9 +383,7 @@ __device__ __forceinline__ void pair_flux_rhd_mixed(double G, const NodeRHD<NU>&
 // (0, (G-1)E] for admissible states D > 0, E > sqrt(D^2 + |m|^2).
 // The iteration starts from ``guess`` when it lies inside the bracket, else
 // from the bracket midpoint.  Returns 0 on success, 1 for an inadmissible state,
-// 2 without convergence.  An iteration is a serial chain, and on small grids that chain is
-// the kernel's time: reciprocals and roots with their own steps instead of three divisions
-// and a general square root (64^2 adaptive step 95.0 -> 91.7 us).
+// 2 without convergence.
 template <int NU>
 __device__ __forceinline__ int c2p_rhd(double G, double D, const double* m, double E, double guess,
                                        double& rho, double* u, double& p) {
@@ -402,16 +394,15 @@ __device__ __forceinline__ int c2p_rhd(double G, double D, const double* m, doub
     double lo = 0.0, hi = (G - 1.0) * E;
     double pk = (guess > lo && guess < hi) ? guess : 0.5 * (lo + hi);
     int conv = 0;
-    // g(p), with its slope by reciprocals (the slope only steers the iteration)
-    auto newton = [&](double pv, double& gv) {
-        const double Ep = E + pv, iEp = frcp(Ep), v2 = mm2 * iEp * iEp, om = fmax(1.0 - v2, 1e-290);
-        gv = (G - 1.0) * (Ep * (1.0 - v2) - pv - D * psqrt(om)) - pv;
-        return pv - gv * frcp((G - 1.0) * v2 * (1.0 - D * iEp * frsqrt(om)) - 1.0);
-    };
     for (int it = 0; it < 200; ++it) {
-        double gv, pn = newton(pk, gv);
+        const double Ep = E + pk;
+        const double v2 = mm2 / (Ep * Ep);
+        const double sq = sqrt(1.0 - v2);
+        const double gv = (G - 1.0) * (Ep * (1.0 - v2) - pk - D * sq) - pk;
         if (gv == 0.0) { conv = 1; break; }
         if (gv > 0.0) lo = pk; else hi = pk;
+        const double dg = (G - 1.0) * v2 * (1.0 - D / (sq * Ep)) - 1.0;
+        double pn = pk - gv / dg;
         // Newton step while it stays in the bracket (end points included), else bisection
         if (!(pn >= lo && pn <= hi)) pn = 0.5 * (lo + hi);
         const double dp = fabs(pn - pk);
@@ -422,19 +413,22 @@ __device__ __forceinline__ int c2p_rhd(double G, double D, const double* m, doub
     }
     // one more Newton correction from the converged iterate
     {
-        double gv;
-        const double pn = newton(pk, gv);
+        const double Ep = E + pk;
+        const double v2 = mm2 / (Ep * Ep);
+        const double sq = sqrt(1.0 - v2);
+        const double gv = (G - 1.0) * (Ep * (1.0 - v2) - pk - D * sq) - pk;
+        const double dg = (G - 1.0) * v2 * (1.0 - D / (sq * Ep)) - 1.0;
+        const double pn = pk - gv / dg;
         if (pn > 0.0) pk = pn;
     }
     p = pk;
-    const double iEp = frcp(E + pk);
+    const double iEp = 1.0 / (E + pk);
     double v2 = 0.0;
     double v[NU];
 #pragma unroll
     for (int k = 0; k < NU; ++k) { v[k] = m[k] * iEp; v2 += v[k] * v[k]; }
-    const double om = 1.0 - v2;
-    const double W = om > 0.0 ? frsqrt(om) : 1.0 / sqrt(om);
-    rho = om > 0.0 ? D * psqrt(om) : D / W;
+    const double W = 1.0 / sqrt(1.0 - v2);
+    rho = D / W;
 #pragma unroll
     for (int k = 0; k < NU; ++k) u[k] = W * v[k];
     return conv ? 0 : 2;
